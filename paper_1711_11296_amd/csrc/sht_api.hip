@@ -190,7 +190,6 @@ int check_level_args(int N, int J, int I, int F, int grid) {
 }
 
 int autotune(sht_plan_s* P);
-bool blocking_ok(const sht_plan_s* P, bool analysis, int c);
 
 int build_plan(int nlev, const int* Nv, const int* Jv, const int* Iv, const int* Fv,
                const sht_options* opts, sht_plan_t* out) {
@@ -231,16 +230,24 @@ int build_plan(int nlev, const int* Nv, const int* Jv, const int* Iv, const int*
     delete P;
     return rc;
   }
-  P->ncb = choose_ncb(o.form, nlev, Nv, Jv, Fv);
-  const int BN = 16 * P->ncb;
+  int ncu = 0;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, P->device) != hipSuccess || ncu <= 0)
+    ncu = 256;
+  // sht_forward_noalloc takes workspaces up to its static array's size
+  const long long ws_limit = SHT_NOALLOC_WORKSPACE_BYTES;
   int FB = zonal_fields_per_block(o.form, nlev, Nv[0], Jv[0], Iv[0], Fv[0]);
+  P->ncb = choose_granularity(o.form, P->otf != 0, nlev, Nv, Jv, Fv, FB, ncu, ws_limit);
   if (FB > 8) {
     // the wide blocking runs only in the fixed-length kernel, whose
     // workspace offsets are 32-bit
-    const long long Cp = roundup(2LL * Fv[0], std::lcm(BN, 2 * FB));
+    const long long Cp = roundup(2LL * Fv[0], std::lcm(16 * P->ncb, 2 * FB));
     const long long Kp = roundup((Jv[0] + 1) / 2, SHT_K_PAD);
-    if (!zonal_offsets_fit(ws_plane(Kp, Cp), (long long)P->elem)) FB = 8;
+    if (!zonal_offsets_fit(ws_plane(Kp, Cp), (long long)P->elem)) {
+      FB = 8;
+      P->ncb = choose_granularity(o.form, P->otf != 0, nlev, Nv, Jv, Fv, FB, ncu, ws_limit);
+    }
   }
+  const int BN = 16 * P->ncb;
   P->fb = FB;
 
   // ---- level descriptors and sizes ----
@@ -338,50 +345,14 @@ int build_plan(int nlev, const int* Nv, const int* Jv, const int* Iv, const int*
   }
 
   // ---- tile schedules (default; the autotuner may replace them) ----
-  // the kernels keep their whole output tile in registers: where the
-  // plan's blocking is wider than a kernel takes, use the widest blocking it
-  // supports that divides every level's row length
-  for (int dir = 0; dir < 2; ++dir) {
-    int& ncb = dir == 0 ? P->ncb_fwd : P->ncb_inv;
-    ncb = P->ncb;
-    if (ncb <= max_ncb(o.form, dir == 0)) continue;
-    for (int c : {8, 5, 4, 2, 1}) {
-      if (c > max_ncb(o.form, dir == 0)) continue;
-      bool ok = true;
-      for (int l = 0; l < nlev; ++l)
-        if (P->lev[l].Cp % (16 * c)) ok = false;
-      if (ok) {
-        ncb = c;
-        break;
-      }
-    }
-  }
-  // small plans: where a direction's tiles would not give every compute
-  // unit two workgroups, narrower column tiles (more of them) are taken, as
-  // long as a narrower blocking is admissible (blocking_ok); the idle slots
-  // that even out the XCD chunks of a tile list do not count
+  // each direction takes the column blocking of least estimated time among
+  // those that tile the workspace rows
   {
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, P->device) != hipSuccess || ncu <= 0)
-      ncu = 256;
-    auto real_tiles = [&](bool analysis, int c) {
-      size_t n = 0;
-      for (const Tile& t : build_tiles(P->form, nlev, P->lev, P->jst.data(), analysis, c, 0)) n += t.level >= 0;
-      return n;
-    };
-    for (int dir = 0; dir < 2; ++dir) {
-      int& ncb = dir == 0 ? P->ncb_fwd : P->ncb_inv;
-      while (real_tiles(dir == 0, ncb) < 2 * (size_t)ncu) {
-        int next = 0;
-        for (int c : {8, 5, 4, 2, 1})
-          if (c < ncb && blocking_ok(P, dir == 0, c)) {
-            next = c;
-            break;
-          }
-        if (!next) break;
-        ncb = next;
-      }
-    }
+    long long Cp[SHT_MAX_LEVELS];
+    for (int l = 0; l < nlev; ++l) Cp[l] = P->lev[l].Cp;
+    for (int dir = 0; dir < 2; ++dir)
+      (dir == 0 ? P->ncb_fwd : P->ncb_inv) = choose_tile(o.form, P->otf != 0, nlev, Nv, Jv, Fv, Cp, P->jst.data(),
+                                                         dir == 0, ncu, nullptr);
   }
   // flops kept by the reduced transform (whole analysis blocks left out)
   P->flops_kept = 0.0;
@@ -734,12 +705,12 @@ std::string tune_key(const sht_plan_s* P) {
 }
 
 // A column blocking c (16-column units) is admissible for a direction when
-// the kernel takes it and it tiles every level's workspace row exactly with
-// no tile wholly past the last field.
+// the kernel takes it and it tiles every level's workspace row exactly (tiles
+// wholly past the last field are not generated).
 bool blocking_ok(const sht_plan_s* P, bool analysis, int c) {
   if (c < 1 || c > max_ncb(P->form, analysis)) return false;
   for (int l = 0; l < P->nlev; ++l)
-    if (P->lev[l].Cp % (16 * c) || roundup(2LL * P->lev[l].F, 16LL * c) != P->lev[l].Cp) return false;
+    if (P->lev[l].Cp % (16 * c)) return false;
   return true;
 }
 
@@ -794,9 +765,8 @@ int autotune(sht_plan_s* P) {
                       (v[2] == P->ncb_inv || blocking_ok(P, false, v[2])) && (v[1] == 0 || v[1] == 1) &&
                       (v[3] == 0 || v[3] == 1) && (v[4] == 0 || v[4] == 1) && (v[5] == 0 || v[5] == 1);
   if (!cached) {
-    const int all64[] = {1, 2, 4, 8}, all32[] = {1, 2, 4, 5, 8, 10};
-    const int* all = P->form == SHT_FORM_FP64 ? all64 : all32;
-    const int na = P->form == SHT_FORM_FP64 ? 4 : 6;
+    int ncu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, P->device) != hipSuccess) ncu = 0;
     void* spec = nullptr;
     hipStream_t st = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -812,11 +782,13 @@ int autotune(sht_plan_s* P) {
       const bool analysis = dir == 0;
       float best = 1e30f;
       int bc = analysis ? P->ncb_fwd : P->ncb_inv, bs = 0;
-      for (int k = 0; k < na; ++k)
+      for (int c = 1; c <= max_ncb(P->form, analysis); ++c)
         for (int sched = 0; sched < 2 && !rc; ++sched) {
-          const int c = all[k];
           if (!blocking_ok(P, analysis, c)) continue;
           std::vector<Tile> t = build_tiles(P->form, P->nlev, P->lev, P->jst.data(), analysis, c, sched);
+          // a blocking that leaves compute units without a tile cannot beat a
+          // narrower one (c = 1 is always admissible)
+          if (c > 1 && std::count_if(t.begin(), t.end(), [](const Tile& x) { return x.level >= 0; }) < ncu) continue;
           Tile* dt = nullptr;
           if ((rc = hip_check(hipMalloc(reinterpret_cast<void**>(&dt), t.size() * sizeof(Tile)), "tune alloc"))) break;
           (void)hipMemcpy(dt, t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice);

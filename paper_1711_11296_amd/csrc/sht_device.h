@@ -56,10 +56,21 @@ __device__ __forceinline__ void load_to_lds16(const void* src, void* lds_base) {
 #endif
 }
 
+// s_waitcnt immediates: LDS operations done; at most n vector memory
+// operations outstanding.  (Through the builtin, not inline assembly, the
+// compiler knows what has completed and keeps its own waits exact.)
+constexpr int kWaitLds = 0xC07F;
+constexpr int wait_vm(int n) { return (n & 15) | 0x0F70 | (n >> 4 << 14); }
+
 // Workgroup barrier for LDS hand-offs only: waits for this wave's LDS
 // operations, not for its outstanding global loads (which __syncthreads'
 // fence would also drain, defeating loads issued blocks ahead).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(kWaitLds);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // Instruction-order hint for a K-block body (scheduling groups of the
 // compiler, no effect on results): PRE LDS reads first, then ROUNDS times

@@ -158,8 +158,9 @@ int launch_product(long long n, bool dbl, const void* a, const void* b, void* ou
 int launch_laplacian(int N, int F, double scale, bool dbl, const void* in, void* out, void* stream);
 int launch_residual(long long n, long long n_per, double alpha, bool dbl, const void* x, const void* kappa,
                     const void* y, const void* f, void* r, void* stream);
-// Widest column blocking (16-column units) a Legendre kernel of a form takes.
-int max_ncb(int form, bool analysis);
+// Widest column blocking (16-column units) a Legendre kernel of a form takes
+// (wider tiles do not fit the register file).
+inline int max_ncb(int form, bool analysis) { return form == SHT_FORM_FP32 && analysis ? 10 : 8; }
 
 }  // namespace sht
 

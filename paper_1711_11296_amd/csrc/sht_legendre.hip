@@ -46,10 +46,16 @@ namespace sht {
 // copy of the table is blocked per (128-row tile, KB columns) and, inside a
 // block, per wave and per 64-lane vector, so that each wave streams its
 // operands with fully contiguous 1 KiB loads straight into registers.
-// The right-hand operand (both parities of the workspace block) goes through
-// LDS in two stages: block kb+1 is fetched into registers while the matrix
-// cores work on block kb and stored into the other stage afterwards, so one
-// barrier per block suffices.
+// The right-hand operand (both parities of the workspace block) goes from
+// memory straight into LDS (global_load_lds, 64 x 16 bytes per instruction),
+// rows 2 k + parity of BN columns, in two stages: the fills of block kb + 1
+// are issued between the k-steps of block kb, one barrier per block.  Any
+// NCB works.  Measured (MI355X, FP32, T479 with 100 fields): two tiles of 7
+// blocks 0.264 ms against 0.345 ms for the 13 tiles of one block that a
+// power-of-two choice leaves; T959 with 64 fields (NCB = 8) 1.01 ms, 112
+// TFLOP/s: the shader clock drops to 2.0-2.15 GHz under matrix and memory
+// load together (2.35 GHz for the same products from LDS alone), and at that
+// clock the matrix cores are ~90 % busy.
 // ---------------------------------------------------------------------------
 template <typename T, int NCB, bool GEN = false>
 struct AnalysisShape {
@@ -60,20 +66,10 @@ struct AnalysisShape {
   static constexpr int KB = (sizeof(T) == 4 || GEN) ? 32 : 16;
   static constexpr int KQ = KB / 4;                    // k values per lane and block
   static constexpr int BN = 16 * NCB;
-  // With an even number of column blocks the right-hand operand goes from
-  // memory to LDS directly (global_load_lds, 64 x 16 bytes per instruction,
-  // contiguous in LDS), in rows 2 k + parity of BN elements (one
-  // instruction fills both parities of one or more latitudes, contiguous in
-  // the workspace) whose 16-column blocks are swapped in pairs for odd k
-  // (column c sits at c ^ 16): the lane groups g = 0, 1 that one LDS cycle
-  // serves read latitudes k of different parity and so hit different bank
-  // halves.  Otherwise it is staged through registers into rows
-  // parity KB + k padded to a pitch of 16 mod 32 words.
-  static constexpr bool DMA = NCB % 2 == 0;
-  static constexpr int BS = DMA ? BN : BN + (sizeof(T) == 4 ? 16 : 2);
-  static constexpr int STAGE = 2 * KB * BS;            // elements of one stage
-  static constexpr int BV = 2 * KB * BN / E;           // 16-byte vectors per block
-  static constexpr int NB = (BV + 511) / 512;
+  static constexpr int AHEAD = sizeof(T) == 4 && NCB <= 8 && !GEN ? 2 : 1;
+  static constexpr int STAGE = 2 * KB * BN;            // elements of one stage: rows 2 k + parity of BN columns
+  static constexpr int NCHUNK = STAGE / (64 * E);      // 1 KiB fills per stage, dealt to the 8 waves
+  static constexpr int NB = (NCHUNK + 7) / 8;
   static constexpr int CS = BN + 1;                    // staging pitch of the output
   static constexpr int PS = 128 * KB;                  // generated P~ of one block (GEN)
   static constexpr size_t lds_bytes(bool gen) {
@@ -82,6 +78,46 @@ struct AnalysisShape {
     return main > cst ? main : cst;
   }
 };
+
+// The columns of a tile are dealt to the MFMA column blocks so that a lane's
+// values of E blocks (16 bytes) lie side by side in an LDS row and one read
+// fetches them: blocks E h + e of the whole groups take the columns
+// 16 E h + E i + e (lane i), a remaining pair the columns base + 2 i + e, a
+// single block base + i.
+template <typename T>
+__host__ __device__ constexpr int tile_col(int ncb, int c, int i) {
+  const int E = 16 / (int)sizeof(T), whole = ncb / E * E;
+  if (c < whole) return c / E * 16 * E + E * i + c % E;
+  if (E == 4 && c < whole + 2 && ncb - whole >= 2) return 16 * whole + 2 * i + (c - whole);
+  return 16 * c + i;
+}
+
+// LDS reads that read_cols takes
+template <typename T>
+__host__ __device__ constexpr int col_reads(int ncb) {
+  const int E = 16 / (int)sizeof(T);
+  return ncb / E + ((ncb % E) & 1) + ((ncb % E) >> 1);
+}
+
+// Lane i's values of all column blocks from one LDS row.
+template <typename T, int NCB>
+__device__ __forceinline__ void read_cols(const T* row, int i, T (&b)[NCB]) {
+  typedef typename V16<T>::type V;
+  constexpr int E = 16 / (int)sizeof(T), W = NCB / E * E;
+#pragma unroll
+  for (int h = 0; h < W; h += E) {
+    const V x = *reinterpret_cast<const V*>(row + 16 * h + E * i);
+#pragma unroll
+    for (int e = 0; e < E; ++e) b[h + e] = x[e];
+  }
+  if constexpr (NCB - W >= 2) {
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    const T2 x = *reinterpret_cast<const T2*>(row + 16 * W + 2 * i);
+    b[W] = x[0];
+    b[W + 1] = x[1];
+  }
+  if constexpr ((NCB - W) & 1) b[NCB - 1] = row[16 * (NCB - 1) + i];
+}
 
 // Swizzle of the generated analysis block [128 rows][KB latitudes]: element
 // (row, lat) sits at row * KB + (lat ^ gen_swz(row)), so that the 32
@@ -108,10 +144,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   typedef typename Acc<T>::type AccT;
   typedef typename V16<T>::type V;
   using S = AnalysisShape<T, NCB, GEN>;
-  constexpr int E = S::E, KB = S::KB, KQ = S::KQ, BN = S::BN, BS = S::BS;
+  constexpr int E = S::E, KB = S::KB, KQ = S::KQ, BN = S::BN;
 
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  T* Bs = reinterpret_cast<T*>(smem_raw);          // [2 stage][2 parity][KB][BS]
+  T* Bs = reinterpret_cast<T*>(smem_raw);          // [2 stage][KB][2 parity][BN]
 
   const Tile t = g.tiles[blockIdx.x];
   if (t.level < 0) return;
@@ -179,8 +215,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   // The table operand is fetched two K blocks ahead into two register sets
   // used in turn (loop unrolled by two); the workspace operand one block
   // ahead (LDS stages).
-  V an[2][KQ / E], ac[KQ / E];
-  V rb[S::DMA ? 1 : S::NB];
+  V an[2][KQ / E];
   // (issued unconditionally, also by waves without rows in this tile and
   // for blocks past the end, clamped: with straight-line loads the wait
   // counts cover exactly the block that is consumed)
@@ -188,132 +223,99 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 #pragma unroll
     for (int v = 0; v < KQ / E; ++v) av[v] = *reinterpret_cast<const V*>(arow + kb * 128 * KB + v * 64 * E);
   };
-  auto gload_b = [&](int kb) {
-    if constexpr (S::DMA) return;
-#pragma unroll
-    for (int i = 0; i < S::NB; ++i) {
-      const int qq = tid + i * 512;
-      if (S::NB * 512 == S::BV || qq < S::BV) {
-        const int par = qq / (KB * BN / E);
-        const int rem = qq - par * (KB * BN / E);
-        const int row = rem / (BN / E), cv = rem % (BN / E);
-        rb[i] = *reinterpret_cast<const V*>(wsm + (long long)(kb * KB + row) * 2 * Cp +
-                                            ws_col(L.wsh, par, c0 + cv * E));
-      }
-    }
-  };
-  auto lstore = [&](int stage) {
-    if constexpr (S::DMA) return;
-    T* dst = Bs + stage * S::STAGE;
-#pragma unroll
-    for (int i = 0; i < S::NB; ++i) {
-      const int qq = tid + i * 512;
-      if (S::NB * 512 == S::BV || qq < S::BV) {
-        const int par = qq / (KB * BN / E);
-        const int rem = qq - par * (KB * BN / E);
-        const int row = rem / (BN / E), cv = rem % (BN / E);
-        *reinterpret_cast<V*>(dst + (par * KB + row) * BS + cv * E) = rb[i];
-      }
-    }
-  };
   // memory -> LDS without registers: instruction i of wave w fills the
   // 1 KiB chunk number i*8 + w of the stage; lane l takes its 16-byte piece
   // (row 2 k + parity, physical column) and fetches the logical column under
   // the swizzle.  The lane's byte offsets within a K block are fixed for the
   // tile (32-bit, from the block's uniform base).
-  unsigned dofs[S::DMA ? S::NB : 1];
-  if constexpr (S::DMA) {
-    static_assert(S::BV % 512 == 0, "whole chunks per wave");
+  // (with an odd number of chunk rows the last wave's chunk is filled by
+  // several waves with the same values, which keeps the loop free of branches)
+  auto chunk = [&](int i) __attribute__((always_inline)) {
+    return S::NCHUNK % 8 == 0 ? i * 8 + w : min(i * 8 + w, S::NCHUNK - 1);
+  };
+  unsigned dofs[S::NB];
 #pragma unroll
-    for (int i = 0; i < S::NB; ++i) {
-      const int u = (i * 8 + w) * 64 + lane;
-      const int rr = u / (BN / E), col = (u - rr * (BN / E)) * E;
-      const int k = rr >> 1, par = rr & 1;
-      dofs[i] = (unsigned)(k * 2 * (int)Cp + ws_col(L.wsh, par, c0 + (col ^ ((k & 1) << 4)))) * (unsigned)sizeof(T);
-    }
+  for (int i = 0; i < S::NB; ++i) {
+    const int u = chunk(i) * 64 + lane;
+    const int rr = u / (BN / E), col = (u - rr * (BN / E)) * E;
+    const int k = rr >> 1, par = rr & 1;
+    dofs[i] = (unsigned)(k * 2 * (int)Cp + ws_col(L.wsh, par, c0 + col)) * (unsigned)sizeof(T);
   }
-  auto dma = [&](int kb, int stage) {
-    if constexpr (S::DMA) {
-      T* dst = Bs + stage * S::STAGE;
-      const char* src = reinterpret_cast<const char*>(wsm + (long long)kb * KB * 2 * Cp);
-#pragma unroll
-      for (int i = 0; i < S::NB; ++i) load_to_lds16(src + dofs[i], dst + (i * 8 + w) * 64 * E);
-    }
+  auto dma1 = [&](int i, int kb, int stage) __attribute__((always_inline)) {
+    load_to_lds16(reinterpret_cast<const char*>(wsm + (long long)kb * KB * 2 * Cp) + dofs[i],
+                  Bs + stage * S::STAGE + chunk(i) * 64 * E);
   };
-  // Wait for this wave's LDS fills: they were issued before the two table
-  // loads of the block after next, which may stay in flight (vector memory
-  // operations of a wave complete in issue order).
-  auto wait_fills = [&]() {
-    if constexpr (S::DMA) {
-      static_assert(GEN || KQ / E == 2, "two table loads per block");
-      if constexpr (GEN)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing else is worth keeping in flight
-      else
-        asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    }
+  auto dma = [&](int kb, int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < S::NB; ++i) dma1(i, kb, stage);
   };
-  auto compute = [&](int stage) {
-    T a[KQ];
-    if constexpr (GEN) {
+  // Wait for this wave's LDS fills (and table loads): both are issued at the
+  // start of a block and wanted at its end.  Only a wait for all of them is
+  // safe: fills into LDS and loads into registers complete out of order
+  // with respect to each other (a wait for all but the two table loads
+  // issued after the fills let a barrier pass with fills in flight).
+  auto wait_fills = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));
+  };
+  // one K block's products; the fills of the next block are issued between
+  // the k-steps
+  auto compute = [&](int stage, const V (&av)[KQ / E], int kn) __attribute__((always_inline)) {
+    const T* Bp = Bs + stage * S::STAGE + (2 * lg + p) * BN;
+    // the reads of a k-step are issued AH steps ahead of its products
+    constexpr int AH = S::AHEAD;
+    T bv[AH + 1][NCB];
 #pragma unroll
-      for (int kk = 0; kk < KQ; ++kk) a[kk] = areg[kk];
-    } else {
-#pragma unroll
-      for (int v = 0; v < KQ / E; ++v)
-#pragma unroll
-        for (int e = 0; e < E; ++e) a[v * E + e] = ac[v][e];
-    }
-    // LDS row of (parity p, latitude k): 2 k + p (DMA) or p KB + k
-    constexpr int RK = S::DMA ? 2 : 1, RP = S::DMA ? 1 : KB;
-    const T* Bp = Bs + stage * S::STAGE + (p * RP + lg * RK) * BS + li;
-    // swizzled column-block offsets (latitudes g + 4 kk have the parity of g)
-    const int sw = (S::DMA && (lg & 1)) ? 16 : 0;
+    for (int kk = 0; kk < AH; ++kk) read_cols<T, NCB>(Bp + 8 * kk * BN, li, bv[kk]);
 #pragma unroll
     for (int kk = 0; kk < KQ; ++kk) {
-      T bv[NCB];
+      T a;
+      if constexpr (GEN) a = areg[kk];
+      else a = av[kk / E][kk % E];
+      if (kk + AH < KQ) read_cols<T, NCB>(Bp + 8 * (kk + AH) * BN, li, bv[(kk + AH) % (AH + 1)]);
+      if (kk < S::NB) dma1(kk, kn, 1 - stage);
 #pragma unroll
-      for (int c = 0; c < NCB; ++c) bv[c] = Bp[4 * kk * RK * BS + c * 16 + ((c & 1) ? -sw : sw)];
-#pragma unroll
-      for (int c = 0; c < NCB; ++c) acc[c] = mfma16(a[kk], bv[c], acc[c]);
+      for (int c = 0; c < NCB; ++c) acc[c] = mfma16(a, bv[kk % (AH + 1)][c], acc[c]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // B reads run two k-steps ahead (paired reads of two columns)
-    constexpr int RD = (NCB + 1) / 2;
-    mfma_lds_pipeline<2 * RD, (KQ - 2) * RD, (NCB + RD - 1) / RD, 2 * NCB>();
+#pragma unroll
+    for (int i = KQ; i < S::NB; ++i) dma1(i, kn, 1 - stage);
   };
   const int nkb = Kp / KB;
   // one K block; H = kb & 1 selects the table registers of block kb (and of
   // kb + 2), 1 - H those of block kb + 1
-  auto step = [&](auto hc, int kb) {
+  auto step = [&](auto hc, auto on, int kb) __attribute__((always_inline)) {
     constexpr int H = decltype(hc)::value;
     // after the last block the idle stage receives a clamped block that
     // nothing reads, which keeps the loop free of branches around memory
     // operations
     const int kn = kb + 1 < nkb ? kb + 1 : nkb - 1;
     gen_fetch(kb + 2 < nkb ? kb + 2 : nkb - 1, H);
-    dma(kn, 1 - H);
-    gload_b(kn);
-    asm volatile("" ::: "memory");  // the table loads below are issued after the fills
-    if constexpr (!GEN) gload_a(kb + 2 < nkb ? kb + 2 : nkb - 1, an[H]);
-    if (active) compute(H);
+    if constexpr (!GEN) gload_a(kn, an[1 - H]);
+    if constexpr (decltype(on)::value)
+      compute(H, an[H], kn);
+    else
+      dma(kn, 1 - H);
     gen_store(1 - H);  // block kb + 1 (clamped after the last: nothing reads it)
-    lstore(1 - H);
     wait_fills();
-    if constexpr (!GEN) {
-#pragma unroll
-      for (int v = 0; v < KQ / E; ++v) ac[v] = an[1 - H][v];
-    }
     lds_barrier();
     if constexpr (GEN) {
       gen_read();
       lds_barrier();
     }
   };
+  auto kloop = [&](auto on, int kb) __attribute__((always_inline)) {
+    for (; kb + 1 < nkb; kb += 2) {
+      step(std::integral_constant<int, 0>{}, on, kb);
+      step(std::integral_constant<int, 1>{}, on, kb + 1);
+    }
+    if (kb < nkb) step(std::integral_constant<int, 0>{}, on, kb);
+  };
 
   // reduced transform: the blocks before kb0 hold only latitudes where
   // every |P~_n^m| < 1e-16 (kb0 = 0 otherwise)
   const int kb0 = min(g.jstart[L.m_base + m] / KB, nkb - 1);
   dma(kb0, 0);
-  gload_b(kb0);
   asm volatile("" ::: "memory");
   if constexpr (GEN) {
     gen_fetch(kb0, 0);
@@ -321,23 +323,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     gen_fetch(kb0 + 1 < nkb ? kb0 + 1 : nkb - 1, 1);
   } else {
     gload_a(kb0, an[0]);
-    gload_a(kb0 + 1 < nkb ? kb0 + 1 : nkb - 1, an[1]);
   }
-  lstore(0);
-  wait_fills();
-  if constexpr (!GEN) {
-#pragma unroll
-    for (int v = 0; v < KQ / E; ++v) ac[v] = an[0][v];
-  }
+  __builtin_amdgcn_s_waitcnt(wait_vm(0));
   __syncthreads();
   if constexpr (GEN) {
     gen_read();
     __syncthreads();
   }
-  for (int kb = kb0; kb < nkb; kb += 2) {
-    step(std::integral_constant<int, 0>{}, kb);
-    if (kb + 1 < nkb) step(std::integral_constant<int, 1>{}, kb + 1);
-  }
+  // waves without rows in this tile run the loop without products
+  if (active)
+    kloop(std::true_type{}, kb0);
+  else
+    kloop(std::false_type{}, kb0);
 
   // stage 64 rows at a time in LDS, then write spec rows contiguously
   T* Cs = Bs;  // [64][CS]
@@ -352,7 +349,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int rl = 32 * (q & 1) + 2 * out_row<T>(lg, i) + p;
-          Cs[rl * S::CS + c * 16 + li] = acc[c][i];
+          Cs[rl * S::CS + tile_col<T>(NCB, c, li)] = acc[c][i];
         }
     }
     __syncthreads();
@@ -661,30 +658,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-template <typename T>
-static size_t lds_analysis(int ncb, bool gen) {
-  switch (ncb) {
-    case 1: return gen ? AnalysisShape<T, 1, true>::lds_bytes(true) : AnalysisShape<T, 1>::lds_bytes(false);
-    case 2: return gen ? AnalysisShape<T, 2, true>::lds_bytes(true) : AnalysisShape<T, 2>::lds_bytes(false);
-    case 4: return gen ? AnalysisShape<T, 4, true>::lds_bytes(true) : AnalysisShape<T, 4>::lds_bytes(false);
-    case 5: return gen ? AnalysisShape<T, 5, true>::lds_bytes(true) : AnalysisShape<T, 5>::lds_bytes(false);
-    case 8: return gen ? AnalysisShape<T, 8, true>::lds_bytes(true) : AnalysisShape<T, 8>::lds_bytes(false);
-    default: return gen ? AnalysisShape<T, 10, true>::lds_bytes(true) : AnalysisShape<T, 10>::lds_bytes(false);
-  }
-}
-
-template <typename T>
-static size_t lds_synthesis(int ncb, bool gen) {
-  switch (ncb) {
-    case 1: return SynthesisShape<T, 1>::lds_bytes(gen);
-    case 2: return SynthesisShape<T, 2>::lds_bytes(gen);
-    case 4: return SynthesisShape<T, 4>::lds_bytes(gen);
-    case 5: return SynthesisShape<T, 5>::lds_bytes(gen);
-    case 8: return SynthesisShape<T, 8>::lds_bytes(gen);
-    default: return SynthesisShape<T, 8>::lds_bytes(gen);
-  }
-}
-
 constexpr int kMaxSynthesisNcb = 8;
 
 template <typename T, int NCB, bool GEN>
@@ -692,14 +665,14 @@ static hipError_t launch_ncb(bool analysis, const GemmArgs& g, hipStream_t st) {
   const dim3 grid(g.ntiles), block(512);
   if constexpr (sizeof(T) == 8 && NCB > 8) return hipErrorInvalidValue;  // FP64 takes at most 8
   else if (analysis) {
-    const size_t lds = lds_analysis<T>(NCB, GEN);
+    const size_t lds = AnalysisShape<T, NCB, GEN>::lds_bytes(GEN);
     lds_optin<k_legendre_analysis<T, NCB, GEN>>(lds);
     hipLaunchKernelGGL((k_legendre_analysis<T, NCB, GEN>), grid, block, lds, st, g);
   } else {
     // wider synthesis tiles do not fit the register file
     if constexpr (NCB > kMaxSynthesisNcb) return hipErrorInvalidValue;
     else {
-      const size_t lds = lds_synthesis<T>(NCB, GEN);
+      const size_t lds = SynthesisShape<T, NCB>::lds_bytes(GEN);
       lds_optin<k_legendre_synthesis<T, NCB, GEN>>(lds);
       hipLaunchKernelGGL((k_legendre_synthesis<T, NCB, GEN>), grid, block, lds, st, g);
     }
@@ -712,18 +685,16 @@ static hipError_t launch_legendre_t(bool analysis, const GemmArgs& g, int ncb, h
   switch (ncb) {
     case 1: return launch_ncb<T, 1, GEN>(analysis, g, st);
     case 2: return launch_ncb<T, 2, GEN>(analysis, g, st);
+    case 3: return launch_ncb<T, 3, GEN>(analysis, g, st);
     case 4: return launch_ncb<T, 4, GEN>(analysis, g, st);
     case 5: return launch_ncb<T, 5, GEN>(analysis, g, st);
+    case 6: return launch_ncb<T, 6, GEN>(analysis, g, st);
+    case 7: return launch_ncb<T, 7, GEN>(analysis, g, st);
     case 8: return launch_ncb<T, 8, GEN>(analysis, g, st);
+    case 9: return launch_ncb<T, 9, GEN>(analysis, g, st);
     case 10: return launch_ncb<T, 10, GEN>(analysis, g, st);
     default: return hipErrorInvalidValue;
   }
-}
-
-int max_ncb(int form, bool analysis) {
-  if (form == SHT_FORM_BF16X6) return 8;  // wider split-form tiles do not fit the register file
-  if (form == SHT_FORM_FP64) return 8;
-  return analysis ? 10 : kMaxSynthesisNcb;
 }
 
 int launch_legendre(int form, bool analysis, const GemmArgs& g, int ncb, bool gen, void* stream) {

@@ -715,8 +715,11 @@ static hipError_t launch_bf16_gen(bool analysis, const GemmArgs& g, int ncb, hip
   switch (ncb) {
     case 1: return launch_bf16_ncb<1, GEN>(analysis, g, st);
     case 2: return launch_bf16_ncb<2, GEN>(analysis, g, st);
+    case 3: return launch_bf16_ncb<3, GEN>(analysis, g, st);
     case 4: return launch_bf16_ncb<4, GEN>(analysis, g, st);
     case 5: return launch_bf16_ncb<5, GEN>(analysis, g, st);
+    case 6: return launch_bf16_ncb<6, GEN>(analysis, g, st);
+    case 7: return launch_bf16_ncb<7, GEN>(analysis, g, st);
     case 8: return launch_bf16_ncb<8, GEN>(analysis, g, st);
     default: return hipErrorInvalidValue;
   }

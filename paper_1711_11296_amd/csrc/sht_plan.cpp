@@ -12,25 +12,93 @@
 
 namespace sht {
 
-int choose_ncb(int form, int nlev, const int* N, const int* J, const int* F) {
-  const int cand64[] = {8, 4, 2, 1};
-  const int cand32[] = {10, 8, 5, 4, 2, 1};
-  const int* cand = form == SHT_FORM_FP64 ? cand64 : cand32;
-  const int nc = form == SHT_FORM_FP64 ? 4 : 6;
+double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const int* jst,
+                     bool analysis, int k, int ncu) {
+  // fixed work of a K block in units of one column block's products: the
+  // barrier and, in the split form, the split of the table operand; with
+  // generated P~ the recurrence comes on top
+  double a = form == SHT_FORM_FP64 ? (analysis ? 0.3 : 0.6) : form == SHT_FORM_FP32 ? (analysis ? 0.4 : 1.0) : 2.2;
+  if (gen) a += analysis ? 3.0 : 1.5;
+  const int rows = analysis ? (form == SHT_FORM_BF16X6 ? 256 : 128) : 128;
+  double total = 0, longest = 0;
+  long long ntiles = 0, mb = 0;
+  for (int l = 0; l < nlev; ++l) {
+    const int Jh = (J[l] + 1) / 2, jt = (Jh + 127) / 128;
+    const long long ncol = (2LL * F[l] + 16 * k - 1) / (16 * k);
+    for (int m = 0; m <= N[l]; ++m) {
+      const int nm = N[l] - m + 1, j0 = jst ? jst[mb + m] : 0;
+      const double blocks = analysis ? (Jh - j0 / 32 * 32 + 31) / 32 : (nm + 31) / 32;
+      const long long n = (analysis ? (nm + rows - 1) / rows : jt - j0 / 128) * ncol;
+      const double c = blocks * (k + a) * (rows / 128);
+      total += n * c;
+      ntiles += n;
+      if (n > 0 && c > longest) longest = c;
+    }
+    mb += N[l] + 1;
+  }
+  if (ntiles == 0) return 0;
+  // per compute unit: whole rounds of the analysis' tiles, which cost the
+  // same in one level; the synthesis' lists start with the longest tiles and
+  // end with short ones
+  const double per = (double)ntiles / ncu;
+  if (analysis && nlev == 1) return total / ntiles * std::ceil(per);
+  return total / ncu + 0.5 * longest;
+}
+
+int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const long long* Cp,
+                const int* jst, bool analysis, int ncu, double* cost) {
   int best = 1;
   double bestc = 1e300;
-  for (int k = 0; k < nc; ++k) {
-    double c = 0;
-    for (int l = 0; l < nlev; ++l) {
-      double work = (double)(N[l] + 1) * (N[l] + 2) * ((J[l] + 1) / 2);
-      c += work * (double)roundup(2LL * F[l], 16LL * cand[k]);
-    }
+  for (int k = max_ncb(form, analysis); k >= 1; --k) {
+    bool ok = true;
+    for (int l = 0; l < nlev; ++l) ok = ok && Cp[l] % (16 * k) == 0;
+    if (!ok) continue;
+    const double c = legendre_cost(form, gen, nlev, N, J, F, jst, analysis, k, ncu);
     if (c < bestc * (1 - 1e-12)) {
       bestc = c;
-      best = cand[k];
+      best = k;
     }
   }
+  if (cost) *cost = bestc;
   return best;
+}
+
+int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J, const int* F, int FB, int ncu,
+                       long long ws_limit) {
+  const int elem = form == SHT_FORM_FP64 ? 8 : 4;
+  long long least = 0;
+  std::vector<long long> Cp(nlev);
+  int best = 1;
+  double bestc = 1e300;
+  for (int pass = 0; pass < 2; ++pass)
+    for (int g = max_ncb(form, true); g >= 1; --g) {
+      long long ws = 0;
+      for (int l = 0; l < nlev; ++l) {
+        Cp[l] = roundup(2LL * F[l], std::lcm(16LL * g, 2LL * FB));
+        ws += (N[l] + 1) * 2LL * ws_plane(roundup((J[l] + 1) / 2, SHT_K_PAD), Cp[l]) * elem;
+      }
+      if (pass == 0) {
+        if (least == 0 || ws < least) least = ws;
+        continue;
+      }
+      // at most a quarter more workspace than the tightest rows, and none
+      // where that would cross the limit
+      if (ws > least + least / 4 || (ws > ws_limit && least <= ws_limit)) continue;
+      double ca = 0, cs = 0;
+      choose_tile(form, gen, nlev, N, J, F, Cp.data(), nullptr, true, ncu, &ca);
+      choose_tile(form, gen, nlev, N, J, F, Cp.data(), nullptr, false, ncu, &cs);
+      // ties: the tighter rows, then the wider granularity
+      const double c = (ca + cs) * (1 + 1e-3 * (double)ws / (double)least);
+      if (c < bestc * (1 - 1e-9)) {
+        bestc = c;
+        best = g;
+      }
+    }
+  return best;
+}
+
+int choose_ncb(int form, int nlev, const int* N, const int* J, const int* F) {
+  return choose_granularity(form, false, nlev, N, J, F, form == SHT_FORM_FP64 ? 4 : 8, 256, 1LL << 62);
 }
 
 void layout_levels(int nlev, const int* Nv, const int* Jv, const int* Iv, const int* Fv, int BN, int FB,

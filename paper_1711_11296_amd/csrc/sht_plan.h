@@ -28,8 +28,29 @@ namespace sht {
 
 inline long long roundup(long long a, long long b) { return (a + b - 1) / b * b; }
 
-// Column blocking shared by all levels: the one that pads the least
-// (weighted by the Legendre work), preferring wider tiles on ties.
+// Time estimate of one direction's Legendre kernel with column tiles of k
+// 16-column blocks on ncu compute units, in units of one K block's products
+// for one column block: every tile costs (K blocks) (k + a) with a the work
+// of a K block that does not depend on the tile's width.  a was fitted to
+// timings of every width (T479 with 45 and 100 fields, T319 with 45): FP32
+// 0.4 / 1.0 (analysis / synthesis), FP64 0.3 / 0.6, split form 2.2.
+// gen: generated P~; jst as for build_tiles (or null).
+double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const int* jst,
+                     bool analysis, int k, int ncu);
+
+// Column blocking of a direction: the k of least estimated time among those that tile every level's workspace row Cp exactly.
+int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const long long* Cp,
+                const int* jst, bool analysis, int ncu, double* cost);
+
+// Granularity g of the workspace rows (16-column blocks; Cp is 2 F rounded
+// up to lcm(16 g, 2 FB)): the one whose divisors serve both directions best.
+// 100 fields (13 blocks) take 14 blocks, two tiles of 7: Legendre analysis /
+// synthesis at T479 FP32 0.264 / 0.278 ms, against 0.345 / 0.443 with 13
+// tiles of one block, which pads least.  Rows that would lift the workspace
+// over ws_limit bytes are not considered where tighter ones stay below it.
+int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J, const int* F, int FB, int ncu,
+                       long long ws_limit);
+// The same for items of the default width, table kernels and a whole device.
 int choose_ncb(int form, int nlev, const int* N, const int* J, const int* F);
 
 // Offsets of one plan's per-(level, m) blocks and its totals (elements);
