@@ -3,7 +3,7 @@
 //
 // Analysis, Sec. 2 (discretised zonal integral, 1/I convention): for the
 // mirror pair of rows (j, J-1-j) the kernel forms z = x_north + i x_south,
-// runs one complex FFT of length I in LDS (Stockham, radices 2/3/4/5), and
+// runs one complex FFT of length I in LDS (Stockham), and
 // separates the two real spectra:
 //   X_north^m = (Z^m + conj Z^{I-m}) / 2,  X_south^m = (Z^m - conj Z^{I-m}) / 2i.
 // It then writes the symmetric and antisymmetric parts of App. B (eqs. B3,
@@ -16,6 +16,9 @@
 // X_south = S - A, packs Z^m = X_north^m + i X_south^m and its Hermitian
 // partner at I-m, and one inverse FFT yields both rows:
 //   x(lambda_i) = Re X^0 + 2 sum_{m>=1} Re(X^m e^{i m lambda_i}).
+//
+// This file holds the kernels of the lengths with a compile-time three-pass
+// plan and the choice of kernel; sht_any.h those of every other length.
 //
 // Work decomposition: one workgroup per (mirror row pair, block of FB
 // fields).  The FB fields go through the LDS buffer one after the other and
@@ -33,345 +36,13 @@
 #include <utility>
 
 #include "sht_internal.h"
+#include "sht_any.h"
+#include "sht_dft.h"
 
 namespace sht {
 
-template <typename T>
-struct cx {
-  T x, y;
-};
-
-template <typename T>
-__device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
-  return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
-
-template <typename T>
-__device__ __forceinline__ cx<T> cadd(cx<T> a, cx<T> b) {
-  return {a.x + b.x, a.y + b.y};
-}
-
-template <typename T>
-__device__ __forceinline__ cx<T> csub(cx<T> a, cx<T> b) {
-  return {a.x - b.x, a.y - b.y};
-}
-
-// multiply by -i
-template <typename T>
-__device__ __forceinline__ cx<T> mul_mi(cx<T> a) {
-  return {a.y, -a.x};
-}
-
-// In-register DFT of length R with the forward sign exp(-2 pi i t k / R).
-template <typename T, int R>
-struct Dft;
-
-template <typename T>
-struct Dft<T, 2> {
-  static __device__ __forceinline__ void run(cx<T>* v) {
-    cx<T> a = v[0], b = v[1];
-    v[0] = cadd(a, b);
-    v[1] = csub(a, b);
-  }
-};
-
-template <typename T>
-struct Dft<T, 3> {
-  static __device__ __forceinline__ void run(cx<T>* v) {
-    const T h = (T)0.5;
-    const T s = (T)0.86602540378443864676372317075293618;  // sin(2 pi / 3)
-    cx<T> a = v[0], b = v[1], c = v[2];
-    cx<T> sbc = cadd(b, c);
-    cx<T> dbc = csub(b, c);
-    cx<T> t1 = {a.x - h * sbc.x, a.y - h * sbc.y};
-    // -i s (b - c)
-    cx<T> t2 = {s * dbc.y, -s * dbc.x};
-    v[0] = cadd(a, sbc);
-    v[1] = cadd(t1, t2);
-    v[2] = csub(t1, t2);
-  }
-};
-
-template <typename T>
-struct Dft<T, 4> {
-  static __device__ __forceinline__ void run(cx<T>* v) {
-    cx<T> a = v[0], b = v[1], c = v[2], d = v[3];
-    cx<T> s0 = cadd(a, c), d0 = csub(a, c);
-    cx<T> s1 = cadd(b, d), d1 = mul_mi(csub(b, d));
-    v[0] = cadd(s0, s1);
-    v[2] = csub(s0, s1);
-    v[1] = cadd(d0, d1);
-    v[3] = csub(d0, d1);
-  }
-};
-
-template <typename T>
-struct Dft<T, 8> {
-  static __device__ __forceinline__ void run(cx<T>* v) {
-    const T r = (T)0.70710678118654752440084436210484904;  // 1/sqrt(2)
-    cx<T> e[4] = {v[0], v[2], v[4], v[6]};
-    cx<T> o[4] = {v[1], v[3], v[5], v[7]};
-    Dft<T, 4>::run(e);
-    Dft<T, 4>::run(o);
-    // o_k *= exp(-2 pi i k / 8)
-    const cx<T> o1 = {r * (o[1].x + o[1].y), r * (o[1].y - o[1].x)};
-    const cx<T> o2 = {o[2].y, -o[2].x};
-    const cx<T> o3 = {r * (o[3].y - o[3].x), -r * (o[3].x + o[3].y)};
-    v[0] = cadd(e[0], o[0]);
-    v[4] = csub(e[0], o[0]);
-    v[1] = cadd(e[1], o1);
-    v[5] = csub(e[1], o1);
-    v[2] = cadd(e[2], o2);
-    v[6] = csub(e[2], o2);
-    v[3] = cadd(e[3], o3);
-    v[7] = csub(e[3], o3);
-  }
-};
-
-template <typename T>
-struct Dft<T, 5> {
-  static __device__ __forceinline__ void run(cx<T>* v) {
-    const T c1 = (T)0.30901699437494742410229341718281906;   // cos(2 pi/5)
-    const T c2 = (T)-0.80901699437494742410229341718281906;  // cos(4 pi/5)
-    const T s1 = (T)0.95105651629515357211643933337938214;   // sin(2 pi/5)
-    const T s2 = (T)0.58778525229247312916870595463907277;   // sin(4 pi/5)
-    cx<T> x0 = v[0];
-    cx<T> p1 = cadd(v[1], v[4]), q1 = csub(v[1], v[4]);
-    cx<T> p2 = cadd(v[2], v[3]), q2 = csub(v[2], v[3]);
-    cx<T> r1 = {x0.x + c1 * p1.x + c2 * p2.x, x0.y + c1 * p1.y + c2 * p2.y};
-    cx<T> r2 = {x0.x + c2 * p1.x + c1 * p2.x, x0.y + c2 * p1.y + c1 * p2.y};
-    // i1 = s1 q1 + s2 q2, i2 = s2 q1 - s1 q2; y1 = r1 - i*i1, y4 = r1 + i*i1,
-    // y2 = r2 - i*i2, y3 = r2 + i*i2
-    cx<T> i1 = {s1 * q1.x + s2 * q2.x, s1 * q1.y + s2 * q2.y};
-    cx<T> i2 = {s2 * q1.x - s1 * q2.x, s2 * q1.y - s1 * q2.y};
-    v[0] = {x0.x + p1.x + p2.x, x0.y + p1.y + p2.y};
-    v[1] = {r1.x + i1.y, r1.y - i1.x};
-    v[4] = {r1.x - i1.y, r1.y + i1.x};
-    v[2] = {r2.x + i2.y, r2.y - i2.x};
-    v[3] = {r2.x - i2.y, r2.y + i2.x};
-  }
-};
-
-// ---------------------------------------------------------------------------
-// Composite in-register DFTs, R = R1 * R2 (Cooley-Tukey): R2 DFTs of length
-// R1 over the inputs n = R2 n1 + n2, the internal twiddles
-// exp(-2 pi i n2 k1 / R), then R1 DFTs of length R2; output index
-// k = k1 + R1 k2.  The twiddles are compile-time constants.
-// ---------------------------------------------------------------------------
-constexpr double kTwoPi = 6.283185307179586476925286766559005768;
-
-// sin(x) for |x| <= pi/2 by its Taylor series (accurate to double rounding)
-constexpr double csin_small(double x) {
-  double x2 = x * x, term = x, sum = x;
-  for (int k = 1; k < 14; ++k) {
-    term *= -x2 / ((2.0 * k) * (2.0 * k + 1.0));
-    sum += term;
-  }
-  return sum;
-}
-
-// sin(2 pi e / R) and cos(2 pi e / R) with exact integer range reduction
-constexpr double csin2pi(int e, int R) {
-  e %= R;
-  if (e < 0) e += R;
-  // reduce to the first half turn by symmetry: sin(2 pi - x) = -sin(x)
-  if (2 * e > R) return -csin2pi(R - e, R);
-  // x = 2 pi e / R in [0, pi]; sin(x) = sin(pi - x)
-  if (4 * e > R) return csin_small(kTwoPi * (double)(R - 2 * e) / (2.0 * R));
-  return csin_small(kTwoPi * (double)e / (double)R);
-}
-
-constexpr double ccos2pi(int e, int R) { return csin2pi(4 * e + R, 4 * R); }
-
-// Calls f(integral_constant<int, i>) for i = 0..N-1, so that f can form
-// constant expressions from i.
-template <class F, int... Is>
-__device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, Is...>) {
-  (f(std::integral_constant<int, Is>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-template <typename T, int R1, int R2>
-struct DftCT {
-  static constexpr int R = R1 * R2;
-  static __device__ __forceinline__ void run(cx<T>* v) {
-    cx<T> y[R2][R1];
-    static_for<R2>([&](auto n2c) {
-      constexpr int n2 = decltype(n2c)::value;
-      cx<T> t[R1];
-#pragma unroll
-      for (int n1 = 0; n1 < R1; ++n1) t[n1] = v[R2 * n1 + n2];
-      Dft<T, R1>::run(t);
-      static_for<R1>([&](auto k1c) {
-        constexpr int k1 = decltype(k1c)::value;
-        if constexpr (n2 == 0 || k1 == 0) {
-          y[n2][k1] = t[k1];
-        } else {
-          constexpr T c = (T)ccos2pi(n2 * k1, R), sn = (T)-csin2pi(n2 * k1, R);
-          y[n2][k1] = cx<T>{t[k1].x * c - t[k1].y * sn, t[k1].x * sn + t[k1].y * c};
-        }
-      });
-    });
-#pragma unroll
-    for (int k1 = 0; k1 < R1; ++k1) {
-      cx<T> t[R2];
-#pragma unroll
-      for (int n2 = 0; n2 < R2; ++n2) t[n2] = y[n2][k1];
-      Dft<T, R2>::run(t);
-#pragma unroll
-      for (int k2 = 0; k2 < R2; ++k2) v[k1 + R1 * k2] = t[k2];
-    }
-  }
-};
-
-template <typename T>
-struct Dft<T, 6> : DftCT<T, 3, 2> {};
-template <typename T>
-struct Dft<T, 9> : DftCT<T, 3, 3> {};
-template <typename T>
-struct Dft<T, 10> : DftCT<T, 5, 2> {};
-template <typename T>
-struct Dft<T, 12> : DftCT<T, 4, 3> {};
-template <typename T>
-struct Dft<T, 15> : DftCT<T, 5, 3> {};
-template <typename T>
-struct Dft<T, 16> : DftCT<T, 4, 4> {};
-template <typename T>
-struct Dft<T, 20> : DftCT<T, 5, 4> {};
-
-// LDS position of element i of the FFT buffers (dense).
-__device__ __forceinline__ int lp(int i) { return i; }
-
-// q = floor(j / d) for 0 <= j < 2^13 and 2 <= d <= 4096, with
-// magic = floor((2^32 - 1) / d) + 1 (exhaustively checked over that range).
-__device__ __forceinline__ int fastdiv(int j, unsigned magic) {
-  return (int)__umulhi((unsigned)j, magic);
-}
-
-// One Stockham pass of radix R over FC sequences of length I that lie one
-// after the other in LDS, in place: every thread first loads and transforms
-// all its butterflies, then (after a barrier) stores them.  Ns is the product
-// of the radices of the earlier passes.  A thread owns butterfly position j
-// in all FC sequences, so the index arithmetic and the twiddles are shared by
-// the FC transforms.  With q = floor(j / Ns) and k = j - q Ns the inputs are
-// j + t I/R and the outputs q Ns R + k + t Ns = j R - k (R-1) + t Ns.
-template <typename T, int NT, int FC, int MAXI, int R>
-__device__ __forceinline__ void stockham_pass(cx<T>* buf, int I, int Ns, int twstep,
-                                              unsigned magic, const cx<T>* __restrict__ tw) {
-  constexpr int BPT = (MAXI / R + NT - 1) / NT;
-  const int nb = twstep * Ns;  // I / R
-  cx<T> v[BPT][FC][R];
-#pragma unroll
-  for (int b = 0; b < BPT; ++b) {
-    const int j = threadIdx.x + b * NT;
-    if (j < nb) {
-      cx<T> w[R];
-      if (Ns > 1) {
-        const int k = j - fastdiv(j, magic) * Ns;
-        const int step = k * twstep;
-        int idx = step;
-#pragma unroll
-        for (int t = 1; t < R; ++t) {
-          w[t] = tw[idx];
-          idx += step;
-        }
-      }
-#pragma unroll
-      for (int f = 0; f < FC; ++f) {
-        const int src = f * I + j;
-#pragma unroll
-        for (int t = 0; t < R; ++t) v[b][f][t] = buf[lp(src + t * nb)];
-        if (Ns > 1) {
-#pragma unroll
-          for (int t = 1; t < R; ++t) v[b][f][t] = cmul(v[b][f][t], w[t]);
-        }
-        Dft<T, R>::run(v[b][f]);
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int b = 0; b < BPT; ++b) {
-    const int j = threadIdx.x + b * NT;
-    if (j < nb) {
-      int out = j * R;
-      if (Ns > 1) out -= (j - fastdiv(j, magic) * Ns) * (R - 1);
-#pragma unroll
-      for (int f = 0; f < FC; ++f) {
-        const int dst = f * I + out;
-#pragma unroll
-        for (int t = 0; t < R; ++t) buf[lp(dst + t * Ns)] = v[b][f][t];
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Forward complex FFTs (sign -) of the FC sequences in buf, natural order in
-// and out.  Every thread of the block must call it.
-template <typename T, int NT, int FC, int MAXI>
-__device__ __forceinline__ void fft_lds(cx<T>* buf, const LevelDesc& L, const cx<T>* tw) {
-  for (int p = 0; p < L.nrad; ++p) {
-    const int R = L.rad[p], Ns = L.pns[p], tws = L.ptw[p];
-    const unsigned mg = L.pmag[p];
-    if (R == 8)
-      stockham_pass<T, NT, FC, MAXI, 8>(buf, L.I, Ns, tws, mg, tw);
-    else if (R == 4)
-      stockham_pass<T, NT, FC, MAXI, 4>(buf, L.I, Ns, tws, mg, tw);
-    else if (R == 2)
-      stockham_pass<T, NT, FC, MAXI, 2>(buf, L.I, Ns, tws, mg, tw);
-    else if (R == 3)
-      stockham_pass<T, NT, FC, MAXI, 3>(buf, L.I, Ns, tws, mg, tw);
-    else
-      stockham_pass<T, NT, FC, MAXI, 5>(buf, L.I, Ns, tws, mg, tw);
-  }
-}
-
-__device__ __forceinline__ int level_of(const FftArgs& a, int item) {
-  int l = 0;
-  while (l + 1 < a.nlev && item >= a.lev[l + 1].fft_item0) ++l;
-  return l;
-}
-
-// One past the last work item (slot) of level l.
-__device__ __forceinline__ int level_end(const FftArgs& a, int l) {
-  return l + 1 < a.nlev ? a.lev[l + 1].fft_item0 : a.nitems;
-}
-
 // Store/load FB complex values (2*FB scalars, 64 bytes) starting at a
 // 64-byte aligned address, as 16-byte vector accesses.
-template <typename T>
-struct Vec16;
-template <>
-struct Vec16<float> {
-  typedef float type __attribute__((ext_vector_type(4)));
-};
-template <>
-struct Vec16<double> {
-  typedef double type __attribute__((ext_vector_type(2)));
-};
-
-template <typename T, int FB>
-__device__ __forceinline__ void store_run(T* dst, const cx<T> (&v)[FB]) {
-  static_assert(2 * FB <= 16, "one analysis workspace column block");
-  typedef typename Vec16<T>::type V;
-  constexpr int E = 16 / sizeof(T);  // scalars per vector
-  V* d = reinterpret_cast<V*>(dst);
-#pragma unroll
-  for (int k = 0; k < 2 * FB / E; ++k) {
-    V o;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int q = k * E + e;
-      o[e] = (q & 1) ? v[q >> 1].y : v[q >> 1].x;
-    }
-    d[k] = o;
-  }
-}
-
 template <typename T, int FB>
 __device__ __forceinline__ void load_run(const T* src, cx<T> (&v)[FB]) {
   typedef typename Vec16<T>::type V;
@@ -462,295 +133,6 @@ __device__ __forceinline__ void store_runs_quad(T* base, long long plane, int m,
       off += step;
     }
   }
-}
-
-// Work item = (level, mirror row pair jp, block fb of FB fields).
-struct Item {
-  int l, jp, fb, js;
-  bool eq;
-};
-
-// Workgroup b runs on XCD b mod 8 and walks the slots b, b + G, ...
-// (G = gridDim.x, a multiple of 8 on a full device).  The slots of a level
-// are a contiguous range; within it, local slot i is mapped to the level's
-// list position x R' + k (x = i mod 8, k = i / 8, R' the length of the
-// x-th eighth of the level's list): the workgroups of one XCD work through
-// one contiguous eighth of every level, so the field blocks of one latitude
-// pair run on one XCD at about the same time and fill whole workspace lines
-// in its L2, and every XCD gets the same share of each level.  The map is a
-// permutation of [0, n).
-__device__ __forceinline__ int xcd_map(int i, int n) {
-  const int x = i & 7, k = i >> 3;
-  const int R = n >> 3, rem = n & 7;
-  return x * R + (x < rem ? x : rem) + k;
-}
-
-__device__ __forceinline__ Item decode_item(const FftArgs& a, int slot) {
-  Item it;
-  it.l = level_of(a, slot);
-  const LevelDesc& L = a.lev[it.l];
-  const int local = xcd_map(slot - L.fft_item0, level_end(a, it.l) - L.fft_item0);
-  it.jp = local / L.nfb;
-  it.fb = local - it.jp * L.nfb;
-  it.eq = (L.J & 1) && (it.jp == (L.J >> 1));
-  it.js = L.J - 1 - it.jp;
-  return it;
-}
-
-template <typename T>
-__device__ __forceinline__ T row_scale(const FftArgs& a, const LevelDesc& L, int jp) {
-  T r = (T)1;
-  if (a.use_w) r = (T)L.wrow[jp];
-  if (a.use_inv_I) r = (T)((double)r / (double)L.I);
-  return r;
-}
-
-// ---------------------------------------------------------------------------
-// analysis: grid [F][J][I] -> workspace S/A
-// Persistent workgroups walk the work items with a stride of gridDim.x.
-// FB fields per item, FC of them transformed together; the rows of the next
-// FC fields (of this item, or the first FC of the next item) are prefetched
-// into registers while the current ones are transformed, so loads, FFTs and
-// the stores of the previous item overlap.  Twiddles are staged in LDS when
-// TWL is set (reloaded when the level changes).
-// ---------------------------------------------------------------------------
-// The slots item, item + G, ... below `end` (any levels); returns the first
-// slot past them.  Every thread of the workgroup calls it alike.
-template <typename T, int NT, int FB, int FC, int MS, int MAXI, bool TWL>
-__device__ __forceinline__ int zonal_analysis_run(const FftArgs& a, int item, int end, unsigned char* smem_raw) {
-  constexpr int NRD = FB / FC;
-  constexpr int LPT = (MAXI + NT - 1) / NT;
-  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  const T* grid0 = static_cast<const T*>(a.src);
-  T* ws0 = static_cast<T*>(a.dst);
-  const T msc = (T)a.mscale;
-
-  T pn[FC][LPT], ps[FC][LPT];
-  auto load_rows = [&](int item, int rd) __attribute__((always_inline)) {
-    const Item it = decode_item(a, item);
-    const LevelDesc& L = a.lev[it.l];
-    const T* grid = grid0 + L.grid_off;
-#pragma unroll
-    for (int fc = 0; fc < FC; ++fc) {
-      const int f = it.fb * FB + rd * FC + fc;
-      const bool valid = f < L.F;
-      const T* rn = grid + ((long long)f * L.J + it.jp) * L.I;
-      const T* rs = grid + ((long long)f * L.J + it.js) * L.I;
-#pragma unroll
-      for (int e = 0; e < LPT; ++e) {
-        const int i = threadIdx.x + e * NT;
-        pn[fc][e] = (valid && i < L.I) ? rn[i] : (T)0;
-        ps[fc][e] = (valid && !it.eq && i < L.I) ? rs[i] : (T)0;
-      }
-    }
-  };
-
-  if (item >= end) return item;
-  int lcur = -1;
-  const cx<T>* tw = nullptr;
-  load_rows(item, 0);
-  for (; item < end; item += gridDim.x) {
-    const Item it = decode_item(a, item);
-    const LevelDesc& L = a.lev[it.l];
-    const int I = L.I, N = L.N;
-    if (it.l != lcur) {
-      if (TWL) {
-        __syncthreads();  // the previous level's twiddles are no longer read
-        cx<T>* twl = buf + a.tw_lds;
-        const cx<T>* twg = static_cast<const cx<T>*>(L.tw);
-        for (int i = threadIdx.x; i < I; i += NT) twl[i] = twg[i];
-        tw = twl;
-      } else {
-        tw = static_cast<const cx<T>*>(L.tw);
-      }
-      lcur = it.l;
-    }
-    const T rscale = row_scale<T>(a, L, it.jp);
-    const int next = item + (int)gridDim.x;
-
-    cx<T> stS[MS][FB], stA[MS][FB];
-#pragma unroll
-    for (int rd = 0; rd < NRD; ++rd) {
-#pragma unroll
-      for (int fc = 0; fc < FC; ++fc)
-#pragma unroll
-        for (int e = 0; e < LPT; ++e) {
-          const int i = threadIdx.x + e * NT;
-          if (i < I) buf[lp(fc * I + i)] = cx<T>{pn[fc][e], ps[fc][e]};
-        }
-      __syncthreads();
-      if (rd + 1 < NRD)
-        load_rows(item, rd + 1);
-      else if (next < end)
-        load_rows(next, 0);
-      fft_lds<T, NT, FC, MAXI>(buf, L, tw);
-#pragma unroll
-      for (int s = 0; s < MS; ++s) {
-        const int m = threadIdx.x + s * NT;
-#pragma unroll
-        for (int fc = 0; fc < FC; ++fc) {
-          cx<T> S = {(T)0, (T)0}, A = {(T)0, (T)0};
-          if (m <= N) {
-            const cx<T> P = buf[lp(fc * I + m)];
-            cx<T> Q = buf[lp(fc * I + (m == 0 ? 0 : I - m))];
-            Q.y = -Q.y;  // conj Z^{I-m}
-            const T h = (T)0.5;
-            const cx<T> Xn = {h * (P.x + Q.x), h * (P.y + Q.y)};
-            const cx<T> Xs = {h * (P.y - Q.y), -h * (P.x - Q.x)};
-            const T sc = m == 0 ? rscale : rscale * msc;
-            S = cx<T>{sc * (Xn.x + Xs.x), sc * (Xn.y + Xs.y)};
-            A = cx<T>{sc * (Xn.x - Xs.x), sc * (Xn.y - Xs.y)};
-            if (m == 0) {
-              S.y = (T)0;
-              A.y = (T)0;
-            }
-            if (it.eq) A = cx<T>{(T)0, (T)0};
-          }
-          stS[s][rd * FC + fc] = S;
-          stA[s][rd * FC + fc] = A;
-        }
-      }
-      __syncthreads();
-    }
-
-    T* ws = ws0 + L.ws_off;
-    const long long Cp = L.Cp;
-    const long long plane = L.wplane;
-#pragma unroll
-    for (int s = 0; s < MS; ++s) {
-      const int m = threadIdx.x + s * NT;
-      if (m <= N) {
-        // the item's column block (ws_col): even run, then odd run
-        T* dS = ws + (2LL * m) * plane + (long long)it.jp * 2 * Cp + 4 * it.fb * FB;
-        store_run<T, FB>(dS, stS[s]);
-        store_run<T, FB>(dS + 2 * FB, stA[s]);
-      }
-    }
-  }
-  return item;
-}
-
-template <typename T, int NT, int FB, int FC, int MS, int MAXI, bool TWL>
-__global__ __launch_bounds__(NT) void k_zonal_analysis(const FftArgs a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  zonal_analysis_run<T, NT, FB, FC, MS, MAXI, TWL>(a, blockIdx.x, a.nitems, smem_raw);
-}
-
-// ---------------------------------------------------------------------------
-// synthesis: workspace S/A -> grid [F][J][I]
-// Persistent like the analysis; the workspace runs of the next item are
-// loaded as soon as the last round of the current item has filled its
-// buffers, so they overlap that round's FFT and row stores.
-// ---------------------------------------------------------------------------
-template <typename T, int NT, int FB, int FC, int MS, int MAXI, bool TWL>
-__device__ __forceinline__ int zonal_synthesis_run(const FftArgs& a, int item, int end, unsigned char* smem_raw) {
-  constexpr int NRD = FB / FC;
-  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  const T* ws0 = static_cast<const T*>(a.src);
-  T* grid0 = static_cast<T*>(a.dst);
-  const T msc = (T)a.mscale;
-
-  cx<T> stS[MS][FB], stA[MS][FB];
-  auto load_ws = [&](int item) __attribute__((always_inline)) {
-    const Item it = decode_item(a, item);
-    const LevelDesc& L = a.lev[it.l];
-    const T* ws = ws0 + L.ws_off;
-    const long long Cp = L.Cp;
-    const long long plane = L.wplane;
-#pragma unroll
-    for (int s = 0; s < MS; ++s) {
-      const int m = threadIdx.x + s * NT;
-      // rows below the first 128-latitude tile the Legendre synthesis
-      // computes for this m (reduced transform) are zero
-      if (m <= L.N && (!a.jstart || it.jp >= (a.jstart[L.m_base + m] & ~127))) {
-        const T* sS = ws + (2LL * m) * plane + (long long)it.jp * Cp + 2 * it.fb * FB;
-        load_run<T, FB>(sS, stS[s]);
-        load_run<T, FB>(sS + L.spoff, stA[s]);
-      } else {
-#pragma unroll
-        for (int q = 0; q < FB; ++q) stS[s][q] = stA[s][q] = cx<T>{(T)0, (T)0};
-      }
-    }
-  };
-
-  if (item >= end) return item;
-  int lcur = -1;
-  const cx<T>* tw = nullptr;
-  load_ws(item);
-  for (; item < end; item += gridDim.x) {
-    const Item it = decode_item(a, item);
-    const LevelDesc& L = a.lev[it.l];
-    const int I = L.I, J = L.J, N = L.N;
-    if (it.l != lcur) {
-      if (TWL) {
-        __syncthreads();
-        cx<T>* twl = buf + a.tw_lds;
-        const cx<T>* twg = static_cast<const cx<T>*>(L.tw);
-        for (int i = threadIdx.x; i < I; i += NT) twl[i] = twg[i];
-        tw = twl;
-      } else {
-        tw = static_cast<const cx<T>*>(L.tw);
-      }
-      lcur = it.l;
-    }
-    const T rscale = row_scale<T>(a, L, it.jp);
-    const int next = item + (int)gridDim.x;
-    T* grid = grid0 + L.grid_off;
-
-#pragma unroll
-    for (int rd = 0; rd < NRD; ++rd) {
-#pragma unroll
-      for (int fc = 0; fc < FC; ++fc) {
-        const int bf = fc * I;
-        // zero the bins no thread fills: N < i < I-N
-        for (int i = N + 1 + threadIdx.x; i < I - N; i += NT) buf[lp(bf + i)] = cx<T>{(T)0, (T)0};
-#pragma unroll
-        for (int s = 0; s < MS; ++s) {
-          const int m = threadIdx.x + s * NT;
-          if (m <= N) {
-            const cx<T> S = stS[s][rd * FC + fc], A = stA[s][rd * FC + fc];
-            const T sc = m == 0 ? (T)1 : msc;
-            cx<T> Xn = {sc * (S.x + A.x), sc * (S.y + A.y)};
-            cx<T> Xs = {sc * (S.x - A.x), sc * (S.y - A.y)};
-            if (m == 0) {
-              Xn.y = (T)0;
-              Xs.y = (T)0;
-            }
-            // the buffer holds conj(Z): the forward FFT of conj(Z) is the
-            // conjugate of the inverse transform of Z, with
-            // Z^m = Xn + i Xs and Z^{I-m} = conj(Xn) + i conj(Xs)
-            buf[lp(bf + m)] = cx<T>{Xn.x - Xs.y, -(Xn.y + Xs.x)};
-            if (m > 0) buf[lp(bf + I - m)] = cx<T>{Xn.x + Xs.y, Xn.y - Xs.x};
-          }
-        }
-      }
-      __syncthreads();
-      if (rd + 1 == NRD && next < end) load_ws(next);
-      fft_lds<T, NT, FC, MAXI>(buf, L, tw);
-#pragma unroll
-      for (int fc = 0; fc < FC; ++fc) {
-        const int f = it.fb * FB + rd * FC + fc;
-        if (f < L.F) {
-          const int bf = fc * I;
-          T* rn = grid + ((long long)f * J + it.jp) * I;
-          T* rs = grid + ((long long)f * J + it.js) * I;
-          for (int i = threadIdx.x; i < I; i += NT) {
-            const cx<T> y = buf[lp(bf + i)];
-            rn[i] = rscale * y.x;
-            if (!it.eq) rs[i] = -rscale * y.y;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-  return item;
-}
-
-template <typename T, int NT, int FB, int FC, int MS, int MAXI, bool TWL>
-__global__ __launch_bounds__(NT) void k_zonal_synthesis(const FftArgs a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  zonal_synthesis_run<T, NT, FB, FC, MS, MAXI, TWL>(a, blockIdx.x, a.nitems, smem_raw);
 }
 
 // ---------------------------------------------------------------------------
@@ -1181,16 +563,17 @@ struct ZP3 {
   }
 };
 
-// runtime radices, twiddles staged in LDS at FftArgs::tw_lds
-template <int FC, int MS, int MAXI>
+// runtime radices (sht_any.h)
+template <bool VEC, int MAXI>
 struct ZRt {
-  static constexpr int fc = FC, maxi = MAXI, ms = MS;
+  static constexpr int maxi = MAXI;
   template <typename T, int NT, int FB, bool ANA>
   static __device__ __forceinline__ int run(const FftArgs& a, int l, int item, unsigned char* smem) {
+    constexpr int VW = sizeof(T) == 4 ? 2 : 1;
     if constexpr (ANA)
-      return zonal_analysis_run<T, NT, FB, FC, MS, MAXI, true>(a, item, level_end(a, l), smem);
+      return any_analysis_run<T, NT, VEC, VW>(a, item, level_end(a, l), smem);
     else
-      return zonal_synthesis_run<T, NT, FB, FC, MS, MAXI, true>(a, item, level_end(a, l), smem);
+      return any_synthesis_run<T, NT, VEC, VW>(a, item, level_end(a, l), smem);
   }
 };
 
@@ -1231,51 +614,6 @@ static void lds_optin(size_t bytes) {
 }
 
 static int g_num_cu = 0;
-
-template <typename T, int NT, int FB, int FC, int MS, int MAXI>
-static hipError_t launch_cfg(bool analysis, const FftArgs& a, int maxI, hipStream_t st) {
-  // FC padded buffers sized for the largest level, then the twiddles
-  FftArgs a2 = a;
-  const int belems = (FC * maxI + 1) & ~1;
-  a2.tw_lds = belems;
-  const size_t buf = (size_t)belems * sizeof(cx<T>);
-  const size_t twb = (size_t)maxI * sizeof(cx<T>);
-  const bool twl = buf + twb <= kMaxLds;
-  const size_t lds = buf + (twl ? twb : 0);
-  if (g_num_cu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&g_num_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        g_num_cu <= 0)
-      g_num_cu = 256;
-  }
-  // persistent workgroups: as many as fit on the device at once
-  int per_cu = (int)(kMaxLds / lds);
-  const int by_waves = 2048 / NT;
-  per_cu = per_cu < by_waves ? per_cu : by_waves;
-  per_cu = per_cu < 1 ? 1 : per_cu;
-  int nwg = g_num_cu * per_cu;
-  nwg = nwg < a.nitems ? nwg : a.nitems;
-  const dim3 grid(nwg), block(NT);
-  if (analysis) {
-    if (twl) {
-      lds_optin<k_zonal_analysis<T, NT, FB, FC, MS, MAXI, true>>(lds);
-      hipLaunchKernelGGL((k_zonal_analysis<T, NT, FB, FC, MS, MAXI, true>), grid, block, lds, st, a2);
-    } else {
-      lds_optin<k_zonal_analysis<T, NT, FB, FC, MS, MAXI, false>>(lds);
-      hipLaunchKernelGGL((k_zonal_analysis<T, NT, FB, FC, MS, MAXI, false>), grid, block, lds, st, a2);
-    }
-  } else {
-    if (twl) {
-      lds_optin<k_zonal_synthesis<T, NT, FB, FC, MS, MAXI, true>>(lds);
-      hipLaunchKernelGGL((k_zonal_synthesis<T, NT, FB, FC, MS, MAXI, true>), grid, block, lds, st, a2);
-    } else {
-      lds_optin<k_zonal_synthesis<T, NT, FB, FC, MS, MAXI, false>>(lds);
-      hipLaunchKernelGGL((k_zonal_synthesis<T, NT, FB, FC, MS, MAXI, false>), grid, block, lds, st, a2);
-    }
-  }
-  return hipGetLastError();
-}
 
 template <typename T, class P, int NT, int FB, int FC, int MS>
 static hipError_t launch_p3_ms(bool analysis, const FftArgs& a, hipStream_t st) {
@@ -1381,24 +719,9 @@ static void ensure_num_cu() {
   }
 }
 
-template <typename T, int FB, int FC>
-static hipError_t launch_generic(bool analysis, const FftArgs& a, int maxN, hipStream_t st) {
-  int maxI = 0;
-  for (int l = 0; l < a.nlev; ++l) maxI = a.lev[l].I > maxI ? a.lev[l].I : maxI;
-  const int nm = maxN + 1;
-  if (maxI <= 1024 && nm <= 512) {
-    if (nm <= 256) return launch_cfg<T, 256, FB, FC, 1, 1024>(analysis, a, maxI, st);
-    return launch_cfg<T, 256, FB, FC, 2, 1024>(analysis, a, maxI, st);
-  }
-  if (maxI <= 2048 && nm <= 1024) {
-    if (nm <= 512) return launch_cfg<T, 512, FB, FC, 1, 2048>(analysis, a, maxI, st);
-    return launch_cfg<T, 512, FB, FC, 2, 2048>(analysis, a, maxI, st);
-  }
-  // one 512-thread workgroup per CU: 256 registers per lane, no spilling
-  if (nm <= 512) return launch_cfg<T, 512, FB, FC, 1, 4096>(analysis, a, maxI, st);
-  if (nm <= 1024) return launch_cfg<T, 512, FB, FC, 2, 4096>(analysis, a, maxI, st);
-  if (nm <= 1536) return launch_cfg<T, 512, FB, FC, 3, 4096>(analysis, a, maxI, st);
-  return launch_cfg<T, 512, FB, FC, 4, 4096>(analysis, a, maxI, st);
+template <typename T>
+static hipError_t launch_generic(bool analysis, const FftArgs& a, hipStream_t st) {
+  return (hipError_t)launch_zonal_any(sizeof(T) == 8, analysis, a, g_num_cu, st);
 }
 
 // The configurations of the one-launch kernel for one element type (zk =
@@ -1410,10 +733,11 @@ struct ZLevels {
   using C1600 = ZP3<Plan3<1600, 10, 10>, dbl ? 2 : 4, 2>;
   using C800 = ZP3<Plan3<800, 5, 10>, 4, 1>;
   using C400 = ZP3<Plan3<400, 5, 5>, dbl ? 4 : 8, 1>;
-  using CRt = ZRt<dbl ? 1 : 4, 1, 1024>;
-  template <int FB, bool ANA>
+  template <bool VEC>
+  using CRt = ZRt<VEC, 1024>;
+  template <int FB, bool ANA, bool VEC>
   static constexpr auto kernel() {
-    return &k_zonal_levels<T, NT, FB, ANA, C1600, C800, C400, CRt>;
+    return &k_zonal_levels<T, NT, FB, ANA, C1600, C800, C400, CRt<VEC>>;
   }
 };
 
@@ -1427,11 +751,11 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
   using C1600 = typename ZLevels<T>::C1600;
   using C800 = typename ZLevels<T>::C800;
   using C400 = typename ZLevels<T>::C400;
-  using CRt = typename ZLevels<T>::CRt;
   if (a.nlev < 2 || a.fb != FB) return false;
   FftArgs b = a;
   size_t lds = 0;
-  int maxIrt = 0, kinds = 0;
+  int maxIrt = 0, maxNrt = 0, maxIP = 0, kinds = 0;
+  bool vec = true;
   for (int l = 0; l < a.nlev; ++l) {
     const LevelDesc& L = a.lev[l];
     int k;
@@ -1443,9 +767,13 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
       k = L.I == 1600 ? 0 : L.I == 800 ? 1 : 2;
       need = k == 0 ? C1600::template lds<T>() : k == 1 ? C800::template lds<T>() : C400::template lds<T>();
     } else {
-      if (L.I > CRt::maxi || L.N + 1 > CRt::ms * NT) return false;
+      if (L.I > ZLevels<T>::template CRt<true>::maxi || L.N + 1 > NT) return false;
       k = 3;
       maxIrt = L.I > maxIrt ? L.I : maxIrt;
+      maxNrt = L.N > maxNrt ? L.N : maxNrt;
+      const int ip = any_stride(L), V = 16 / (int)sizeof(T);
+      maxIP = ip > maxIP ? ip : maxIP;
+      vec = vec && L.I % V == 0;
     }
     kinds |= 1 << k;
     b.lev[l].zk = k;
@@ -1454,7 +782,23 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
   // one runtime-radix launch or one length alone gains nothing
   if (__builtin_popcount(kinds) < 2) return false;
   if (maxIrt) {
-    b.tw_lds = (CRt::fc * maxIrt + 1) & ~1;
+    // a whole block of FB fields per item where it fits the kernels'
+    // capacity per thread (AnyCap), else half of it
+    constexpr int E = AnyCap<T>::E;
+    b.lfc = FB == 8 ? 3 : 2;
+    while ((maxIrt << b.lfc) > NT * E || (2 * (maxNrt + 1) << b.lfc) > NT * E) --b.lfc;
+    b.tw_lds = ((maxIP << b.lfc) + 1) & ~1;
+    b.nitems = 0;
+    for (int l = 0; l < a.nlev; ++l) {
+      LevelDesc& L = b.lev[l];
+      if (L.zk == 3) {
+        const int nv = vec ? L.I / (16 / (int)sizeof(T)) : L.I;
+        L.ivm = nv > 1 ? 0xFFFFFFFFu / (unsigned)nv + 1u : 0u;
+        L.nfb = (L.F + (1 << b.lfc) - 1) >> b.lfc;
+      }
+      L.fft_item0 = b.nitems;
+      b.nitems += L.Jh * L.nfb;
+    }
     const size_t rt = (size_t)(b.tw_lds + maxIrt) * sizeof(cx<T>);
     lds = rt > lds ? rt : lds;
   }
@@ -1463,17 +807,17 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
   per_cu = per_cu < by_waves ? per_cu : by_waves;
   per_cu = per_cu < 1 ? 1 : per_cu;
   int nwg = g_num_cu * per_cu;
-  nwg = nwg < a.nitems ? nwg : a.nitems;
+  nwg = nwg < b.nitems ? nwg : b.nitems;
   const dim3 grid(nwg), block(NT);
-  if (analysis) {
-    constexpr auto K = ZLevels<T>::template kernel<FB, true>();
+  auto go = [&](auto ana, auto v) {
+    constexpr auto K = ZLevels<T>::template kernel<FB, decltype(ana)::value, decltype(v)::value>();
     lds_optin<K>(lds);
     hipLaunchKernelGGL(K, grid, block, lds, st, b);
-  } else {
-    constexpr auto K = ZLevels<T>::template kernel<FB, false>();
-    lds_optin<K>(lds);
-    hipLaunchKernelGGL(K, grid, block, lds, st, b);
-  }
+  };
+  if (analysis)
+    vec ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
+  else
+    vec ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
   *err = hipGetLastError();
   return true;
 }
@@ -1484,14 +828,13 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
 // from 0), and the other levels share one launch of the runtime-radix
 // kernel.  All launches go to the same stream, and the levels
 // write disjoint parts of the output.
-template <typename T, int FB, int FC>
+template <typename T, int FB>
 static hipError_t launch_levels(bool analysis, const FftArgs& a, hipStream_t st) {
   hipError_t e1 = hipSuccess;
   if (a.one_launch && launch_levels_one<T, FB>(analysis, a, st, &e1)) return e1;
   FftArgs rest = a;
   rest.nlev = 0;
   rest.nitems = 0;
-  int rest_maxN = 0;
   for (int l = 0; l < a.nlev; ++l) {
     FftArgs one = a;
     one.nlev = 1;
@@ -1507,29 +850,28 @@ static hipError_t launch_levels(bool analysis, const FftArgs& a, hipStream_t st)
     rest.lev[rest.nlev].fft_item0 = rest.nitems;
     rest.nitems += one.nitems;
     rest.nlev += 1;
-    rest_maxN = a.lev[l].N > rest_maxN ? a.lev[l].N : rest_maxN;
   }
   if (rest.nlev == 0) return hipSuccess;
-  return launch_generic<T, FB, FC>(analysis, rest, rest_maxN, st);
+  return launch_generic<T>(analysis, rest, st);
 }
 
-template <typename T, int FB, int FC>
+template <typename T, int FB>
 static hipError_t launch_zonal_t(bool analysis, const FftArgs& a, int maxN, hipStream_t st) {
   ensure_num_cu();
-  if (a.nlev > 1) return launch_levels<T, FB, FC>(analysis, a, st);
+  if (a.nlev > 1) return launch_levels<T, FB>(analysis, a, st);
   hipError_t err = hipSuccess;
   if (launch_fixed<T, FB>(analysis, a, maxN, st, &err)) return err;
-  return launch_generic<T, FB, FC>(analysis, a, maxN, st);
+  return launch_generic<T>(analysis, a, st);
 }
 
 int zonal_one_launch_spills(int form, bool analysis) {
   const void* k = nullptr;
   if (form == SHT_FORM_FP64)
-    k = analysis ? reinterpret_cast<const void*>(ZLevels<double>::kernel<4, true>())
-                 : reinterpret_cast<const void*>(ZLevels<double>::kernel<4, false>());
+    k = analysis ? reinterpret_cast<const void*>(ZLevels<double>::kernel<4, true, true>())
+                 : reinterpret_cast<const void*>(ZLevels<double>::kernel<4, false, true>());
   else
-    k = analysis ? reinterpret_cast<const void*>(ZLevels<float>::kernel<8, true>())
-                 : reinterpret_cast<const void*>(ZLevels<float>::kernel<8, false>());
+    k = analysis ? reinterpret_cast<const void*>(ZLevels<float>::kernel<8, true, true>())
+                 : reinterpret_cast<const void*>(ZLevels<float>::kernel<8, false, true>());
   hipFuncAttributes fa;
   if (hipFuncGetAttributes(&fa, k) != hipSuccess) return 1;
   return fa.localSizeBytes > 0 ? 1 : 0;
@@ -1549,14 +891,14 @@ int launch_zonal(int form, bool analysis, const FftArgs& a, int maxN, void* stre
   const int fb = form == SHT_FORM_FP64 ? 4 : (a.fb == 16 ? 16 : 8);
   for (int l = 0; l < a.nlev; ++l)
     if ((1 << a.lev[l].wsh) != (2 * fb < 16 ? 2 * fb : 16)) return (int)hipErrorInvalidValue;
-  if (form == SHT_FORM_FP64) return (int)launch_zonal_t<double, 4, 1>(analysis, a, maxN, st);
+  if (form == SHT_FORM_FP64) return (int)launch_zonal_t<double, 4>(analysis, a, maxN, st);
   if (a.fb == 16) {
     ensure_num_cu();
     hipError_t err = hipErrorInvalidValue;
     if (!launch_fixed<float, 16>(analysis, a, maxN, st, &err)) return (int)hipErrorInvalidValue;
     return (int)err;
   }
-  return (int)launch_zonal_t<float, 8, 4>(analysis, a, maxN, st);
+  return (int)launch_zonal_t<float, 8>(analysis, a, maxN, st);
 }
 
 }  // namespace sht

@@ -293,31 +293,35 @@ void alf_table(int N, int nr, const double* mu, const double* sint,
   for (auto& th : pool) th.join();
 }
 
+// Fewest passes with radices from the kernels' set; among those the least
+// sum (balanced radices), the largest radix first.
+static void factor_search(int n, int most, int depth, int sum, int* cur, int* rad, int* nrad, int* best) {
+  if (n == 1) {
+    if (depth < *nrad || (depth == *nrad && sum < *best)) {
+      for (int q = 0; q < depth; ++q) rad[q] = cur[q];
+      *nrad = depth;
+      *best = sum;
+    }
+    return;
+  }
+  if (depth >= SHT_MAX_RADICES || depth >= *nrad) return;
+  for (int r : {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2})
+    if (r <= most && n % r == 0) {
+      cur[depth] = r;
+      factor_search(n / r, r, depth + 1, sum + r, cur, rad, nrad, best);
+    }
+}
+
 bool factor_radices(int I, int* rad, int* nrad) {
-  int n = I, k = 0;
-  while (n % 8 == 0) {
-    rad[k++] = 8;
-    n /= 8;
-  }
-  while (n % 4 == 0) {
-    rad[k++] = 4;
-    n /= 4;
-  }
-  while (n % 2 == 0) {
-    rad[k++] = 2;
-    n /= 2;
-  }
-  while (n % 3 == 0) {
-    rad[k++] = 3;
-    n /= 3;
-  }
-  while (n % 5 == 0) {
-    rad[k++] = 5;
-    n /= 5;
-  }
-  if (n != 1 || k > SHT_MAX_RADICES) return false;
-  *nrad = k;
-  return true;
+  if (I < 1) return false;
+  int n = I;
+  for (int p : {2, 3, 5})
+    while (n % p == 0) n /= p;
+  if (n != 1) return false;
+  int cur[SHT_MAX_RADICES], best = 0;
+  *nrad = SHT_MAX_RADICES + 1;
+  factor_search(I, 16, 0, 0, cur, rad, nrad, &best);
+  return *nrad <= SHT_MAX_RADICES;
 }
 
 }  // namespace sht

@@ -8,7 +8,7 @@
 #include "../../include/sht.h"
 
 #define SHT_MAX_LEVELS 8
-#define SHT_MAX_RADICES 12
+#define SHT_MAX_RADICES 6
 #define SHT_MAX_I 4096
 
 // Latitude (contraction) dimension of the table and workspace is padded to a
@@ -40,6 +40,9 @@ struct LevelDesc {
   int pns[SHT_MAX_RADICES];   // product of the radices of the earlier passes
   int ptw[SHT_MAX_RADICES];   // twiddle index stride I / (pns * rad)
   unsigned pmag[SHT_MAX_RADICES];  // floor((2^32-1)/pns) + 1 (0 when pns == 1)
+  int pnb[SHT_MAX_RADICES];        // butterflies per sequence, I / rad
+  unsigned pbm[SHT_MAX_RADICES];   // floor((2^32-1)/pnb) + 1 (0 when pnb == 1)
+  unsigned ivm;                    // the same for the vectors of a grid row (set at launch)
   int fft_item0;   // first FFT work item of this level
   int nfb;         // field blocks of the FFT kernels
   int m_base;      // index of (level, m=0) in the per-m offset arrays
@@ -67,6 +70,7 @@ struct FftArgs {
   double mscale;
   int tw_lds;        // element offset of the LDS twiddle table (set at launch)
   int fb;            // fields per work item (zonal_fields_per_block)
+  int lfc;           // any-length kernels: log2 of the fields per item (set at launch)
   int one_launch;    // multi-level plans: one launch over all levels where they allow it
   // per (level, m): first latitude of the Legendre sums (reduced transform;
   // null otherwise); the synthesis leaves whole 128-latitude tiles below it
@@ -142,6 +146,8 @@ inline bool zonal_offsets_fit(long long wplane, long long elem) {
 // 1 if the one-launch multi-level zonal kernel of this form and direction
 // keeps values in scratch memory (register spills), else 0
 int zonal_one_launch_spills(int form, bool analysis);
+// Any lengths (sht_zonal_any.hip); ncu compute units.
+int launch_zonal_any(bool dbl, bool analysis, const FftArgs& a, int ncu, void* stream);
 int launch_zonal(int form, bool analysis, const FftArgs& a, int maxN, void* stream);
 // gen: generate P~ in the kernels from the plan's seed rows instead of
 // reading a table (plan option otf)

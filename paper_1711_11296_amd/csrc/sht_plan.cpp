@@ -123,6 +123,8 @@ void layout_levels(int nlev, const int* Nv, const int* Jv, const int* Iv, const 
       L.pns[q] = ns;
       L.ptw[q] = L.I / (ns * L.rad[q]);
       L.pmag[q] = ns > 1 ? 0xFFFFFFFFu / (unsigned)ns + 1u : 0u;
+      L.pnb[q] = L.I / L.rad[q];
+      L.pbm[q] = L.pnb[q] > 1 ? 0xFFFFFFFFu / (unsigned)L.pnb[q] + 1u : 0u;
     }
     L.nfb = (L.F + FB - 1) / FB;
     while ((1 << L.wsh) < 2 * FB && L.wsh < 4) ++L.wsh;  // W = min(2 FB, 16), a power of two

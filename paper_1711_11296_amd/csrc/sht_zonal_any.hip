@@ -1,0 +1,115 @@
+// Launches of the any-length zonal kernels (sht_any.h).
+
+#include <hip/hip_runtime.h>
+
+#include "sht_any.h"
+#include "sht_internal.h"
+
+namespace sht {
+
+// waves per SIMD the kernels are compiled for
+template <typename T>
+constexpr int any_wpe() {
+  return sizeof(T) == 4 ? 4 : 2;
+}
+
+template <typename T, int NT, bool VEC, int VW>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()))) void k_zonal_any_analysis(const FftArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  any_analysis_run<T, NT, VEC, VW>(a, blockIdx.x, a.nitems, smem_raw);
+}
+
+template <typename T, int NT, bool VEC, int VW>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()))) void k_zonal_any_synthesis(const FftArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  any_synthesis_run<T, NT, VEC, VW>(a, blockIdx.x, a.nitems, smem_raw);
+}
+
+// ---------------------------------------------------------------------------
+// launcher
+// ---------------------------------------------------------------------------
+constexpr size_t kAnyMaxLds = 160 * 1024;
+
+template <auto Kernel>
+static hipError_t any_go(const FftArgs& a, int NT, int wpe, size_t lds, int ncu, hipStream_t st) {
+  static size_t done = 0;
+  if (lds > 65536 && lds > done) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)kAnyMaxLds);
+    done = kAnyMaxLds;
+  }
+  // persistent workgroups, as many as fit at the kernels' waves per SIMD
+  int per_cu = (int)(kAnyMaxLds / lds);
+  per_cu = per_cu < wpe * 256 / NT ? per_cu : wpe * 256 / NT;
+  per_cu = per_cu < 1 ? 1 : per_cu;
+  const int nwg = ncu * per_cu < a.nitems ? ncu * per_cu : a.nitems;
+  hipLaunchKernelGGL(Kernel, dim3(nwg), dim3(NT), lds, st, a);
+  return hipGetLastError();
+}
+
+template <typename T, int NT, bool VEC, int VW>
+static hipError_t any_dir(bool analysis, const FftArgs& a, size_t lds, int ncu, hipStream_t st) {
+  return analysis ? any_go<k_zonal_any_analysis<T, NT, VEC, VW>>(a, NT, any_wpe<T>(), lds, ncu, st)
+                  : any_go<k_zonal_any_synthesis<T, NT, VEC, VW>>(a, NT, any_wpe<T>(), lds, ncu, st);
+}
+
+template <typename T>
+static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStream_t st) {
+  constexpr int E = AnyCap<T>::E;
+  FftArgs a = a0;
+  int maxI = 0, maxN = 0, maxIP = 0, maxF = 0;
+  bool vec = true;
+  for (int l = 0; l < a.nlev; ++l) {
+    const LevelDesc& L = a.lev[l];
+    maxI = L.I > maxI ? L.I : maxI;
+    maxN = L.N > maxN ? L.N : maxN;
+    maxF = L.F > maxF ? L.F : maxF;
+    const int ip = any_stride(L);
+    maxIP = ip > maxIP ? ip : maxIP;
+    vec = vec && L.I % (16 / (int)sizeof(T)) == 0;
+  }
+  // fields per item: as many as a workspace run holds, as long as two
+  // workgroups share a compute unit's LDS, no group is mostly empty and the
+  // device has two items per compute unit
+  auto lds_of = [&](int fc) { return (size_t)((size_t)fc * maxIP + maxI) * sizeof(cx<T>); };
+  auto items_of = [&](int fc) {
+    long long n = 0;
+    for (int l = 0; l < a.nlev; ++l) n += (long long)a.lev[l].Jh * ((a.lev[l].F + fc - 1) / fc);
+    return n;
+  };
+  int lfc = sizeof(T) == 4 ? 3 : 2;
+  while (lfc > 0 && ((1 << lfc) * (long long)maxI > 512LL * E || (1 << lfc) * (maxN + 1LL) > 256LL * E ||
+                     lds_of(1 << lfc) > kAnyMaxLds / 2 || (1 << (lfc - 1)) >= maxF || items_of(1 << lfc) < 2LL * ncu))
+    --lfc;
+  const int fc = 1 << lfc;
+  const bool small = fc * (long long)maxI <= 256LL * E && fc * (maxN + 1LL) <= 128LL * E;
+  a.lfc = lfc;
+  a.tw_lds = (fc * maxIP + 1) & ~1;
+  const size_t lds = ((size_t)a.tw_lds + maxI) * sizeof(cx<T>);
+  if (lds > kAnyMaxLds) return hipErrorInvalidValue;
+  long long items = 0;
+  for (int l = 0; l < a.nlev; ++l) {
+    LevelDesc& L = a.lev[l];
+    const int nv = vec ? L.I / (16 / (int)sizeof(T)) : L.I;
+    L.ivm = nv > 1 ? 0xFFFFFFFFu / (unsigned)nv + 1u : 0u;
+    L.nfb = (L.F + fc - 1) / fc;
+    L.fft_item0 = (int)items;
+    items += (long long)L.Jh * L.nfb;
+  }
+  if (items > 0x7fffffff) return hipErrorInvalidValue;
+  a.nitems = (int)items;
+  constexpr int VW = sizeof(T) == 4 ? 2 : 1;
+  if (VW == 2 && lfc == 0) {
+    if (small) return vec ? any_dir<T, 256, true, 1>(analysis, a, lds, ncu, st) : any_dir<T, 256, false, 1>(analysis, a, lds, ncu, st);
+    return vec ? any_dir<T, 512, true, 1>(analysis, a, lds, ncu, st) : any_dir<T, 512, false, 1>(analysis, a, lds, ncu, st);
+  }
+  if (small) return vec ? any_dir<T, 256, true, VW>(analysis, a, lds, ncu, st) : any_dir<T, 256, false, VW>(analysis, a, lds, ncu, st);
+  return vec ? any_dir<T, 512, true, VW>(analysis, a, lds, ncu, st) : any_dir<T, 512, false, VW>(analysis, a, lds, ncu, st);
+}
+
+int launch_zonal_any(bool dbl, bool analysis, const FftArgs& a, int ncu, void* stream) {
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  return (int)(dbl ? any_launch<double>(analysis, a, ncu, st) : any_launch<float>(analysis, a, ncu, st));
+}
+
+}  // namespace sht
