@@ -243,8 +243,8 @@ __device__ __forceinline__ int any_analysis_run(const FftArgs& a, int item, int 
 
     // fold: unit = (wavenumber, VW fields)
     const T rscale = row_scale<T>(a, L, it.jp);
-    T* ws = ws0 + L.ws_off + (long long)it.jp * 2 * L.Cp;
-    const long long plane2 = 2 * L.wplane;
+    T* ws = ws0 + L.ws_off + (it.jp / SHT_K_PAD) * L.wjb + (long long)(it.jp % SHT_K_PAD) * 2 * L.Cp;
+    const long long region = L.wblk;
     constexpr int LVW = VW == 2 ? 1 : 0;
     const int units = (N + 1) << (lfc - LVW);
     for (int x = threadIdx.x; x < units; x += NT) {
@@ -274,7 +274,7 @@ __device__ __forceinline__ int any_analysis_run(const FftArgs& a, int item, int 
         oA[2 * q] = A.x;
         oA[2 * q + 1] = A.y;
       }
-      T* d = ws + m * plane2 + ws_col(L.wsh, 0, 2 * fld);
+      T* d = ws + m * region + ws_col(L.wsh, 0, 2 * fld);
       typedef T TW __attribute__((ext_vector_type(2 * VW)));
       TW s, o;
 #pragma unroll
@@ -308,8 +308,9 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgs& a, int item, int
   auto load_ws = [&](int slot) __attribute__((always_inline)) {
     const AnyItem it = any_item(a, slot);
     const LevelDesc& L = a.lev[it.l];
-    const T* ws = ws0 + L.ws_off + (long long)it.jp * L.Cp + 2 * it.fg * FC;
-    const long long plane2 = 2 * L.wplane;
+    const int jb = it.jp / SHT_K_PAD;
+    const T* ws = ws0 + L.ws_off + jb * L.wjb + (long long)(it.jp % SHT_K_PAD) * L.Cp + 2 * it.fg * FC;
+    const long long region = L.wblk, odd = ws_odd(L.Jh, L.Cp, L.wblk, jb);
 #pragma unroll
     for (int u = 0; u < UM; ++u) {
       const int x = (int)threadIdx.x + u * NT;
@@ -319,9 +320,9 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgs& a, int item, int
       // rows below the first 128-latitude tile the Legendre synthesis
       // computes for this m (reduced transform) are zero
       if (m <= L.N && it.fg * FC + f0 < L.F && (!a.jstart || it.jp >= (a.jstart[L.m_base + m] & ~127))) {
-        const T* s = ws + m * plane2 + 2 * f0;
+        const T* s = ws + m * region + 2 * f0;
         pS[u] = *reinterpret_cast<const TW*>(s);
-        pA[u] = *reinterpret_cast<const TW*>(s + L.spoff);
+        pA[u] = *reinterpret_cast<const TW*>(s + odd);
       }
     }
   };

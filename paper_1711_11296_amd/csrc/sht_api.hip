@@ -235,18 +235,8 @@ int build_plan(int nlev, const int* Nv, const int* Jv, const int* Iv, const int*
     ncu = 256;
   // sht_forward_noalloc takes workspaces up to its static array's size
   const long long ws_limit = SHT_NOALLOC_WORKSPACE_BYTES;
-  int FB = zonal_fields_per_block(o.form, nlev, Nv[0], Jv[0], Iv[0], Fv[0]);
+  const int FB = zonal_fields_per_block(o.form);
   P->ncb = choose_granularity(o.form, P->otf != 0, nlev, Nv, Jv, Fv, FB, ncu, ws_limit);
-  if (FB > 8) {
-    // the wide blocking runs only in the fixed-length kernel, whose
-    // workspace offsets are 32-bit
-    const long long Cp = roundup(2LL * Fv[0], std::lcm(16 * P->ncb, 2 * FB));
-    const long long Kp = roundup((Jv[0] + 1) / 2, SHT_K_PAD);
-    if (!zonal_offsets_fit(ws_plane(Kp, Cp), (long long)P->elem)) {
-      FB = 8;
-      P->ncb = choose_granularity(o.form, P->otf != 0, nlev, Nv, Jv, Fv, FB, ncu, ws_limit);
-    }
-  }
   const int BN = 16 * P->ncb;
   P->fb = FB;
 
@@ -663,11 +653,14 @@ int run_forward_noalloc(sht_plan_s* P, const void* grid, void* spec, void* strea
   for (int l = 0; l < P->nlev; ++l) {
     const LevelDesc& L = P->lev[l];
     // an analysis row holds 2 Cp elements (both parities), Cp a multiple of
-    // 16; the regions are 2 wplane elements apart, wplane a multiple of 16
+    // 16; the regions of the last row block are wblk elements apart, wblk a
+    // multiple of 16
     const long long row16 = 2LL * L.Cp * (long long)P->elem / 16;
-    const long long region16 = 2LL * L.wplane * (long long)P->elem / 16;
-    const int e = launch_clear_span(static_cast<unsigned char*>(ws) + L.ws_off * (long long)P->elem,
-                                    (long long)(L.N + 1), region16, row16 * L.Jh, row16 * (L.Kp - L.Jh), stream);
+    const long long region16 = L.wblk * (long long)P->elem / 16;
+    const int jb = L.Kp / SHT_K_PAD - 1;
+    const int e = launch_clear_span(static_cast<unsigned char*>(ws) + (L.ws_off + jb * L.wjb) * (long long)P->elem,
+                                    (long long)(L.N + 1), region16, row16 * (L.Jh - SHT_K_PAD * jb),
+                                    row16 * (L.Kp - L.Jh), stream);
     if (e) return hip_check((hipError_t)e, "workspace clear launch");
   }
   const int saved_profile = P->profile;  // profiling would create events

@@ -27,7 +27,7 @@
 // parity, row) instead of one isolated complex value; the analysis stores
 // both parities of a row as one run of 4*FB values (ws_col).
 //
-// Workspace layout (per level): see ws_col and ws_plane; the analysis and
+// Workspace layout (per level): see ws_col and ws_block; the analysis and
 // the synthesis lay it out differently.
 
 #include <hip/hip_runtime.h>
@@ -38,6 +38,7 @@
 #include "sht_internal.h"
 #include "sht_any.h"
 #include "sht_dft.h"
+#include "sht_group.h"
 
 namespace sht {
 
@@ -101,19 +102,19 @@ __device__ __forceinline__ void quad_transpose(int (&x)[4][4]) {
 }
 
 // Store the runs v of the quad's four wavenumbers m - j .. m - j + 3
-// (j = lane in quad) at dst(m') = base + (2 m') * plane; runs with m' > N
+// (j = lane in quad) at dst(m') = base + m' * region; runs with m' > N
 // are skipped.  All lanes of the quad must call it.  base is uniform and the
 // 64 lanes of a wave hold consecutive wavenumbers: each address is a
 // uniform 64-bit base at the wave's first wavenumber plus a 32-bit per-lane
-// byte offset of fewer than 128 planes (zonal_offsets_fit).  A run of 2 FB
+// byte offset of fewer than 64 regions (zonal_offsets_fit).  A run of 2 FB
 // values is 64 or 128 bytes; a 128-byte run goes as two 64-byte halves.
 template <typename T, int FB>
-__device__ __forceinline__ void store_runs_quad(T* base, long long plane, int m, int N,
+__device__ __forceinline__ void store_runs_quad(T* base, long long region, int m, int N,
                                                 const cx<T> (&v)[FB]) {
   constexpr int HALVES = 2 * FB * (int)sizeof(T) / 64;
   static_assert(HALVES * 64 == 2 * FB * (int)sizeof(T) && HALVES <= 2, "64- or 128-byte runs");
   const int lane = threadIdx.x & 63, j = lane & 3;
-  const long long step64 = 2 * plane * (long long)sizeof(T);
+  const long long step64 = region * (long long)sizeof(T);
   const int mw = __builtin_amdgcn_readfirstlane(m - lane);  // the wave's first wavenumber
   char* b = reinterpret_cast<char*>(base) + (long long)mw * step64;
   const unsigned step = (unsigned)step64;
@@ -155,19 +156,6 @@ __device__ __forceinline__ void store_runs_quad(T* base, long long plane, int m,
 // is coalesced across the lanes); synthesis stores the last pass straight to
 // the grid rows (element j + t Ns3 of each of the two rows).
 // ---------------------------------------------------------------------------
-template <int I_, int R2_, int R3_>
-struct Plan3 {
-  static constexpr int I = I_, R1 = 16, R2 = R2_, R3 = R3_;
-  static_assert(R1 * R2 * R3 == I, "radices must multiply to I");
-  static constexpr int nb1 = I / R1, nb2 = I / R2, nb3 = I / R3;
-  static constexpr int Ns2 = R1, Ns3 = R1 * R2;
-  static_assert(nb3 == Ns3, "last pass");
-  static_assert(I % 16 == 0 && nb2 % 16 == 0, "padded layout");
-  static constexpr int IP = I + I / 16;        // padded field stride
-  static constexpr int S2P = nb2 + nb2 / 16;   // padded stride of pass-2 inputs
-  static constexpr int tw2 = 0, tw3 = (R2 - 1) * Ns2, ntw = tw3 + (R3 - 1) * Ns3;
-};
-
 template <typename T, class P, int NT, int FC>
 struct Fft3 {
   static constexpr int S1 = (FC * P::nb1 + NT - 1) / NT;
@@ -388,31 +376,14 @@ __device__ __forceinline__ int zonal_analysis_run_p3(const FftArgs& a, int l, in
     }
 
     const long long Cp = L.Cp;
-    const long long plane = L.wplane;
-    // the item's column blocks of W = min(2 FB, 16) columns (ws_col): the
-    // even run at the start of each, the odd one W elements later; a
-    // 16-field item's two blocks are written in address order (even and odd
-    // piece of the first block, then of the second), one 128-byte line after
-    // the other
-    constexpr int WB = 2 * FB < 16 ? 2 * FB : 16;
-    T* wrow = ws + (long long)jp * 2 * Cp + 4 * fb * FB;
+    const long long plane = L.wblk;
+    // the item's column block (ws_col): even run, then odd run
+    T* wrow = ws + (jp / SHT_K_PAD) * L.wjb + (long long)(jp % SHT_K_PAD) * 2 * Cp + 4 * fb * FB;
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
       const int m = threadIdx.x + s * NT;
-      if constexpr (2 * FB == WB) {
-        store_runs_quad<T, FB>(wrow, plane, m, N, stS[s]);
-        store_runs_quad<T, FB>(wrow + WB, plane, m, N, stA[s]);
-      } else {
-        static_assert(2 * FB == 2 * WB, "one or two column blocks per item");
-        typedef const cx<T>(&Half)[FB / 2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          store_runs_quad<T, FB / 2>(wrow + 2 * WB * h, plane, m, N,
-                                     reinterpret_cast<Half>(stS[s][h * (FB / 2)]));
-          store_runs_quad<T, FB / 2>(wrow + 2 * WB * h + WB, plane, m, N,
-                                     reinterpret_cast<Half>(stA[s][h * (FB / 2)]));
-        }
-      }
+      store_runs_quad<T, FB>(wrow, plane, m, N, stS[s]);
+      store_runs_quad<T, FB>(wrow + 2 * FB, plane, m, N, stA[s]);
     }
   }
   return item;
@@ -437,7 +408,7 @@ __device__ __forceinline__ int zonal_synthesis_run_p3(const FftArgs& a, int l, i
   const T msc = (T)a.mscale;
   const int N = L.N, J = L.J;
   const long long Cp = L.Cp;
-  const long long plane = L.wplane;
+  const long long plane = L.wblk;
 
   cx<T> stS[MS][FB], stA[MS][FB];
   auto load_ws = [&](int slot) __attribute__((always_inline)) {
@@ -446,7 +417,9 @@ __device__ __forceinline__ int zonal_synthesis_run_p3(const FftArgs& a, int l, i
     // the runs of the wave's 64 consecutive wavenumbers: a uniform base at
     // its first wavenumber plus 32-bit lane offsets (zonal_offsets_fit)
     const int lane = threadIdx.x & 63;
-    const unsigned lstep = (unsigned)(2 * plane * (long long)sizeof(T));
+    const unsigned lstep = (unsigned)(plane * (long long)sizeof(T));
+    const int jb = jp / SHT_K_PAD;
+    const long long odd = ws_odd(L.Jh, Cp, L.wblk, jb);
 #pragma unroll
     for (int s = 0; s < MS; ++s) {
       const int m = threadIdx.x + s * NT;
@@ -454,10 +427,11 @@ __device__ __forceinline__ int zonal_synthesis_run_p3(const FftArgs& a, int l, i
       // computes for this m (reduced transform) are zero
       if (m <= N && (!a.jstart || jp >= (a.jstart[L.m_base + m] & ~127))) {
         const int mw = __builtin_amdgcn_readfirstlane(m - lane);
-        const char* wb = reinterpret_cast<const char*>(ws + (2LL * mw) * plane + (long long)jp * Cp + 2 * fb * FB);
+        const char* wb = reinterpret_cast<const char*>(ws + jb * L.wjb + mw * plane +
+                                                       (long long)(jp % SHT_K_PAD) * Cp + 2 * fb * FB);
         const T* sS = reinterpret_cast<const T*>(wb + (unsigned)lane * lstep);
         load_run<T, FB>(sS, stS[s]);
-        load_run<T, FB>(sS + L.spoff, stA[s]);
+        load_run<T, FB>(sS + odd, stA[s]);
       } else {
 #pragma unroll
         for (int q = 0; q < FB; ++q) stS[s][q] = stA[s][q] = cx<T>{(T)0, (T)0};
@@ -540,7 +514,7 @@ __global__ __launch_bounds__(NT) void k_zonal_synthesis_p3(const FftArgs a) {
 
 // ---------------------------------------------------------------------------
 // Multi-level plans in one launch.  A configuration says how a level runs:
-// with a compile-time three-pass plan (ZP3) or with runtime radices (ZRt).
+// with a compile-time three-pass plan (ZGrp) or with runtime radices (ZRt).
 // The persistent workgroups of k_zonal_levels walk their slots in increasing
 // order, which visits the levels one after the other, each as a contiguous
 // run of slots (every level's items are spread over all XCDs, see xcd_map);
@@ -548,18 +522,19 @@ __global__ __launch_bounds__(NT) void k_zonal_synthesis_p3(const FftArgs a) {
 // is reused by the next run after a barrier.  One launch therefore covers
 // every level, with no idle tail between levels.
 // ---------------------------------------------------------------------------
-template <class P, int FC, int MS>
-struct ZP3 {
-  template <typename T>
+template <class P, int FC>
+struct ZGrp {
+  static constexpr int fc = FC;
+  template <typename T, int NT>
   static constexpr size_t lds() {
-    return (size_t)(FC * P::IP + P::ntw) * sizeof(cx<T>);
+    return Grp<T, P, NT, FC, false>::lds();
   }
   template <typename T, int NT, int FB, bool ANA>
   static __device__ __forceinline__ int run(const FftArgs& a, int l, int item, unsigned char* smem) {
     if constexpr (ANA)
-      return zonal_analysis_run_p3<T, P, NT, FB, FC, MS>(a, l, item, smem);
+      return Grp<T, P, NT, FC, false>::analysis(a, l, item, smem);
     else
-      return zonal_synthesis_run_p3<T, P, NT, FB, FC, MS>(a, l, item, smem);
+      return Grp<T, P, NT, FC, false>::synthesis(a, l, item, smem);
   }
 };
 
@@ -587,7 +562,7 @@ __device__ __forceinline__ int zonal_run_cfg(const FftArgs& a, int k, int l, int
 }
 
 template <typename T, int NT, int FB, bool ANA, class... Cs>
-__global__ __launch_bounds__(NT) void k_zonal_levels(const FftArgs a) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_zonal_levels(const FftArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   int item = blockIdx.x;
   while (item < a.nitems) {
@@ -615,8 +590,8 @@ static void lds_optin(size_t bytes) {
 
 static int g_num_cu = 0;
 
-template <typename T, class P, int NT, int FB, int FC, int MS>
-static hipError_t launch_p3_ms(bool analysis, const FftArgs& a, hipStream_t st) {
+template <typename T, class P, int NT, int FB, int FC, int MS, bool ANA>
+static hipError_t launch_p3_ms(const FftArgs& a, hipStream_t st) {
   const size_t lds = (size_t)(FC * P::IP + P::ntw) * sizeof(cx<T>);
   int per_cu = (int)(kMaxLds / lds);
   const int by_waves = 2048 / NT;
@@ -625,7 +600,7 @@ static hipError_t launch_p3_ms(bool analysis, const FftArgs& a, hipStream_t st) 
   int nwg = g_num_cu * per_cu;
   nwg = nwg < a.nitems ? nwg : a.nitems;
   const dim3 grid(nwg), block(NT);
-  if (analysis) {
+  if constexpr (ANA) {
     lds_optin<k_zonal_analysis_p3<T, P, NT, FB, FC, MS>>(lds);
     hipLaunchKernelGGL((k_zonal_analysis_p3<T, P, NT, FB, FC, MS>), grid, block, lds, st, a);
   } else {
@@ -635,17 +610,39 @@ static hipError_t launch_p3_ms(bool analysis, const FftArgs& a, hipStream_t st) 
   return hipGetLastError();
 }
 
-template <typename T, class P, int NT, int FB, int FC>
-static hipError_t launch_p3(bool analysis, const FftArgs& a, int maxN, hipStream_t st) {
-  static_assert(FB % FC == 0, "field rounds");
+// Two fields per round (four spill registers and cost ~5 %) on 512 threads.
+template <typename T, int FB, bool ANA, class P>
+static hipError_t launch_p3(const FftArgs& a, int maxN, hipStream_t st) {
+  constexpr int NT = 512, FC = 2;
   constexpr int MSMAX = ((P::I + 1) / 2 + NT - 1) / NT;  // N + 1 <= (I + 1) / 2
-  static_assert(MSMAX <= 3, "wavenumbers per thread");
+  static_assert(MSMAX == 3, "wavenumbers per thread");
   const int nm = maxN + 1;
-  if constexpr (MSMAX >= 3)
-    if (nm > 2 * NT) return launch_p3_ms<T, P, NT, FB, FC, 3>(analysis, a, st);
-  if constexpr (MSMAX >= 2)
-    if (nm > NT) return launch_p3_ms<T, P, NT, FB, FC, 2>(analysis, a, st);
-  return launch_p3_ms<T, P, NT, FB, FC, 1>(analysis, a, st);
+  if (nm > 2 * NT) return launch_p3_ms<T, P, NT, FB, FC, 3, ANA>(a, st);
+  if (nm > NT) return launch_p3_ms<T, P, NT, FB, FC, 2, ANA>(a, st);
+  return launch_p3_ms<T, P, NT, FB, FC, 1, ANA>(a, st);
+}
+
+// Lengths past 2048 whose S and A runs are better held in registers: FP32
+// analysis (64 fields, 1601 rows, group kernels in brackets: I = 2304 398
+// (450), 2560 456 (523), 2880 497 (599), 3072 516 us (657)) and FP64
+// synthesis (2880, 48 fields, 801 rows: 422 (440)).  With 4 fields of a block
+// per item, which is all the LDS holds there, the group kernels' analysis
+// stores 32-byte pieces.  Up to three wavenumbers per thread (I <= 3072).
+template <typename T, int FB, bool ANA>
+static bool launch_held(const FftArgs& a, int maxN, hipStream_t st, hipError_t* err) {
+  if constexpr ((sizeof(T) == 4) != ANA) {
+    return false;
+  } else {
+    switch (a.lev[0].I) {
+      case 2160: *err = launch_p3<T, FB, ANA, Plan3<2160, 9, 15>>(a, maxN, st); return true;
+      case 2304: *err = launch_p3<T, FB, ANA, Plan3<2304, 12, 12>>(a, maxN, st); return true;
+      case 2400: *err = launch_p3<T, FB, ANA, Plan3<2400, 10, 15>>(a, maxN, st); return true;
+      case 2560: *err = launch_p3<T, FB, ANA, Plan3<2560, 16, 10>>(a, maxN, st); return true;
+      case 2880: *err = launch_p3<T, FB, ANA, Plan3<2880, 12, 15>>(a, maxN, st); return true;
+      case 3072: *err = launch_p3<T, FB, ANA, Plan3<3072, 16, 12>>(a, maxN, st); return true;
+      default: return false;
+    }
+  }
 }
 
 // Single-level plans whose I has a compile-time three-pass plan.
@@ -654,58 +651,15 @@ static bool launch_fixed(bool analysis, const FftArgs& a, int maxN, hipStream_t 
   if (a.nlev != 1) return false;
   // the fixed-length kernels address the workspace with 32-bit offsets
   // from a per-wave base
-  const LevelDesc& L = a.lev[0];
-  if (!zonal_offsets_fit(L.wplane, sizeof(T))) return false;
-  constexpr bool dbl = sizeof(T) == 8;
-  switch (a.lev[0].I) {
-    case 2880:
-      if constexpr (FB > 8) return false;  // several wavenumbers per thread: 8 fields at most
-      else {
-        // two fields per round (four spill registers and ~5 % more time with
-        // four); 512 threads: 768- and 1024-thread workgroups (one per CU,
-        // more waves) spill and measured 10-50 % slower at T959
-        *err = launch_p3<T, Plan3<2880, 12, 15>, 512, FB, 2>(analysis, a, maxN, st);
-        return true;
-      }
-    case 1440:
-      *err = launch_p3<T, Plan3<1440, 9, 10>, 512, FB, dbl ? 2 : 4>(analysis, a, maxN, st);
-      return true;
-    case 480:
-      *err = launch_p3<T, Plan3<480, 6, 5>, 256, FB, dbl ? 4 : 8>(analysis, a, maxN, st);
-      return true;
-    case 1920:
-      if constexpr (FB > 8) return false;
-      else {
-        *err = launch_p3<T, Plan3<1920, 12, 10>, 512, FB, dbl ? 2 : 4>(analysis, a, maxN, st);
-        return true;
-      }
-    case 960:
-      if constexpr (FB > 8) return false;
-      else {
-        *err = launch_p3<T, Plan3<960, 6, 10>, 512, FB, dbl ? 2 : 4>(analysis, a, maxN, st);
-        return true;
-      }
-    case 1600:
-      if constexpr (FB > 8) return false;
-      else {
-        *err = launch_p3<T, Plan3<1600, 10, 10>, 512, FB, dbl ? 2 : 4>(analysis, a, maxN, st);
-        return true;
-      }
-    case 800:
-      if constexpr (FB > 8) return false;
-      else {
-        *err = launch_p3<T, Plan3<800, 5, 10>, 256, FB, 4>(analysis, a, maxN, st);
-        return true;
-      }
-    case 400:
-      if constexpr (FB > 8) return false;
-      else {
-        *err = launch_p3<T, Plan3<400, 5, 5>, 256, FB, dbl ? 4 : 8>(analysis, a, maxN, st);
-        return true;
-      }
-    default:
-      return false;
-  }
+  if (!zonal_offsets_fit(a.lev[0].wblk, sizeof(T))) return false;
+  if (analysis ? launch_held<T, FB, true>(a, maxN, st, err) : launch_held<T, FB, false>(a, maxN, st, err)) return true;
+  const int e = sizeof(T) == 8 ? (analysis ? launch_zonal_group_analysis_f64(a, g_num_cu, st)
+                                           : launch_zonal_group_synthesis_f64(a, g_num_cu, st))
+                               : (analysis ? launch_zonal_group_analysis_f32(a, g_num_cu, st)
+                                           : launch_zonal_group_synthesis_f32(a, g_num_cu, st));
+  if (e < 0) return false;
+  *err = (hipError_t)e;
+  return true;
 }
 
 // compute units of the current device (persistent grids are sized by it)
@@ -730,9 +684,9 @@ template <typename T>
 struct ZLevels {
   static constexpr bool dbl = sizeof(T) == 8;
   static constexpr int NT = 512;
-  using C1600 = ZP3<Plan3<1600, 10, 10>, dbl ? 2 : 4, 2>;
-  using C800 = ZP3<Plan3<800, 5, 10>, 4, 1>;
-  using C400 = ZP3<Plan3<400, 5, 5>, dbl ? 4 : 8, 1>;
+  using C1600 = ZGrp<Plan3<1600, 10, 10>, 4>;
+  using C800 = ZGrp<Plan3<800, 10, 5>, dbl ? 4 : 8>;
+  using C400 = ZGrp<Plan3<400, 5, 5>, dbl ? 4 : 8>;
   template <bool VEC>
   using CRt = ZRt<VEC, 1024>;
   template <int FB, bool ANA, bool VEC>
@@ -763,9 +717,12 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
     if (L.I == 1600 || L.I == 800 || L.I == 400) {
       // the three-pass kernels address the workspace with 32-bit offsets
       // from a per-wave base
-      if (!zonal_offsets_fit(L.wplane, sizeof(T))) return false;
+      if (!zonal_offsets_fit(L.wblk, sizeof(T))) return false;
       k = L.I == 1600 ? 0 : L.I == 800 ? 1 : 2;
-      need = k == 0 ? C1600::template lds<T>() : k == 1 ? C800::template lds<T>() : C400::template lds<T>();
+      need = k == 0 ? C1600::template lds<T, NT>() : k == 1 ? C800::template lds<T, NT>() : C400::template lds<T, NT>();
+      const int fc = k == 0 ? C1600::fc : k == 1 ? C800::fc : C400::fc;
+      if ((double)fc * L.J * L.I * sizeof(T) >= 4294967296.0) return false;
+      b.lev[l].nfb = (L.F + fc - 1) / fc;
     } else {
       if (L.I > ZLevels<T>::template CRt<true>::maxi || L.N + 1 > NT) return false;
       k = 3;
@@ -788,22 +745,24 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
     b.lfc = FB == 8 ? 3 : 2;
     while ((maxIrt << b.lfc) > NT * E || (2 * (maxNrt + 1) << b.lfc) > NT * E) --b.lfc;
     b.tw_lds = ((maxIP << b.lfc) + 1) & ~1;
-    b.nitems = 0;
-    for (int l = 0; l < a.nlev; ++l) {
-      LevelDesc& L = b.lev[l];
-      if (L.zk == 3) {
-        const int nv = vec ? L.I / (16 / (int)sizeof(T)) : L.I;
-        L.ivm = nv > 1 ? 0xFFFFFFFFu / (unsigned)nv + 1u : 0u;
-        L.nfb = (L.F + (1 << b.lfc) - 1) >> b.lfc;
-      }
-      L.fft_item0 = b.nitems;
-      b.nitems += L.Jh * L.nfb;
-    }
     const size_t rt = (size_t)(b.tw_lds + maxIrt) * sizeof(cx<T>);
     lds = rt > lds ? rt : lds;
   }
+  long long items = 0;
+  for (int l = 0; l < a.nlev; ++l) {
+    LevelDesc& L = b.lev[l];
+    if (L.zk == 3) {
+      const int nv = vec ? L.I / (16 / (int)sizeof(T)) : L.I;
+      L.ivm = nv > 1 ? 0xFFFFFFFFu / (unsigned)nv + 1u : 0u;
+      L.nfb = (L.F + (1 << b.lfc) - 1) >> b.lfc;
+    }
+    L.fft_item0 = (int)items;
+    items += (long long)L.Jh * L.nfb;
+    if (items > 0x7fffffff) return false;
+  }
+  b.nitems = (int)items;
   int per_cu = (int)(kMaxLds / lds);
-  const int by_waves = 2048 / NT;
+  constexpr int by_waves = (sizeof(T) == 4 ? 1024 : 512) / NT;  // waves per SIMD of k_zonal_levels
   per_cu = per_cu < by_waves ? per_cu : by_waves;
   per_cu = per_cu < 1 ? 1 : per_cu;
   int nwg = g_num_cu * per_cu;
@@ -877,27 +836,13 @@ int zonal_one_launch_spills(int form, bool analysis) {
   return fa.localSizeBytes > 0 ? 1 : 0;
 }
 
-int zonal_fields_per_block(int form, int nlev, int N, int J, int I, int F) {
-  if (form == SHT_FORM_FP64) return 4;
-  // wide items halve the item count: only where plenty remain for 256 CUs
-  const long long items16 = (long long)((J + 1) / 2) * ((F + 15) / 16);
-  if (nlev == 1 && items16 >= 4096 && ((I == 1440 && N + 1 <= 512) || (I == 480 && N + 1 <= 256))) return 16;
-  return 8;
-}
-
 int launch_zonal(int form, bool analysis, const FftArgs& a, int maxN, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   // the kernels' item width must match every level's analysis column block
-  const int fb = form == SHT_FORM_FP64 ? 4 : (a.fb == 16 ? 16 : 8);
+  const int fb = form == SHT_FORM_FP64 ? 4 : 8;
   for (int l = 0; l < a.nlev; ++l)
     if ((1 << a.lev[l].wsh) != (2 * fb < 16 ? 2 * fb : 16)) return (int)hipErrorInvalidValue;
   if (form == SHT_FORM_FP64) return (int)launch_zonal_t<double, 4>(analysis, a, maxN, st);
-  if (a.fb == 16) {
-    ensure_num_cu();
-    hipError_t err = hipErrorInvalidValue;
-    if (!launch_fixed<float, 16>(analysis, a, maxN, st, &err)) return (int)hipErrorInvalidValue;
-    return (int)err;
-  }
   return (int)launch_zonal_t<float, 8>(analysis, a, maxN, st);
 }
 

@@ -51,8 +51,8 @@ struct LevelDesc {
   long long grid_off;  // element offset of this level in the grid buffer
   long long spec_off;  // element offset of this level in the spec buffer
   long long ws_off;    // element offset in the workspace
-  long long wplane;    // half the workspace elements from one wavenumber's region to the next (ws_plane)
-  long long spoff;     // synthesis: offset of the odd-parity plane in a region (wplane, or Jh Cp when Kp > Jh)
+  long long wblk;      // workspace elements from one wavenumber's region to the next (ws_block)
+  long long wjb;       // and from one block of 32 latitude rows to the next, (N + 1) wblk
   const void* tw;      // I twiddles exp(-2 pi i k / I), complex, data type
   const double* wrow;  // Jh quadrature weights of the northern rows
   const double* murow; // Kp nodes mu_j of the northern rows, zero past Jh (analysis with generated P~)
@@ -106,46 +106,58 @@ struct GemmArgs {
 
 // ---- kernel launchers (sht_fft.hip, sht_legendre.hip) ----
 // The stream argument is a hipStream_t.
-// Fields per zonal work item: 4 (FP64) or 8, and 16 for large single-level
-// FP32-data plans whose fixed-length kernel holds one wavenumber per thread
-// (I = 1440 or 480), so that every workspace run is a whole 128-byte line.
-// The level's workspace size with that blocking must be below 4 GiB (the
-// planner checks and falls back to 8).
-int zonal_fields_per_block(int form, int nlev, int N, int J, int I, int F);
-// Workspace layout (per level).  The region of wavenumber m starts
-// 2 wplane elements after that of m - 1 and holds Kp rows j of 2 Cp
-// elements (rows j >= ceil(J/2) stay zero), for the columns
-// c = 2 field + {re, im} < Cp of both parities p.  The two directions use
-// it differently (each writes and reads its own):
-// * synthesis (and forward adjoint): two planes, parity p at p spoff,
-//   row j < ceil(J/2) at j Cp, column c; spoff = wplane, or ceil(J/2) Cp
-//   when Kp > ceil(J/2), so that these planes never overlap the rows the
-//   analysis keeps zero;
-// * analysis (and inverse adjoint): row j at 2 j Cp holds both parities in
+// Fields per column block of the analysis workspace (and per item of the
+// zonal kernels that hold their runs in registers).
+inline int zonal_fields_per_block(int form) { return form == SHT_FORM_FP64 ? 4 : 8; }
+// Workspace layout (per level).  The latitude rows j < Kp come in blocks of
+// 32; block jb holds, for every wavenumber m, one region of 32 rows of 2 Cp
+// elements, the regions of consecutive m next to each other: region (jb, m)
+// starts at jb wjb + m wblk, wjb = (N + 1) wblk.  The rows j >= ceil(J/2) of
+// the last block stay zero.  A row holds the columns c = 2 field + {re, im}
+// < Cp of both parities p.  (With all rows of one m in one region, a zonal
+// item, which touches one row of every m, met another page at every
+// wavenumber: regions 3 MB apart at T479 with 400 fields.  Blocks of 32 rows
+// bring them within a few KB, and a Legendre tile still reads whole K blocks
+// as one run.)
+// The two directions use a region differently (each writes and reads its own):
+// * synthesis (and forward adjoint): two planes, row r of the block at r Cp,
+//   column c, the odd parity's plane ws_odd elements after the even one's:
+//   behind the block's existing rows, so that the planes never overlap the
+//   rows the analysis keeps zero;
+// * analysis (and inverse adjoint): row r at 2 r Cp holds both parities in
 //   blocks of W = 2^wsh = min(2 FB, 16) columns, [column block][parity][W]
-//   (ws_col): the columns of a zonal work item are one block (two for
-//   16-field items), so the item's stores for one m are one contiguous run
-//   of 4 FB elements (128 bytes for 8 FP32 fields), and each latitude row
-//   of a Legendre analysis tile is one run over both parities.
+//   (ws_col): the stores of a block's FB fields for one m are one contiguous
+//   run of 4 FB elements (128 bytes), and each latitude row of a Legendre
+//   analysis tile is one run over both parities.
 // Offset of (parity, column c) within an analysis row:
 constexpr int ws_col(int wsh, int par, int c) {
   return ((c >> wsh) << (wsh + 1)) + (par << wsh) + (c & ((1 << wsh) - 1));
 }
-// wplane is one parity's share of a region, Kp Cp elements, plus a pad, so
-// that the regions of consecutive wavenumbers (one wave's 64 lanes in the
-// zonal kernels) do not start at the same offset modulo the large powers of
-// two that HBM channels are interleaved by.
-constexpr long long kWsPlanePad = 32;  // elements (a multiple of 16; chosen by measurement)
-inline long long ws_plane(long long Kp, long long Cp) { return Kp * Cp + kWsPlanePad; }
-// The fixed-length zonal kernels address the workspace with 32-bit byte
-// offsets from a per-wave base: 64 wavenumbers x 2 wplane must stay below
-// 4 GiB (else the runtime-radix kernels run).
-inline bool zonal_offsets_fit(long long wplane, long long elem) {
-  return 128.0 * (double)wplane * (double)elem < 4294967296.0;
+// A region's 32 rows plus a pad of 256 bytes: an odd number of 256-byte
+// pieces, so that the regions of consecutive wavenumbers (one wave's lanes in
+// the zonal kernels) start on different HBM channels.
+constexpr long long ws_block(long long Cp, int elem, bool pad) {
+  return 2LL * SHT_K_PAD * Cp + (pad ? 256 / elem : 0);
 }
+// Synthesis: offset of the odd-parity plane in a region of block jb; in a
+// whole block half the region's pad lies between the planes (the two loads of
+// one wavenumber would otherwise meet the same channel).
+constexpr long long ws_odd(int Jh, long long Cp, long long wblk, int jb) {
+  return Jh - SHT_K_PAD * jb < SHT_K_PAD ? (Jh - SHT_K_PAD * jb) * Cp : wblk / 2;
+}
+// The fixed-length zonal kernels address the workspace with 32-bit byte
+// offsets from a per-wave base: 64 regions must stay below 4 GiB (else the
+// any-length kernels run).
+inline bool zonal_offsets_fit(long long wblk, long long elem) { return 64.0 * (double)wblk * (double)elem < 4294967296.0; }
 // 1 if the one-launch multi-level zonal kernel of this form and direction
 // keeps values in scratch memory (register spills), else 0
 int zonal_one_launch_spills(int form, bool analysis);
+// Lengths 16 R2 R3 of a single level (sht_group.h): -1 where these kernels do
+// not take the level, else a hipError_t; ncu compute units.
+int launch_zonal_group_analysis_f32(const FftArgs& a, int ncu, void* stream);
+int launch_zonal_group_synthesis_f32(const FftArgs& a, int ncu, void* stream);
+int launch_zonal_group_analysis_f64(const FftArgs& a, int ncu, void* stream);
+int launch_zonal_group_synthesis_f64(const FftArgs& a, int ncu, void* stream);
 // Any lengths (sht_zonal_any.hip); ncu compute units.
 int launch_zonal_any(bool dbl, bool analysis, const FftArgs& a, int ncu, void* stream);
 int launch_zonal(int form, bool analysis, const FftArgs& a, int maxN, void* stream);

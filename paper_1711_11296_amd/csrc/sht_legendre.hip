@@ -17,7 +17,7 @@
 // kernel streams it (analysis: rows r = n - m padded to 128 by Kp columns j;
 // synthesis: 128-latitude tiles by blocks of 32 natural rows; zero padding;
 // see the kernels below).  The split-bfloat16 kernels read the same FP32
-// copies.  Workspace layouts: see ws_col and ws_plane (the analysis reads
+// copies.  Workspace layouts: see ws_col and ws_block (the analysis reads
 // rows of both parities interleaved in column blocks, the synthesis writes
 // one plane per parity).
 //
@@ -158,8 +158,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   const int c0 = t.cb * BN;
   const int Kp = L.Kp;
   const long long Cp = L.Cp;
-  const long long plane = L.wplane;
-  const T* wsm = static_cast<const T*>(g.ws) + L.ws_off + (2LL * m) * plane;  // region m
+  const T* wsm = static_cast<const T*>(g.ws) + L.ws_off + m * L.wblk;  // region m of row block 0
+  const long long wjb = L.wjb;
 
   const int tid = threadIdx.x;
   // wave-uniform values live in scalar registers
@@ -242,7 +242,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
     dofs[i] = (unsigned)(k * 2 * (int)Cp + ws_col(L.wsh, par, c0 + col)) * (unsigned)sizeof(T);
   }
   auto dma1 = [&](int i, int kb, int stage) __attribute__((always_inline)) {
-    load_to_lds16(reinterpret_cast<const char*>(wsm + (long long)kb * KB * 2 * Cp) + dofs[i],
+    // K block kb: rows KB kb .. of row block KB kb / 32
+    const long long ko = KB == SHT_K_PAD ? kb * wjb : (kb >> 1) * wjb + (kb & 1) * (KB * 2 * Cp);
+    load_to_lds16(reinterpret_cast<const char*>(wsm + ko) + dofs[i],
                   Bs + stage * S::STAGE + chunk(i) * 64 * E);
   };
   auto dma = [&](int kb, int stage) __attribute__((always_inline)) {
@@ -641,8 +643,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
   }
 
   if (!active) return;
-  const long long plane = L.wplane;
-  T* ws = static_cast<T*>(g.ws) + L.ws_off + (2LL * m) * plane + p * L.spoff;
+  // the wave's 32 latitudes are one row block
+  const int jblk = jt * 4 + q;
+  T* ws = static_cast<T*>(g.ws) + L.ws_off + jblk * L.wjb + m * L.wblk + p * ws_odd(L.Jh, Cp, L.wblk, jblk);
 #pragma unroll
   for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
@@ -650,7 +653,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
       const int j = jt * 128 + 32 * q + 16 * jb + out_row<T>(lg, i);
       if (j < L.Jh) {
 #pragma unroll
-        for (int c = 0; c < NCB; ++c) ws[(long long)j * Cp + c0 + c * 16 + li] = acc[jb][c][i];
+        for (int c = 0; c < NCB; ++c) ws[(j % SHT_K_PAD) * Cp + c0 + c * 16 + li] = acc[jb][c][i];
       }
     }
 }

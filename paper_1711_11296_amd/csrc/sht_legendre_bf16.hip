@@ -180,8 +180,8 @@ __global__ __launch_bounds__(X6Analysis<NCB>::NT) __attribute__((amdgpu_waves_pe
   const int c0 = t.cb * BN;
   const int Kp = L.Kp;
   const long long Cp = L.Cp;
-  const long long plane = L.wplane;
-  const float* wsm = static_cast<const float*>(g.ws) + L.ws_off + (2LL * m) * plane;  // region m
+  const float* wsm = static_cast<const float*>(g.ws) + L.ws_off + m * L.wblk;  // region m of row block 0
+  const long long wjb = L.wjb;
 
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(X6Analysis<NCB>::NT) __attribute__((amdgpu_waves_pe
     for (int i = 0; i < TR; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        braw[set][i][e] = *reinterpret_cast<const f4*>(bsrc[i] + (long long)(kb * KB + 4 * e) * 2 * Cp);
+        braw[set][i][e] = *reinterpret_cast<const f4*>(bsrc[i] + kb * wjb + (long long)(4 * e) * 2 * Cp);
   };
   auto split_a = [&](int set) __attribute__((always_inline)) {
 #pragma unroll
@@ -678,8 +678,9 @@ __global__ __launch_bounds__(X6Synthesis<NCB>::NT) __attribute__((amdgpu_waves_p
   }
 
   if (!active) return;
-  const long long plane = L.wplane;
-  float* ws = static_cast<float*>(g.ws) + L.ws_off + (2LL * m) * plane + p * L.spoff;
+  // the wave's 32 latitudes are one row block
+  const int jblk = jt * 4 + q;
+  float* ws = static_cast<float*>(g.ws) + L.ws_off + jblk * L.wjb + m * L.wblk + p * ws_odd(L.Jh, Cp, L.wblk, jblk);
 #pragma unroll
   for (int jb = 0; jb < 2; ++jb)
 #pragma unroll
@@ -687,7 +688,7 @@ __global__ __launch_bounds__(X6Synthesis<NCB>::NT) __attribute__((amdgpu_waves_p
       const int j = jt * 128 + 32 * q + 16 * jb + 4 * lg + i;
       if (j < L.Jh) {
 #pragma unroll
-        for (int c = 0; c < NCB; ++c) ws[(long long)j * Cp + c0 + c * 16 + li] = acc[jb][c][i];
+        for (int c = 0; c < NCB; ++c) ws[(j % SHT_K_PAD) * Cp + c0 + c * 16 + li] = acc[jb][c][i];
       }
     }
 }

@@ -75,7 +75,7 @@ int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J,
       long long ws = 0;
       for (int l = 0; l < nlev; ++l) {
         Cp[l] = roundup(2LL * F[l], std::lcm(16LL * g, 2LL * FB));
-        ws += (N[l] + 1) * 2LL * ws_plane(roundup((J[l] + 1) / 2, SHT_K_PAD), Cp[l]) * elem;
+        ws += (N[l] + 1) * ws_block(Cp[l], elem, false) * (((J[l] + 1) / 2 + SHT_K_PAD - 1) / SHT_K_PAD) * elem;
       }
       if (pass == 0) {
         if (least == 0 || ws < least) least = ws;
@@ -106,6 +106,17 @@ void layout_levels(int nlev, const int* Nv, const int* Jv, const int* Iv, const 
   Layout& Y = *out;
   Y = Layout();
   long long moff = 0;
+  // the pads are left out where they would lift a workspace over the size of
+  // sht_forward_noalloc's static array
+  const int elem = FB == 4 ? 8 : 4;
+  long long bare = 0, padded = 0;
+  for (int l = 0; l < nlev; ++l) {
+    const long long Cp = roundup(2LL * Fv[l], std::lcm(BN, 2 * FB));
+    const long long n = (Nv[l] + 1) * (((Jv[l] + 1) / 2 + SHT_K_PAD - 1) / SHT_K_PAD);
+    bare += n * ws_block(Cp, elem, false) * elem;
+    padded += n * ws_block(Cp, elem, true) * elem + 64 * elem;
+  }
+  const bool pad = padded <= (long long)SHT_NOALLOC_WORKSPACE_BYTES || bare > (long long)SHT_NOALLOC_WORKSPACE_BYTES;
   for (int l = 0; l < nlev; ++l) {
     LevelDesc& L = lev[l];
     std::memset(&L, 0, sizeof(L));
@@ -137,9 +148,9 @@ void layout_levels(int nlev, const int* Nv, const int* Jv, const int* Iv, const 
     L.spec_off = Y.spec;
     Y.spec += (long long)L.F * (L.N + 1) * (L.N + 2);
     L.ws_off = Y.ws;
-    L.wplane = ws_plane(L.Kp, L.Cp);
-    L.spoff = L.Kp == L.Jh ? L.wplane : (long long)L.Jh * L.Cp;
-    Y.ws += roundup((long long)(L.N + 1) * 2 * L.wplane, 64);
+    L.wblk = ws_block(L.Cp, elem, pad);
+    L.wjb = (L.N + 1) * L.wblk;
+    Y.ws += roundup(L.Kp / SHT_K_PAD * L.wjb, 64);
     for (int m = 0; m <= L.N; ++m) {
       Y.taboff.push_back(Y.tab);
       // analysis copy: rows padded to the row tile of 128
@@ -156,8 +167,13 @@ void layout_levels(int nlev, const int* Nv, const int* Jv, const int* Iv, const 
     SHT_ASSERT(L.Kp % SHT_K_PAD == 0 && L.Kp >= L.Jh);
     // the synthesis planes stay inside the region and off the rows the
     // analysis keeps zero (rows Jh .. Kp of its layout, 2 Cp elements each)
-    SHT_ASSERT(L.spoff + (long long)L.Jh * L.Cp <= 2 * L.wplane &&
-               (L.Kp == L.Jh || L.spoff + (long long)L.Jh * L.Cp <= 2LL * L.Jh * L.Cp));
+    for (int jb = 0; jb < L.Kp / SHT_K_PAD; ++jb) {
+      const int rows = std::min(SHT_K_PAD, L.Jh - SHT_K_PAD * jb);
+      const long long odd = ws_odd(L.Jh, L.Cp, L.wblk, jb);
+      SHT_ASSERT(rows > 0 && odd >= rows * (long long)L.Cp && odd + rows * (long long)L.Cp <= L.wblk);
+      SHT_ASSERT(rows == SHT_K_PAD || odd + rows * (long long)L.Cp <= 2LL * rows * L.Cp);
+      SHT_ASSERT(odd % 16 == 0 && L.wblk % 16 == 0);
+    }
   }
   // one sentinel past the last (level, m): block m of a level spans
   // [off[m], off[m + 1])

@@ -1,0 +1,69 @@
+"""Row lengths 16 R2 R3 of the group kernels: every length once in each
+element type, N from a few wavenumbers to (I - 1) / 2, field counts with a
+partial last group, rows with and without an equator; few items and nearly
+empty groups (which the any-length kernels take) at the edges.  Oracle on
+three fields; bounds as for every parity test."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O
+from paper_1711_11296_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-12, "fp32": 1e-6}
+LENGTHS = [288, 320, 384, 400, 432, 480, 512, 576, 640, 720, 768, 800, 864, 960, 1024, 1152, 1200, 1280, 1296, 1440,
+           1536, 1600, 1728, 1920, 2048, 2160, 2304, 2400, 2560, 2880, 3072, 3600, 3840, 4096]
+
+
+def _rel(x, ref):
+    return np.linalg.norm(x - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("form", ["fp32", "fp64"])
+@pytest.mark.parametrize("I", LENGTHS)
+def test_every_length(I, form):
+    from paper_1711_11296_amd import Plan
+    dt = torch.float64 if form == "fp64" else torch.float32
+    k = LENGTHS.index(I)
+    N = [(I - 1) // 2, 37, I // 3][k % 3]
+    J = 21 + k % 2
+    # at least 256 items of the kernel's group size (1 to 8 fields)
+    F = 8 * (256 // ((J + 1) // 2) + 1) + 3
+    if N > 300:
+        J, F = 9 + k % 2, 8 * 52 + 5
+    if N > 900:
+        F = 131 if form == "fp64" else 8 * 52 + 1
+    p = Plan(N, J, I, F, grid="fejer2", form=form, otf=True)
+    pick = [0, F // 2, F - 1]
+    g = torch.randn((F, J, I), dtype=dt, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(I))
+    nc = (N + 1) * (N + 2) // 2
+    a = torch.randn((F, nc, 2), dtype=dt, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(I + 1))
+    a[:, :N + 1, 1] = 0
+    s, x = p.forward(g), p.inverse(a)
+    torch.cuda.synchronize()
+    gh, ah = g[pick].double().cpu().numpy(), a[pick].double().cpu().numpy()
+    assert _rel(s[pick].double().cpu().numpy(), O.forward(gh, N, "fejer2")) < TOL[form]
+    assert _rel(x[pick].double().cpu().numpy(), O.inverse(ah, N, J, I, "fejer2")) < TOL[form]
+    p.close()
+
+
+@pytest.mark.parametrize("form", ["fp32", "fp64"])
+@pytest.mark.parametrize("I,N,J,F", [(480, 159, 601, 3), (960, 200, 520, 2), (1920, 479, 519, 3), (640, 213, 64, 8),
+                                     (1024, 90, 512, 1), (2880, 60, 514, 5)])
+def test_few_fields_and_items(I, N, J, F, form):
+    from paper_1711_11296_amd import Plan
+    dt = torch.float64 if form == "fp64" else torch.float32
+    p = Plan(N, J, I, F, grid="cc_poles", form=form, reduced=True)
+    g = torch.from_numpy(inputs.random_grid(1, J, I, seed=I)).to("cuda:0", dt).expand(F, J, I).contiguous()
+    g *= torch.arange(1, F + 1, device="cuda:0", dtype=dt)[:, None, None]
+    a = torch.from_numpy(inputs.random_spectra(N, F, seed=I, profile="white")).to("cuda:0", dt)
+    s, x = p.forward(g), p.inverse(a)
+    torch.cuda.synchronize()
+    pick = [0, F - 1]
+    assert _rel(s[pick].double().cpu().numpy(), O.forward(g[pick].double().cpu().numpy(), N, "cc_poles")) < TOL[form]
+    assert _rel(x[pick].double().cpu().numpy(), O.inverse(a[pick].double().cpu().numpy(), N, J, I, "cc_poles")) < TOL[form]
+    p.close()
