@@ -17,10 +17,12 @@
 // partner at I-m, and one inverse FFT yields both rows:
 //   x(lambda_i) = Re X^0 + 2 sum_{m>=1} Re(X^m e^{i m lambda_i}).
 //
-// This file holds the kernels of the lengths with a compile-time three-pass
-// plan and the choice of kernel; sht_any.h those of every other length.
+// Three families of kernels: sht_group.h (lengths 16 R2 R3 known at compile
+// time), sht_any.h (any length), and here the ones that hold their runs in
+// registers, which lengths past 2048 use in one direction (launch_held),
+// with the choice of kernel and the multi-level launches.
 //
-// Work decomposition: one workgroup per (mirror row pair, block of FB
+// Work decomposition of the kernels here: one workgroup per (mirror row pair, block of FB
 // fields).  The FB fields go through the LDS buffer one after the other and
 // the wavenumbers m <= N of all FB fields are kept in registers, so that each
 // workspace access is a contiguous run of 2*FB values (64 bytes) per (m,
@@ -106,55 +108,37 @@ __device__ __forceinline__ void quad_transpose(int (&x)[4][4]) {
 // are skipped.  All lanes of the quad must call it.  base is uniform and the
 // 64 lanes of a wave hold consecutive wavenumbers: each address is a
 // uniform 64-bit base at the wave's first wavenumber plus a 32-bit per-lane
-// byte offset of fewer than 64 regions (zonal_offsets_fit).  A run of 2 FB
-// values is 64 or 128 bytes; a 128-byte run goes as two 64-byte halves.
+// byte offset of fewer than 64 regions (zonal_offsets_fit).
 template <typename T, int FB>
 __device__ __forceinline__ void store_runs_quad(T* base, long long region, int m, int N,
                                                 const cx<T> (&v)[FB]) {
-  constexpr int HALVES = 2 * FB * (int)sizeof(T) / 64;
-  static_assert(HALVES * 64 == 2 * FB * (int)sizeof(T) && HALVES <= 2, "64- or 128-byte runs");
+  static_assert(2 * FB * (int)sizeof(T) == 64, "64-byte runs");
   const int lane = threadIdx.x & 63, j = lane & 3;
   const long long step64 = region * (long long)sizeof(T);
   const int mw = __builtin_amdgcn_readfirstlane(m - lane);  // the wave's first wavenumber
   char* b = reinterpret_cast<char*>(base) + (long long)mw * step64;
   const unsigned step = (unsigned)step64;
+  int x[4][4];
+  __builtin_memcpy(x, v, 64);
+  quad_transpose(x);
+  unsigned off = (unsigned)(lane - j) * step + 16u * (unsigned)j;
 #pragma unroll
-  for (int hf = 0; hf < HALVES; ++hf) {
-    int x[4][4];
-    __builtin_memcpy(x, reinterpret_cast<const char*>(v) + 64 * hf, 64);
-    quad_transpose(x);
-    unsigned off = (unsigned)(lane - j) * step + 16u * (unsigned)j + 64u * (unsigned)hf;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int mr = m - j + r;
-      if (mr <= N) {
-        typedef int i32x4 __attribute__((ext_vector_type(4)));
-        *reinterpret_cast<i32x4*>(b + off) = i32x4{x[r][0], x[r][1], x[r][2], x[r][3]};
-      }
-      off += step;
+  for (int r = 0; r < 4; ++r) {
+    const int mr = m - j + r;
+    if (mr <= N) {
+      typedef int i32x4 __attribute__((ext_vector_type(4)));
+      *reinterpret_cast<i32x4*>(b + off) = i32x4{x[r][0], x[r][1], x[r][2], x[r][3]};
     }
+    off += step;
   }
 }
 
 // ---------------------------------------------------------------------------
 // Fixed-length transforms: I = 16 R2 R3 in three passes with compile-time
-// radices, twiddle strides and index arithmetic.
-//
-// The FC sequences of a round lie in LDS with a field stride of IP = 17 I/16
-// complex values.  The output of the radix-16 first pass (Ns = 1, element
-// 16 j + t of the natural order) is stored at the padded position 17 j + t,
-// so that the 64 lanes of a wave, which own consecutive j, hit distinct
-// banks; the second pass reads that padded order (its inputs j + t I/R2 sit
-// at j + j/16 + t (17/16)(I/R2), since I/R2 is a multiple of 16) and writes
-// the natural order; the third pass reads and writes the natural order.
-// The twiddles of passes two and three are staged in LDS as [t-1][k]
-// (k = butterfly position within its Ns-block), so that consecutive lanes
-// read consecutive entries.
-//
-// Analysis loads the grid rows straight into the registers of the first
-// pass (thread of butterfly j loads elements j + t I/16 of both rows, which
-// is coalesced across the lanes); synthesis stores the last pass straight to
-// the grid rows (element j + t Ns3 of each of the two rows).
+// radices, twiddle strides and index arithmetic (Plan3; the passes are those
+// of sht_group.h with a field stride of IP).  Analysis loads the grid rows
+// straight into the registers of the first pass; synthesis stores the last
+// pass straight to the grid rows.
 // ---------------------------------------------------------------------------
 template <typename T, class P, int NT, int FC>
 struct Fft3 {
@@ -684,9 +668,11 @@ template <typename T>
 struct ZLevels {
   static constexpr bool dbl = sizeof(T) == 8;
   static constexpr int NT = 512;
-  using C1600 = ZGrp<Plan3<1600, 10, 10>, 4>;
-  using C800 = ZGrp<Plan3<800, 10, 5>, dbl ? 4 : 8>;
-  using C400 = ZGrp<Plan3<400, 5, 5>, dbl ? 4 : 8>;
+  template <int I, int FC>
+  using Z = ZGrp<Plan3<I, grp_r2(I, NT, FC), I / 16 / grp_r2(I, NT, FC)>, FC>;
+  using C1600 = Z<1600, 4>;
+  using C800 = Z<800, dbl ? 4 : 8>;
+  using C400 = Z<400, dbl ? 4 : 8>;
   template <bool VEC>
   using CRt = ZRt<VEC, 1024>;
   template <int FB, bool ANA, bool VEC>

@@ -25,14 +25,46 @@
 
 namespace sht {
 
-// Every length 16 R2 R3 from 288 on with radices up to 16 (X(I, R2, R3)).
-#define SHT_GROUP_LENGTHS(X)                                                                                     \
-  X(288, 6, 3) X(320, 5, 4) X(384, 6, 4) X(400, 5, 5) X(432, 9, 3) X(480, 6, 5) X(512, 8, 4) X(576, 6, 6)        \
-  X(640, 8, 5) X(720, 9, 5) X(768, 8, 6) X(800, 10, 5) X(864, 9, 6) X(960, 10, 6) X(1024, 8, 8) X(1152, 9, 8)    \
-  X(1200, 15, 5) X(1280, 10, 8) X(1296, 9, 9) X(1440, 10, 9) X(1536, 12, 8) X(1600, 10, 10) X(1728, 12, 9)       \
-  X(1920, 12, 10) X(2048, 16, 8) X(2160, 15, 9) X(2304, 12, 12) X(2400, 15, 10) X(2560, 16, 10) X(2880, 15, 12)  \
-  X(3072, 16, 12) X(3600, 15, 15) X(3840, 16, 15) X(4096, 16, 16)
+// Every length 16 R2 R3 from 288 on with radices up to 16.
+#define SHT_GROUP_LENGTHS(X)                                                                                      \
+  X(288) X(320) X(384) X(400) X(432) X(480) X(512) X(576) X(640) X(720) X(768) X(800) X(864) X(960) X(1024)       \
+  X(1152) X(1200) X(1280) X(1296) X(1440) X(1536) X(1600) X(1728) X(1920) X(2048) X(2160) X(2304) X(2400) X(2560) \
+  X(2880) X(3072) X(3600) X(3840) X(4096)
 
+// Radices of the second and third pass for NT threads and FC sequences: a
+// thread holds ceil(FC (I / R) / NT) butterflies of R values in a pass; the
+// pair of least sum (a second, nearly empty round of butterflies costs as
+// much as a full one, and its registers), then the larger second radix.
+constexpr bool grp_radix(int r) {
+  return r == 2 || r == 3 || r == 4 || r == 5 || r == 6 || r == 8 || r == 9 || r == 10 || r == 12 || r == 15 || r == 16;
+}
+constexpr int grp_held(int I, int R, int NT, int FC) { return (FC * (I / R) + NT - 1) / NT * R; }
+constexpr int grp_r2(int I, int NT, int FC) {
+  int best = 0, cost = 1 << 30;
+  for (int r = 16; r >= 2; --r) {
+    const int q = I / 16;
+    if (q % r || !grp_radix(r) || !grp_radix(q / r)) continue;
+    const int c = grp_held(I, r, NT, FC) + grp_held(I, q / r, NT, FC);
+    if (c < cost) {
+      cost = c;
+      best = r;
+    }
+  }
+  return best;
+}
+constexpr int grp_most_held(int I, int NT, int FC) {
+  const int r2 = grp_r2(I, NT, FC), a = grp_held(I, r2, NT, FC), b = grp_held(I, I / 16 / r2, NT, FC);
+  return a > b ? a : b;
+}
+
+// Three passes of radices 16, R2, R3 over sequences that lie side by side in
+// LDS.  The first pass stores element 16 j + t at the padded position
+// 17 j + t, so that the lanes of a wave, which own consecutive j, hit
+// distinct banks; the second reads that order (its inputs j + t I/R2 sit at
+// j + j/16 + t (17/16)(I/R2), I/R2 being a multiple of 16) and writes the
+// natural order; the third reads and writes the natural order.  Twiddles of
+// passes two and three are staged in LDS as [t-1][k] (k = butterfly position
+// within its Ns-block).
 template <int I_, int R2_, int R3_>
 struct Plan3 {
   static constexpr int I = I_, R1 = 16, R2 = R2_, R3 = R3_;
@@ -47,13 +79,17 @@ struct Plan3 {
 };
 
 // field stride in LDS
-template <class P> constexpr int grp_stride() { return ((P::IP + 15) & ~15) + 2; }
+template <class P>
+constexpr int grp_stride() {
+  return ((P::IP + 15) & ~15) + 2;
+}
 
 template <typename T, class P, int NT, int FC, bool PF>
 struct Grp {
   static constexpr int I = P::I, GP = grp_stride<P>();
   static constexpr int VW = sizeof(T) == 4 && FC >= 2 ? 2 : 1, LV = FC / VW;
-  static constexpr int S1 = (FC * P::nb1 + NT - 1) / NT, S2 = (FC * P::nb2 + NT - 1) / NT, S3 = (FC * P::nb3 + NT - 1) / NT;
+  static constexpr int S1 = (FC * P::nb1 + NT - 1) / NT, S2 = (FC * P::nb2 + NT - 1) / NT,
+                       S3 = (FC * P::nb3 + NT - 1) / NT;
   static constexpr int UM = ((I + 1) / 2 * LV + NT - 1) / NT;
   static constexpr size_t lds() { return (size_t)(FC * GP + P::ntw) * sizeof(cx<T>); }
 
@@ -196,7 +232,8 @@ struct Grp {
       if constexpr (!PF) load_rows(item);
       pass1_store(v1, buf);
       __syncthreads();
-      if constexpr (PF) { if (next < end) load_rows(next); }
+      if constexpr (PF)
+        if (next < end) load_rows(next);
       pass2(buf, twl);
       {
         cx<T> v3[S3][P::R3];
@@ -231,7 +268,7 @@ struct Grp {
           const cx<T>* z = buf + (f0 + q) * GP;
           const cx<T> Pm = z[m];
           cx<T> Q = z[m == 0 ? 0 : I - m];
-          Q.y = -Q.y;
+          Q.y = -Q.y;  // conj Z^{I-m}
           const T h = (T)0.5;
           const cx<T> Xn = {h * (Pm.x + Q.x), h * (Pm.y + Q.y)};
           const cx<T> Xs = {h * (Pm.y - Q.y), -h * (Pm.x - Q.x)};
@@ -286,6 +323,8 @@ struct Grp {
         const int mw = __builtin_amdgcn_readfirstlane(m);
         const char* wb = reinterpret_cast<const char*>(w + mw * plane2);
         const unsigned lo = (unsigned)(m - mw) * step + (unsigned)(2 * f0 * sizeof(T));
+        // rows below the first 128-latitude tile the Legendre synthesis
+        // computes for this m (reduced transform) are zero
         if (m <= N && fg * FC + f0 < F && (!a.jstart || jp >= (a.jstart[L.m_base + m] & ~127))) {
           pS[u] = *reinterpret_cast<const TW*>(wb + lo);
           pA[u] = *reinterpret_cast<const TW*>(wb + odd + lo);
@@ -303,7 +342,7 @@ struct Grp {
       const int next = item + (int)gridDim.x;
       if constexpr (!PF) load_ws(item);
 #pragma unroll
-      for (int f = 0; f < FC; ++f)
+      for (int f = 0; f < FC; ++f)  // the bins no unit fills: N < i < I - N
         for (int i = N + 1 + (int)threadIdx.x; i < I - N; i += NT) buf[f * GP + i] = cx<T>{(T)0, (T)0};
 #pragma unroll
       for (int u = 0; u < UM; ++u) {
@@ -320,6 +359,7 @@ struct Grp {
               Xn.y = (T)0;
               Xs.y = (T)0;
             }
+            // conj(Z), as in sht_fft.hip
             cx<T>* z = buf + (f0 + q) * GP;
             z[m] = cx<T>{Xn.x - Xs.y, -(Xn.y + Xs.x)};
             if (m > 0) z[I - m] = cx<T>{Xn.x + Xs.y, Xn.y - Xs.x};
@@ -327,7 +367,8 @@ struct Grp {
         }
       }
       __syncthreads();
-      if constexpr (PF) { if (next < end) load_ws(next); }
+      if constexpr (PF)
+        if (next < end) load_ws(next);
       pass1_lds(buf);
       pass2(buf, twl);
       cx<T> v3[S3][P::R3];
@@ -371,23 +412,19 @@ struct Grp {
 // and a pass at most 20 per buffer; FP32 synthesis mostly 4.  From 1600 on
 // one workgroup fills a compute unit's LDS: it has 1024 threads and fetches
 // ahead.
-template <typename T, class P, bool ANA>
+template <typename T, int I, bool ANA>
 struct GroupShape {
   static constexpr bool dbl = sizeof(T) == 8;
-  static constexpr int I = P::I;
-  // values a pass holds per thread
-  static constexpr int held(int nt, int fc) {
-    const int s2 = (fc * P::nb2 + nt - 1) / nt * P::R2, s3 = (fc * P::nb3 + nt - 1) / nt * P::R3;
-    return s2 > s3 ? s2 : s3;
-  }
-  static constexpr bool all8 = !dbl && (ANA ? I <= 2048 && held(I <= 512 ? 256 : I <= 1024 ? 512 : 1024, 8) <= 20
-                                            : I > 512 && I <= 1024 && held(512, 8) <= 16);
+  static constexpr bool all8 =
+      !dbl && (ANA ? I <= 2048 && grp_most_held(I, I <= 512 ? 256 : I <= 1024 ? 512 : 1024, 8) <= 20
+                   : I > 512 && I <= 1024 && grp_most_held(I, 512, 8) <= 16);
   static constexpr int NT = dbl ? (I <= 1024 ? 256 : 512)
                             : all8 ? (I <= 512 ? 256 : I <= 1024 ? 512 : 1024)
                                    : (I <= 512 ? 256 : I <= 1600 ? 512 : 1024);
   static constexpr int FC = dbl ? (I <= 1920 ? 4 : I <= 3072 ? 2 : 1) : all8 ? 8 : I <= 3840 ? 4 : 2;
   static constexpr bool PF = dbl ? (I > 1024 && (ANA || I <= 1280 || I > 1920)) : !all8 && I > 1600;
   static constexpr int WPE = dbl ? 2 : 4;
+  using P = Plan3<I, grp_r2(I, NT, FC), I / 16 / grp_r2(I, NT, FC)>;
 };
 
 }  // namespace sht

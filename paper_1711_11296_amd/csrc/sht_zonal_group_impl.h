@@ -11,21 +11,21 @@ namespace sht {
 
 namespace {
 
-template <typename T, class P, bool ANA>
-__global__ __launch_bounds__((GroupShape<T, P, ANA>::NT))
-    __attribute__((amdgpu_waves_per_eu(GroupShape<T, P, ANA>::WPE))) void k_zonal_group(const FftArgs a) {
-  using S = GroupShape<T, P, ANA>;
+template <typename T, int I, bool ANA>
+__global__ __launch_bounds__((GroupShape<T, I, ANA>::NT))
+    __attribute__((amdgpu_waves_per_eu(GroupShape<T, I, ANA>::WPE))) void k_zonal_group(const FftArgs a) {
+  using S = GroupShape<T, I, ANA>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if constexpr (ANA)
-    Grp<T, P, S::NT, S::FC, S::PF>::analysis(a, 0, blockIdx.x, smem_raw);
+    Grp<T, typename S::P, S::NT, S::FC, S::PF>::analysis(a, 0, blockIdx.x, smem_raw);
   else
-    Grp<T, P, S::NT, S::FC, S::PF>::synthesis(a, 0, blockIdx.x, smem_raw);
+    Grp<T, typename S::P, S::NT, S::FC, S::PF>::synthesis(a, 0, blockIdx.x, smem_raw);
 }
 
-template <typename T, class P, bool ANA>
+template <typename T, int I, bool ANA>
 int go(const FftArgs& a0, int ncu, hipStream_t st) {
-  using S = GroupShape<T, P, ANA>;
-  using G = Grp<T, P, S::NT, S::FC, S::PF>;
+  using S = GroupShape<T, I, ANA>;
+  using G = Grp<T, typename S::P, S::NT, S::FC, S::PF>;
   constexpr size_t lds = G::lds(), most = 160 * 1024;
   static_assert(lds <= most, "one workgroup's LDS");
   FftArgs a = a0;
@@ -39,14 +39,14 @@ int go(const FftArgs& a0, int ncu, hipStream_t st) {
   if ((double)S::FC * L.J * L.I * sizeof(T) >= 4294967296.0 || items > 0x7fffffff) return -1;
   a.nitems = (int)items;
   if constexpr (lds > 65536) {
-    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_zonal_group<T, P, ANA>),
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_zonal_group<T, I, ANA>),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     (void)e;
   }
   constexpr int by_lds = (int)(most / lds), by_waves = S::WPE * 256 / S::NT;
   constexpr int per_cu = by_lds < by_waves ? by_lds : by_waves < 1 ? 1 : by_waves;
   const int nwg = ncu * per_cu < a.nitems ? ncu * per_cu : a.nitems;
-  hipLaunchKernelGGL((k_zonal_group<T, P, ANA>), dim3(nwg), dim3(S::NT), lds, st, a);
+  hipLaunchKernelGGL((k_zonal_group<T, I, ANA>), dim3(nwg), dim3(S::NT), lds, st, a);
   return (int)hipGetLastError();
 }
 
@@ -57,8 +57,8 @@ int go(const FftArgs& a0, int ncu, hipStream_t st) {
 int SHT_GROUP_LAUNCH(const FftArgs& a, int ncu, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   switch (a.lev[0].I) {
-#define SHT_GROUP_CASE(i, r2, r3) \
-  case i: return go<SHT_GROUP_T, Plan3<i, r2, r3>, SHT_GROUP_ANA>(a, ncu, st);
+#define SHT_GROUP_CASE(i) \
+  case i: return go<SHT_GROUP_T, i, SHT_GROUP_ANA>(a, ncu, st);
     SHT_GROUP_LENGTHS(SHT_GROUP_CASE)
 #undef SHT_GROUP_CASE
     default: return -1;
