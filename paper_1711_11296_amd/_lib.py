@@ -102,6 +102,16 @@ def load(require_torch=True):
     return lib
 
 
+def raw_stream(device):
+    """The hipStream_t of torch's current stream on a CUDA (HIP) device, as an
+    integer, without building a torch.cuda.Stream object (1.9 us a call)."""
+    import torch
+    index = device.index
+    if index is None:
+        index = torch.cuda.current_device()
+    return torch._C._cuda_getCurrentRawStream(index)
+
+
 def check(rc):
     if rc != SHT_OK:
         raise SHTError(rc, _lib.sht_last_error().decode())

@@ -14,7 +14,7 @@ import numpy as np
 
 from . import inputs
 from .plan import Plan
-from .transfer import grid_product, spec_retruncate
+from .transfer import product_into, spec_retruncate
 
 
 class NonlinearTerms:
@@ -39,12 +39,16 @@ class NonlinearTerms:
         if (Nt + 1) * (Nt + 2) // 2 != nc or Nt > self.N:
             raise ValueError("spectra must be triangular with truncation <= %d" % self.N)
         p = self.plan
-        g = p.inverse(spec_retruncate(torch.cat([U, V, W]).to(p.dtype), Nt, self.N))
-        q = grid_product(g[0], g[1])
-        c = grid_product(q, g[2])
-        # the plan holds three fields; the third analysed slot is unused
-        x = p.forward(torch.stack([q, c, torch.zeros_like(q)]))
-        return spec_retruncate(x[:2].contiguous(), self.N, Nt)
+        s = torch.cat([U, V, W]).to(p.dtype)
+        g = p.inverse(s if Nt == self.N else spec_retruncate(s, Nt, self.N))
+        # the products go straight into the analysis' input (stacking them
+        # copied three grids); the third analysed slot is unused
+        t = torch.empty_like(g)
+        product_into(g[0], g[1], t[0])
+        product_into(t[0], g[2], t[1])
+        t[2].zero_()
+        x = p.forward(t)[:2]
+        return x if Nt == self.N else spec_retruncate(x, self.N, Nt)
 
     def close(self):
         self.plan.close()

@@ -145,10 +145,11 @@ struct AnyItem {
   bool eq;
 };
 
-__device__ __forceinline__ AnyItem any_item(const FftArgs& a, int slot) {
+template <int NL>
+__device__ __forceinline__ AnyItem any_item(const FftArgsN<NL>& a, int slot) {
   AnyItem it;
   it.l = level_of(a, slot);
-  const LevelDesc& L = a.lev[it.l];
+  const LevelDesc& L = a.lev[NL == 1 ? 0 : it.l];
   const int local = xcd_map(slot - L.fft_item0, level_end(a, it.l) - L.fft_item0);
   it.jp = local / L.nfb;
   it.fg = local - it.jp * L.nfb;
@@ -179,8 +180,8 @@ __device__ __forceinline__ T any_get(const typename AnyVec<T, V>::type& v, int e
 // VW: fields per workspace piece (2 in FP32 with FC >= 2: 16 bytes).
 // The slots item, item + G, ... below `end` (any levels); returns the first
 // slot past them.  Every thread of the workgroup calls it alike.
-template <typename T, int NT, bool VEC, int VW>
-__device__ __forceinline__ int any_analysis_run(const FftArgs& a, int item, int end, unsigned char* smem_raw) {
+template <typename T, int NT, bool VEC, int VW, int NL>
+__device__ __forceinline__ int any_analysis_run(const FftArgsN<NL>& a, int item, int end, unsigned char* smem_raw) {
   constexpr int E = AnyCap<T>::E, V = VEC ? 16 / (int)sizeof(T) : 1, LU = E / V;
   typedef typename AnyVec<T, V>::type TV;
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
@@ -193,7 +194,7 @@ __device__ __forceinline__ int any_analysis_run(const FftArgs& a, int item, int 
   TV pn[LU], ps[LU];
   auto load_rows = [&](int slot) __attribute__((always_inline)) {
     const AnyItem it = any_item(a, slot);
-    const LevelDesc& L = a.lev[it.l];
+    const LevelDesc& L = a.lev[NL == 1 ? 0 : it.l];
     const int nv = L.I / V, F = L.F - it.fg * FC;  // fields of this group that exist
     const unsigned mv = L.ivm;
     const T* rn = grid0 + L.grid_off + ((long long)it.fg * FC * L.J + it.jp) * L.I;
@@ -217,7 +218,7 @@ __device__ __forceinline__ int any_analysis_run(const FftArgs& a, int item, int 
   int lcur = -1;
   for (; item < end; item += gridDim.x) {
     const AnyItem it = any_item(a, item);
-    const LevelDesc& L = a.lev[it.l];
+    const LevelDesc& L = a.lev[NL == 1 ? 0 : it.l];
     const int I = L.I, N = L.N, IP = any_stride(L);
     if (it.l != lcur) {
       any_twiddles<T, NT>(twl, L);  // (the barrier at the end of an item precedes it)
@@ -291,8 +292,8 @@ __device__ __forceinline__ int any_analysis_run(const FftArgs& a, int item, int 
 }
 
 // synthesis: workspace S/A -> grid [F][J][I]
-template <typename T, int NT, bool VEC, int VW>
-__device__ __forceinline__ int any_synthesis_run(const FftArgs& a, int item, int end, unsigned char* smem_raw) {
+template <typename T, int NT, bool VEC, int VW, int NL>
+__device__ __forceinline__ int any_synthesis_run(const FftArgsN<NL>& a, int item, int end, unsigned char* smem_raw) {
   constexpr int E = AnyCap<T>::E, V = VEC ? 16 / (int)sizeof(T) : 1, LU = E / V, UM = E / (2 * VW);
   typedef typename AnyVec<T, V>::type TV;
   typedef T TW __attribute__((ext_vector_type(2 * VW)));
@@ -307,7 +308,7 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgs& a, int item, int
   TW pS[UM], pA[UM];
   auto load_ws = [&](int slot) __attribute__((always_inline)) {
     const AnyItem it = any_item(a, slot);
-    const LevelDesc& L = a.lev[it.l];
+    const LevelDesc& L = a.lev[NL == 1 ? 0 : it.l];
     const int jb = it.jp / SHT_K_PAD;
     const T* ws = ws0 + L.ws_off + jb * L.wjb + (long long)(it.jp % SHT_K_PAD) * L.Cp + 2 * it.fg * FC;
     const long long region = L.wblk, odd = ws_odd(L.Jh, L.Cp, L.wblk, jb);
@@ -332,7 +333,7 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgs& a, int item, int
   int lcur = -1;
   for (; item < end; item += gridDim.x) {
     const AnyItem it = any_item(a, item);
-    const LevelDesc& L = a.lev[it.l];
+    const LevelDesc& L = a.lev[NL == 1 ? 0 : it.l];
     const int I = L.I, N = L.N, IP = any_stride(L);
     if (it.l != lcur) {
       any_twiddles<T, NT>(twl, L);

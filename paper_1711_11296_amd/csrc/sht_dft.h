@@ -236,14 +236,18 @@ struct Vec16<double> {
   typedef double type __attribute__((ext_vector_type(2)));
 };
 
-__device__ __forceinline__ int level_of(const FftArgs& a, int item) {
+template <int NL>
+__device__ __forceinline__ int level_of(const FftArgsN<NL>& a, int item) {
+  if (NL == 1) return 0;
   int l = 0;
   while (l + 1 < a.nlev && item >= a.lev[l + 1].fft_item0) ++l;
   return l;
 }
 
 // One past the last work item (slot) of level l.
-__device__ __forceinline__ int level_end(const FftArgs& a, int l) {
+template <int NL>
+__device__ __forceinline__ int level_end(const FftArgsN<NL>& a, int l) {
+  if (NL == 1) return a.nitems;
   return l + 1 < a.nlev ? a.lev[l + 1].fft_item0 : a.nitems;
 }
 
@@ -262,8 +266,8 @@ __device__ __forceinline__ int xcd_map(int i, int n) {
   return x * R + (x < rem ? x : rem) + k;
 }
 
-template <typename T>
-__device__ __forceinline__ T row_scale(const FftArgs& a, const LevelDesc& L, int jp) {
+template <typename T, int NL>
+__device__ __forceinline__ T row_scale(const FftArgsN<NL>& a, const LevelDesc& L, int jp) {
   T r = (T)1;
   if (a.use_w) r = (T)L.wrow[jp];
   if (a.use_inv_I) r = (T)((double)r / (double)L.I);

@@ -250,23 +250,21 @@ struct Fft3 {
   }
 };
 
-// The slots item, item + G, ... of level l (item is one of them); returns
-// the first slot past the level.  Every thread of the workgroup calls it
-// alike.
+// The slots item, item + G, ... of the level.
 template <typename T, class P, int NT, int FB, int FC, int MS>
-__device__ __forceinline__ int zonal_analysis_run_p3(const FftArgs& a, int l, int item, unsigned char* smem_raw) {
+__device__ __forceinline__ void zonal_analysis_run_p3(const FftArgs1& a, int item, unsigned char* smem_raw) {
   using F3 = Fft3<T, P, NT, FC>;
   constexpr int NRD = FB / FC, I = P::I;
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   cx<T>* twl = buf + FC * P::IP;
-  const LevelDesc& L = a.lev[l];
-  const int s0 = L.fft_item0, end = level_end(a, l), n = end - s0;
+  const LevelDesc& L = a.lev[0];
+  const int s0 = 0, end = a.nitems, n = end;
   const T* grid = static_cast<const T*>(a.src) + L.grid_off;
   T* ws = static_cast<T*>(a.dst) + L.ws_off;
   const T msc = (T)a.mscale;
   const int N = L.N, J = L.J;
 
-  if (item >= end) return item;
+  if (item >= end) return;
   F3::stage_twiddles(twl, static_cast<const cx<T>*>(L.tw));
 
   cx<T> v1[F3::S1][16];
@@ -370,23 +368,22 @@ __device__ __forceinline__ int zonal_analysis_run_p3(const FftArgs& a, int l, in
       store_runs_quad<T, FB>(wrow + 2 * FB, plane, m, N, stA[s]);
     }
   }
-  return item;
 }
 
 template <typename T, class P, int NT, int FB, int FC, int MS>
-__global__ __launch_bounds__(NT) void k_zonal_analysis_p3(const FftArgs a) {
+__global__ __launch_bounds__(NT) void k_zonal_analysis_p3(const FftArgs1 a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  zonal_analysis_run_p3<T, P, NT, FB, FC, MS>(a, 0, blockIdx.x, smem_raw);
+  zonal_analysis_run_p3<T, P, NT, FB, FC, MS>(a, blockIdx.x, smem_raw);
 }
 
 template <typename T, class P, int NT, int FB, int FC, int MS>
-__device__ __forceinline__ int zonal_synthesis_run_p3(const FftArgs& a, int l, int item, unsigned char* smem_raw) {
+__device__ __forceinline__ void zonal_synthesis_run_p3(const FftArgs1& a, int item, unsigned char* smem_raw) {
   using F3 = Fft3<T, P, NT, FC>;
   constexpr int NRD = FB / FC, I = P::I;
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   cx<T>* twl = buf + FC * P::IP;
-  const LevelDesc& L = a.lev[l];
-  const int s0 = L.fft_item0, end = level_end(a, l), n = end - s0;
+  const LevelDesc& L = a.lev[0];
+  const int s0 = 0, end = a.nitems, n = end;
   const T* ws = static_cast<const T*>(a.src) + L.ws_off;
   T* grid = static_cast<T*>(a.dst) + L.grid_off;
   const T msc = (T)a.mscale;
@@ -423,7 +420,7 @@ __device__ __forceinline__ int zonal_synthesis_run_p3(const FftArgs& a, int l, i
     }
   };
 
-  if (item >= end) return item;
+  if (item >= end) return;
   F3::stage_twiddles(twl, static_cast<const cx<T>*>(L.tw));
   load_ws(item);
   for (; item < end; item += gridDim.x) {
@@ -486,13 +483,12 @@ __device__ __forceinline__ int zonal_synthesis_run_p3(const FftArgs& a, int l, i
       __syncthreads();  // the next round refills the buffer
     }
   }
-  return item;
 }
 
 template <typename T, class P, int NT, int FB, int FC, int MS>
-__global__ __launch_bounds__(NT) void k_zonal_synthesis_p3(const FftArgs a) {
+__global__ __launch_bounds__(NT) void k_zonal_synthesis_p3(const FftArgs1 a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  zonal_synthesis_run_p3<T, P, NT, FB, FC, MS>(a, 0, blockIdx.x, smem_raw);
+  zonal_synthesis_run_p3<T, P, NT, FB, FC, MS>(a, blockIdx.x, smem_raw);
 }
 
 
@@ -575,7 +571,7 @@ static void lds_optin(size_t bytes) {
 static int g_num_cu = 0;
 
 template <typename T, class P, int NT, int FB, int FC, int MS, bool ANA>
-static hipError_t launch_p3_ms(const FftArgs& a, hipStream_t st) {
+static hipError_t launch_p3_ms(const FftArgs1& a, hipStream_t st) {
   const size_t lds = (size_t)(FC * P::IP + P::ntw) * sizeof(cx<T>);
   int per_cu = (int)(kMaxLds / lds);
   const int by_waves = 2048 / NT;
@@ -596,7 +592,7 @@ static hipError_t launch_p3_ms(const FftArgs& a, hipStream_t st) {
 
 // Two fields per round (four spill registers and cost ~5 %) on 512 threads.
 template <typename T, int FB, bool ANA, class P>
-static hipError_t launch_p3(const FftArgs& a, int maxN, hipStream_t st) {
+static hipError_t launch_p3(const FftArgs1& a, int maxN, hipStream_t st) {
   constexpr int NT = 512, FC = 2;
   constexpr int MSMAX = ((P::I + 1) / 2 + NT - 1) / NT;  // N + 1 <= (I + 1) / 2
   static_assert(MSMAX == 3, "wavenumbers per thread");
@@ -613,7 +609,7 @@ static hipError_t launch_p3(const FftArgs& a, int maxN, hipStream_t st) {
 // per item, which is all the LDS holds there, the group kernels' analysis
 // stores 32-byte pieces.  Up to three wavenumbers per thread (I <= 3072).
 template <typename T, int FB, bool ANA>
-static bool launch_held(const FftArgs& a, int maxN, hipStream_t st, hipError_t* err) {
+static bool launch_held(const FftArgs1& a, int maxN, hipStream_t st, hipError_t* err) {
   if constexpr ((sizeof(T) == 4) != ANA) {
     return false;
   } else {
@@ -636,11 +632,12 @@ static bool launch_fixed(bool analysis, const FftArgs& a, int maxN, hipStream_t 
   // the fixed-length kernels address the workspace with 32-bit offsets
   // from a per-wave base
   if (!zonal_offsets_fit(a.lev[0].wblk, sizeof(T))) return false;
-  if (analysis ? launch_held<T, FB, true>(a, maxN, st, err) : launch_held<T, FB, false>(a, maxN, st, err)) return true;
-  const int e = sizeof(T) == 8 ? (analysis ? launch_zonal_group_analysis_f64(a, g_num_cu, st)
-                                           : launch_zonal_group_synthesis_f64(a, g_num_cu, st))
-                               : (analysis ? launch_zonal_group_analysis_f32(a, g_num_cu, st)
-                                           : launch_zonal_group_synthesis_f32(a, g_num_cu, st));
+  const FftArgs1 o = one_level(a);
+  if (analysis ? launch_held<T, FB, true>(o, maxN, st, err) : launch_held<T, FB, false>(o, maxN, st, err)) return true;
+  const int e = sizeof(T) == 8 ? (analysis ? launch_zonal_group_analysis_f64(o, g_num_cu, st)
+                                           : launch_zonal_group_synthesis_f64(o, g_num_cu, st))
+                               : (analysis ? launch_zonal_group_analysis_f32(o, g_num_cu, st)
+                                           : launch_zonal_group_synthesis_f32(o, g_num_cu, st));
   if (e < 0) return false;
   *err = (hipError_t)e;
   return true;

@@ -184,7 +184,8 @@ struct Grp {
     }
   }
 
-  static __device__ __forceinline__ int analysis(const FftArgs& a, int l, int item, unsigned char* smem_raw) {
+  template <int NL>
+  static __device__ __forceinline__ int analysis(const FftArgsN<NL>& a, int l, int item, unsigned char* smem_raw) {
     cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
     cx<T>* twl = buf + FC * GP;
     const LevelDesc& L = a.lev[l];
@@ -295,7 +296,8 @@ struct Grp {
     return item;
   }
 
-  static __device__ __forceinline__ int synthesis(const FftArgs& a, int l, int item, unsigned char* smem_raw) {
+  template <int NL>
+  static __device__ __forceinline__ int synthesis(const FftArgsN<NL>& a, int l, int item, unsigned char* smem_raw) {
     typedef T TW __attribute__((ext_vector_type(2 * VW)));
     cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
     cx<T>* twl = buf + FC * GP;

@@ -4,6 +4,8 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <cstring>
+#include <type_traits>
 
 #include "../../include/sht.h"
 
@@ -58,10 +60,13 @@ struct LevelDesc {
   const double* murow; // Kp nodes mu_j of the northern rows, zero past Jh (analysis with generated P~)
 };
 
-struct FftArgs {
+// Kernel arguments, for NL levels: a launch over one level passes one
+// descriptor instead of eight (a launch with 2.7 KB of arguments takes the
+// host 4.1 us, one with 512 bytes 3.1 us).
+template <int NL>
+struct FftArgsN {
   int nlev;
   int nitems;
-  LevelDesc lev[SHT_MAX_LEVELS];
   const void* src;   // grid (analysis) or workspace (synthesis)
   void* dst;         // workspace (analysis) or grid (synthesis)
   // scalars: value *= (use_w ? w_j : 1) * (use_inv_I ? 1/I : 1) * (m ? mscale : 1)
@@ -76,17 +81,21 @@ struct FftArgs {
   // null otherwise); the synthesis leaves whole 128-latitude tiles below it
   // out of the workspace, and the zonal synthesis reads them as zero
   const int* jstart;
+  LevelDesc lev[NL];
 };
+typedef FftArgsN<SHT_MAX_LEVELS> FftArgs;
+typedef FftArgsN<1> FftArgs1;
+
 
 // One work tile of a Legendre kernel; level < 0 marks an idle slot.
 struct Tile {
   int level, m, rb, cb;
 };
 
-struct GemmArgs {
+template <int NL>
+struct GemmArgsN {
   int nlev;
   int ntiles;
-  LevelDesc lev[SHT_MAX_LEVELS];
   const Tile* tiles;           // one per workgroup
   const long long* tab_off;    // per (level, m): element offset of the table block
   const void* table;           // P~ table copy (FP64 in the FP64 form, else FP32)
@@ -102,7 +111,27 @@ struct GemmArgs {
   const long long* seed_off;
   const double* rec;
   const long long* rec_off;
+  LevelDesc lev[NL];
 };
+typedef GemmArgsN<SHT_MAX_LEVELS> GemmArgs;
+
+
+// The arguments of a single-level launch (level 0 of a).
+inline FftArgs1 one_level(const FftArgs& a) {
+  FftArgs1 o;
+  std::memcpy(&o, &a, sizeof(o));  // the levels come last, level 0 first
+  o.nlev = 1;
+  return o;
+}
+inline GemmArgsN<1> one_level(const GemmArgs& a) {
+  GemmArgsN<1> o;
+  std::memcpy(&o, &a, sizeof(o));
+  o.nlev = 1;
+  return o;
+}
+static_assert(std::is_trivially_copyable<FftArgs>::value && offsetof(FftArgs, lev) == offsetof(FftArgs1, lev) &&
+                  std::is_trivially_copyable<GemmArgs>::value && offsetof(GemmArgs, lev) == offsetof(GemmArgsN<1>, lev),
+              "one layout up to the levels");
 
 // ---- kernel launchers (sht_fft.hip, sht_legendre.hip) ----
 // The stream argument is a hipStream_t.
@@ -154,10 +183,10 @@ inline bool zonal_offsets_fit(long long wblk, long long elem) { return 64.0 * (d
 int zonal_one_launch_spills(int form, bool analysis);
 // Lengths 16 R2 R3 of a single level (sht_group.h): -1 where these kernels do
 // not take the level, else a hipError_t; ncu compute units.
-int launch_zonal_group_analysis_f32(const FftArgs& a, int ncu, void* stream);
-int launch_zonal_group_synthesis_f32(const FftArgs& a, int ncu, void* stream);
-int launch_zonal_group_analysis_f64(const FftArgs& a, int ncu, void* stream);
-int launch_zonal_group_synthesis_f64(const FftArgs& a, int ncu, void* stream);
+int launch_zonal_group_analysis_f32(const FftArgs1& a, int ncu, void* stream);
+int launch_zonal_group_synthesis_f32(const FftArgs1& a, int ncu, void* stream);
+int launch_zonal_group_analysis_f64(const FftArgs1& a, int ncu, void* stream);
+int launch_zonal_group_synthesis_f64(const FftArgs1& a, int ncu, void* stream);
 // Any lengths (sht_zonal_any.hip); ncu compute units.
 int launch_zonal_any(bool dbl, bool analysis, const FftArgs& a, int ncu, void* stream);
 int launch_zonal(int form, bool analysis, const FftArgs& a, int maxN, void* stream);

@@ -137,10 +137,10 @@ __device__ __forceinline__ int gen_swz(int row) {
 // the generated block is written after the products (its previous contents
 // were read into registers before the last barrier), read after the next
 // barrier, and a second barrier guards it against the next block's writes.
-template <typename T, int NCB, bool GEN>
+template <typename T, int NCB, bool GEN, int NL>
 // (The FP64 generated kernel with 8 column blocks fills the LDS, one
 // workgroup per compute unit: it takes the registers of two waves per SIMD.)
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GEN && NCB > 4 ? 2 : 4))) void k_legendre_analysis(const GemmArgs g) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GEN && NCB > 4 ? 2 : 4))) void k_legendre_analysis(const GemmArgsN<NL> g) {
   typedef typename Acc<T>::type AccT;
   typedef typename V16<T>::type V;
   using S = AnalysisShape<T, NCB, GEN>;
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 
   const Tile t = g.tiles[blockIdx.x];
   if (t.level < 0) return;
-  const LevelDesc& L = g.lev[t.level];
+  const LevelDesc& L = g.lev[NL == 1 ? 0 : t.level];
   const int N = L.N, m = t.m;
   const int nm = N - m + 1;
   const int r0 = t.rb * 128;
@@ -405,8 +405,8 @@ struct SynthesisShape {
 // 16 rows of one group for 64 latitudes of the tile each into an LDS block
 // [row][latitude] (pitch 130: the reads of one instruction, 16 latitudes by
 // 4 rows, fall on distinct banks); barriers as in the analysis.
-template <typename T, int NCB, bool GEN>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_legendre_synthesis(const GemmArgs g) {
+template <typename T, int NCB, bool GEN, int NL>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) void k_legendre_synthesis(const GemmArgsN<NL> g) {
   typedef typename Acc<T>::type AccT;
   typedef typename V16<T>::type V;
   using S = SynthesisShape<T, NCB>;
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 
   const Tile t = g.tiles[blockIdx.x];
   if (t.level < 0) return;
-  const LevelDesc& L = g.lev[t.level];
+  const LevelDesc& L = g.lev[NL == 1 ? 0 : t.level];
   const int N = L.N, m = t.m;
   const int nm = N - m + 1;
   const int nkb = (nm + 2 * KR - 1) / (2 * KR);
@@ -663,28 +663,28 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) =
 // ---------------------------------------------------------------------------
 constexpr int kMaxSynthesisNcb = 8;
 
-template <typename T, int NCB, bool GEN>
-static hipError_t launch_ncb(bool analysis, const GemmArgs& g, hipStream_t st) {
+template <typename T, int NCB, bool GEN, int NL>
+static hipError_t launch_ncb(bool analysis, const GemmArgsN<NL>& g, hipStream_t st) {
   const dim3 grid(g.ntiles), block(512);
   if constexpr (sizeof(T) == 8 && NCB > 8) return hipErrorInvalidValue;  // FP64 takes at most 8
   else if (analysis) {
     const size_t lds = AnalysisShape<T, NCB, GEN>::lds_bytes(GEN);
-    lds_optin<k_legendre_analysis<T, NCB, GEN>>(lds);
-    hipLaunchKernelGGL((k_legendre_analysis<T, NCB, GEN>), grid, block, lds, st, g);
+    lds_optin<k_legendre_analysis<T, NCB, GEN, NL>>(lds);
+    hipLaunchKernelGGL((k_legendre_analysis<T, NCB, GEN, NL>), grid, block, lds, st, g);
   } else {
     // wider synthesis tiles do not fit the register file
     if constexpr (NCB > kMaxSynthesisNcb) return hipErrorInvalidValue;
     else {
       const size_t lds = SynthesisShape<T, NCB>::lds_bytes(GEN);
-      lds_optin<k_legendre_synthesis<T, NCB, GEN>>(lds);
-      hipLaunchKernelGGL((k_legendre_synthesis<T, NCB, GEN>), grid, block, lds, st, g);
+      lds_optin<k_legendre_synthesis<T, NCB, GEN, NL>>(lds);
+      hipLaunchKernelGGL((k_legendre_synthesis<T, NCB, GEN, NL>), grid, block, lds, st, g);
     }
   }
   return hipGetLastError();
 }
 
-template <typename T, bool GEN>
-static hipError_t launch_legendre_t(bool analysis, const GemmArgs& g, int ncb, hipStream_t st) {
+template <typename T, bool GEN, int NL>
+static hipError_t launch_legendre_t(bool analysis, const GemmArgsN<NL>& g, int ncb, hipStream_t st) {
   switch (ncb) {
     case 1: return launch_ncb<T, 1, GEN>(analysis, g, st);
     case 2: return launch_ncb<T, 2, GEN>(analysis, g, st);
@@ -700,15 +700,22 @@ static hipError_t launch_legendre_t(bool analysis, const GemmArgs& g, int ncb, h
   }
 }
 
+template <int NL>
+static hipError_t launch_legendre_n(int form, bool analysis, const GemmArgsN<NL>& g, int ncb, bool gen,
+                                    hipStream_t st) {
+  if (form == SHT_FORM_FP64)
+    return gen ? launch_legendre_t<double, true>(analysis, g, ncb, st)
+               : launch_legendre_t<double, false>(analysis, g, ncb, st);
+  return gen ? launch_legendre_t<float, true>(analysis, g, ncb, st)
+             : launch_legendre_t<float, false>(analysis, g, ncb, st);
+}
+
 int launch_legendre(int form, bool analysis, const GemmArgs& g, int ncb, bool gen, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (g.ntiles <= 0) return (int)hipSuccess;
   if (form == SHT_FORM_BF16X6) return (int)launch_legendre_bf16(analysis, g, ncb, gen, st);
-  if (form == SHT_FORM_FP64)
-    return (int)(gen ? launch_legendre_t<double, true>(analysis, g, ncb, st)
-                     : launch_legendre_t<double, false>(analysis, g, ncb, st));
-  return (int)(gen ? launch_legendre_t<float, true>(analysis, g, ncb, st)
-                   : launch_legendre_t<float, false>(analysis, g, ncb, st));
+  return (int)(g.nlev == 1 ? launch_legendre_n(form, analysis, one_level(g), ncb, gen, st)
+                           : launch_legendre_n(form, analysis, g, ncb, gen, st));
 }
 
 }  // namespace sht

@@ -162,8 +162,8 @@ __device__ __forceinline__ int x6_swz(int row) { return 2 * ((row >> 1) & 15); }
 // latitude t % 32 into an LDS block; after a barrier each wave reads and
 // splits its values, and a second barrier guards the block against the
 // next block's writes.
-template <int NCB, bool GEN>
-__global__ __launch_bounds__(X6Analysis<NCB>::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_legendre_analysis_bf16(const GemmArgs g) {
+template <int NCB, bool GEN, int NL>
+__global__ __launch_bounds__(X6Analysis<NCB>::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_legendre_analysis_bf16(const GemmArgsN<NL> g) {
   using S = X6Analysis<NCB>;
   constexpr int BN = S::BN, KB = S::KB, P = kX6Pitch, TR = S::TR;
   typedef float f4 __attribute__((ext_vector_type(4)));
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(X6Analysis<NCB>::NT) __attribute__((amdgpu_waves_pe
 
   const Tile t = g.tiles[blockIdx.x];
   if (t.level < 0) return;
-  const LevelDesc& L = g.lev[t.level];
+  const LevelDesc& L = g.lev[NL == 1 ? 0 : t.level];
   const int N = L.N, m = t.m;
   const int nm = N - m + 1;
   const int r0 = t.rb * 256;
@@ -440,8 +440,8 @@ struct X6Synthesis {
 // analysis): per block of 64 natural rows wave w produces the 16 rows of
 // group w >> 1 at the latitudes 64 (w & 1) + lane of the tile into an LDS
 // block [row][GP].
-template <int NCB, bool GEN>
-__global__ __launch_bounds__(X6Synthesis<NCB>::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_legendre_synthesis_bf16(const GemmArgs g) {
+template <int NCB, bool GEN, int NL>
+__global__ __launch_bounds__(X6Synthesis<NCB>::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_legendre_synthesis_bf16(const GemmArgsN<NL> g) {
   using S = X6Synthesis<NCB>;
   constexpr int BN = S::BN, P = kX6Pitch, TR = S::TR;
   typedef float f4 __attribute__((ext_vector_type(4)));
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(X6Synthesis<NCB>::NT) __attribute__((amdgpu_waves_p
 
   const Tile t = g.tiles[blockIdx.x];
   if (t.level < 0) return;
-  const LevelDesc& L = g.lev[t.level];
+  const LevelDesc& L = g.lev[NL == 1 ? 0 : t.level];
   const int N = L.N, m = t.m;
   const int nm = N - m + 1;
   const int nkb = (nm + 63) / 64;       // blocks of 64 natural rows
@@ -696,23 +696,23 @@ __global__ __launch_bounds__(X6Synthesis<NCB>::NT) __attribute__((amdgpu_waves_p
 // ---------------------------------------------------------------------------
 // launcher
 // ---------------------------------------------------------------------------
-template <int NCB, bool GEN>
-static hipError_t launch_bf16_ncb(bool analysis, const GemmArgs& g, hipStream_t st) {
+template <int NCB, bool GEN, int NL>
+static hipError_t launch_bf16_ncb(bool analysis, const GemmArgsN<NL>& g, hipStream_t st) {
   const dim3 grid(g.ntiles);
   if (analysis) {
     const size_t lds = X6Analysis<NCB>::lds_bytes(GEN);
-    lds_optin<k_legendre_analysis_bf16<NCB, GEN>>(lds);
-    hipLaunchKernelGGL((k_legendre_analysis_bf16<NCB, GEN>), grid, dim3(X6Analysis<NCB>::NT), lds, st, g);
+    lds_optin<k_legendre_analysis_bf16<NCB, GEN, NL>>(lds);
+    hipLaunchKernelGGL((k_legendre_analysis_bf16<NCB, GEN, NL>), grid, dim3(X6Analysis<NCB>::NT), lds, st, g);
   } else {
     const size_t lds = X6Synthesis<NCB>::lds_bytes(GEN);
-    lds_optin<k_legendre_synthesis_bf16<NCB, GEN>>(lds);
-    hipLaunchKernelGGL((k_legendre_synthesis_bf16<NCB, GEN>), grid, dim3(X6Synthesis<NCB>::NT), lds, st, g);
+    lds_optin<k_legendre_synthesis_bf16<NCB, GEN, NL>>(lds);
+    hipLaunchKernelGGL((k_legendre_synthesis_bf16<NCB, GEN, NL>), grid, dim3(X6Synthesis<NCB>::NT), lds, st, g);
   }
   return hipGetLastError();
 }
 
-template <bool GEN>
-static hipError_t launch_bf16_gen(bool analysis, const GemmArgs& g, int ncb, hipStream_t st) {
+template <bool GEN, int NL>
+static hipError_t launch_bf16_gen(bool analysis, const GemmArgsN<NL>& g, int ncb, hipStream_t st) {
   switch (ncb) {
     case 1: return launch_bf16_ncb<1, GEN>(analysis, g, st);
     case 2: return launch_bf16_ncb<2, GEN>(analysis, g, st);
@@ -727,6 +727,10 @@ static hipError_t launch_bf16_gen(bool analysis, const GemmArgs& g, int ncb, hip
 }
 
 hipError_t launch_legendre_bf16(bool analysis, const GemmArgs& g, int ncb, bool gen, hipStream_t st) {
+  if (g.nlev == 1) {
+    const GemmArgsN<1> o = one_level(g);
+    return gen ? launch_bf16_gen<true>(analysis, o, ncb, st) : launch_bf16_gen<false>(analysis, o, ncb, st);
+  }
   return gen ? launch_bf16_gen<true>(analysis, g, ncb, st) : launch_bf16_gen<false>(analysis, g, ncb, st);
 }
 

@@ -2,6 +2,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "sht_any.h"
 #include "sht_internal.h"
 
@@ -13,14 +15,14 @@ constexpr int any_wpe() {
   return sizeof(T) == 4 ? 4 : 2;
 }
 
-template <typename T, int NT, bool VEC, int VW>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()))) void k_zonal_any_analysis(const FftArgs a) {
+template <typename T, int NT, bool VEC, int VW, int NL>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()))) void k_zonal_any_analysis(const FftArgsN<NL> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   any_analysis_run<T, NT, VEC, VW>(a, blockIdx.x, a.nitems, smem_raw);
 }
 
-template <typename T, int NT, bool VEC, int VW>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()))) void k_zonal_any_synthesis(const FftArgs a) {
+template <typename T, int NT, bool VEC, int VW, int NL>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()))) void k_zonal_any_synthesis(const FftArgsN<NL> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   any_synthesis_run<T, NT, VEC, VW>(a, blockIdx.x, a.nitems, smem_raw);
 }
@@ -30,8 +32,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()
 // ---------------------------------------------------------------------------
 constexpr size_t kAnyMaxLds = 160 * 1024;
 
-template <auto Kernel>
-static hipError_t any_go(const FftArgs& a, int NT, int wpe, size_t lds, int ncu, hipStream_t st) {
+template <auto Kernel, class A>
+static hipError_t any_go(const A& a, int NT, int wpe, size_t lds, int ncu, hipStream_t st) {
   static size_t done = 0;
   if (lds > 65536 && lds > done) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -47,10 +49,26 @@ static hipError_t any_go(const FftArgs& a, int NT, int wpe, size_t lds, int ncu,
   return hipGetLastError();
 }
 
-template <typename T, int NT, bool VEC, int VW>
-static hipError_t any_dir(bool analysis, const FftArgs& a, size_t lds, int ncu, hipStream_t st) {
-  return analysis ? any_go<k_zonal_any_analysis<T, NT, VEC, VW>>(a, NT, any_wpe<T>(), lds, ncu, st)
-                  : any_go<k_zonal_any_synthesis<T, NT, VEC, VW>>(a, NT, any_wpe<T>(), lds, ncu, st);
+template <typename T, int NT, bool VEC, int VW, int NL>
+static hipError_t any_dir(bool analysis, const FftArgsN<NL>& a, size_t lds, int ncu, hipStream_t st) {
+  return analysis ? any_go<k_zonal_any_analysis<T, NT, VEC, VW, NL>>(a, NT, any_wpe<T>(), lds, ncu, st)
+                  : any_go<k_zonal_any_synthesis<T, NT, VEC, VW, NL>>(a, NT, any_wpe<T>(), lds, ncu, st);
+}
+
+template <typename T, int NL>
+static hipError_t any_shape(bool analysis, bool small, bool vec, const FftArgsN<NL>& a, size_t lds, int ncu,
+                            hipStream_t st) {
+  auto go = [&](auto nt, auto vw) {
+    constexpr int NT = decltype(nt)::value, VW = decltype(vw)::value;
+    return vec ? any_dir<T, NT, true, VW>(analysis, a, lds, ncu, st)
+               : any_dir<T, NT, false, VW>(analysis, a, lds, ncu, st);
+  };
+  using N256 = std::integral_constant<int, 256>;
+  using N512 = std::integral_constant<int, 512>;
+  using One = std::integral_constant<int, 1>;
+  using VWT = std::integral_constant<int, sizeof(T) == 4 ? 2 : 1>;
+  if (a.lfc == 0) return small ? go(N256{}, One{}) : go(N512{}, One{});
+  return small ? go(N256{}, VWT{}) : go(N512{}, VWT{});
 }
 
 template <typename T>
@@ -70,7 +88,8 @@ static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStrea
   }
   // fields per item: as many as a workspace run holds, as long as two
   // workgroups share a compute unit's LDS, no group is mostly empty and the
-  // device has two items per compute unit
+  // device has an item per compute unit (T85 with 7 fields: 28 us a pair with
+  // two per unit, one field each, 24 with one)
   auto lds_of = [&](int fc) { return (size_t)((size_t)fc * maxIP + maxI) * sizeof(cx<T>); };
   auto items_of = [&](int fc) {
     long long n = 0;
@@ -79,7 +98,7 @@ static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStrea
   };
   int lfc = sizeof(T) == 4 ? 3 : 2;
   while (lfc > 0 && ((1 << lfc) * (long long)maxI > 512LL * E || (1 << lfc) * (maxN + 1LL) > 256LL * E ||
-                     lds_of(1 << lfc) > kAnyMaxLds / 2 || (1 << (lfc - 1)) >= maxF || items_of(1 << lfc) < 2LL * ncu))
+                     lds_of(1 << lfc) > kAnyMaxLds / 2 || (1 << (lfc - 1)) >= maxF || items_of(1 << lfc) < ncu))
     --lfc;
   const int fc = 1 << lfc;
   const bool small = fc * (long long)maxI <= 256LL * E && fc * (maxN + 1LL) <= 128LL * E;
@@ -98,13 +117,8 @@ static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStrea
   }
   if (items > 0x7fffffff) return hipErrorInvalidValue;
   a.nitems = (int)items;
-  constexpr int VW = sizeof(T) == 4 ? 2 : 1;
-  if (VW == 2 && lfc == 0) {
-    if (small) return vec ? any_dir<T, 256, true, 1>(analysis, a, lds, ncu, st) : any_dir<T, 256, false, 1>(analysis, a, lds, ncu, st);
-    return vec ? any_dir<T, 512, true, 1>(analysis, a, lds, ncu, st) : any_dir<T, 512, false, 1>(analysis, a, lds, ncu, st);
-  }
-  if (small) return vec ? any_dir<T, 256, true, VW>(analysis, a, lds, ncu, st) : any_dir<T, 256, false, VW>(analysis, a, lds, ncu, st);
-  return vec ? any_dir<T, 512, true, VW>(analysis, a, lds, ncu, st) : any_dir<T, 512, false, VW>(analysis, a, lds, ncu, st);
+  return a.nlev == 1 ? any_shape<T>(analysis, small, vec, one_level(a), lds, ncu, st)
+                     : any_shape<T>(analysis, small, vec, a, lds, ncu, st);
 }
 
 int launch_zonal_any(bool dbl, bool analysis, const FftArgs& a, int ncu, void* stream) {

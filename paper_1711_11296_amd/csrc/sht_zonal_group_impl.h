@@ -13,7 +13,7 @@ namespace {
 
 template <typename T, int I, bool ANA>
 __global__ __launch_bounds__((GroupShape<T, I, ANA>::NT))
-    __attribute__((amdgpu_waves_per_eu(GroupShape<T, I, ANA>::WPE))) void k_zonal_group(const FftArgs a) {
+    __attribute__((amdgpu_waves_per_eu(GroupShape<T, I, ANA>::WPE))) void k_zonal_group(const FftArgs1 a) {
   using S = GroupShape<T, I, ANA>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if constexpr (ANA)
@@ -23,12 +23,12 @@ __global__ __launch_bounds__((GroupShape<T, I, ANA>::NT))
 }
 
 template <typename T, int I, bool ANA>
-int go(const FftArgs& a0, int ncu, hipStream_t st) {
+int go(const FftArgs1& a0, int ncu, hipStream_t st) {
   using S = GroupShape<T, I, ANA>;
   using G = Grp<T, typename S::P, S::NT, S::FC, S::PF>;
   constexpr size_t lds = G::lds(), most = 160 * 1024;
   static_assert(lds <= most, "one workgroup's LDS");
-  FftArgs a = a0;
+  FftArgs1 a = a0;
   LevelDesc& L = a.lev[0];
   L.nfb = (L.F + S::FC - 1) / S::FC;
   L.fft_item0 = 0;
@@ -52,9 +52,9 @@ int go(const FftArgs& a0, int ncu, hipStream_t st) {
 
 }  // namespace
 
-// Launch level 0 of a (single-level arguments); -1 if these kernels do not
+// Launch a's level; -1 if these kernels do not
 // take it.
-int SHT_GROUP_LAUNCH(const FftArgs& a, int ncu, void* stream) {
+int SHT_GROUP_LAUNCH(const FftArgs1& a, int ncu, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   switch (a.lev[0].I) {
 #define SHT_GROUP_CASE(i) \

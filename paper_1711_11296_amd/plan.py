@@ -119,7 +119,7 @@ class Plan:
         if out is None:
             out = torch.empty(out_shape, dtype=self.dtype, device=x.device)
         self._check(out, out_elems, names[1])
-        stream = torch.cuda.current_stream(x.device).cuda_stream
+        stream = _lib.raw_stream(x.device)
         _lib.check(fn(self._h, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()),
                       ctypes.c_void_p(stream)))
         return out

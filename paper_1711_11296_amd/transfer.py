@@ -32,7 +32,7 @@ def spec_retruncate(spec, N_in, N_out):
     if tuple(spec.shape) != (F, nc_in, 2):
         raise ValueError("spec must be [F, %d, 2]" % nc_in)
     out = torch.empty((F, (N_out + 1) * (N_out + 2) // 2, 2), dtype=spec.dtype, device=spec.device)
-    stream = torch.cuda.current_stream(spec.device).cuda_stream
+    stream = _lib.raw_stream(spec.device)
     _lib.check(lib.sht_spec_retruncate(N_in, N_out, F, _dbl(spec), ctypes.c_void_p(spec.data_ptr()),
                                        ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(stream)))
     return out
@@ -58,27 +58,30 @@ def grid_inject(grid, J_coarse, I_coarse, kind="cc_poles", out=None):
         out = torch.empty((F, J_coarse, I_coarse), dtype=grid.dtype, device=grid.device)
     else:
         _check_out(out, (F, J_coarse, I_coarse), grid)
-    stream = torch.cuda.current_stream(grid.device).cuda_stream
+    stream = _lib.raw_stream(grid.device)
     _lib.check(lib.sht_grid_inject(J, I, J_coarse, I_coarse, F, _GRID[kind], _dbl(grid),
                                    ctypes.c_void_p(grid.data_ptr()), ctypes.c_void_p(out.data_ptr()),
                                    ctypes.c_void_p(stream)))
     return out
 
 
-def grid_product(a, b):
-    """Pointwise product a * b of two grids of the same shape and dtype."""
-    import torch
+def product_into(a, b, out):
+    """out = a * b for contiguous grids of one shape, dtype and device (out
+    may be a or b); no checks beyond the library's own."""
     lib = _lib.load()
-    if a.shape != b.shape or a.dtype != b.dtype or a.device != b.device:
-        raise ValueError("a and b must match in shape, dtype and device")
-    a = a.contiguous()
-    b = b.contiguous()
-    out = torch.empty_like(a)
-    stream = torch.cuda.current_stream(a.device).cuda_stream
+    stream = _lib.raw_stream(a.device)
     _lib.check(lib.sht_grid_product(a.numel(), _dbl(a), ctypes.c_void_p(a.data_ptr()), ctypes.c_void_p(b.data_ptr()),
                                     ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(stream)))
     return out
 
+
+def grid_product(a, b):
+    """Pointwise product a * b of two grids of the same shape and dtype."""
+    import torch
+    if a.shape != b.shape or a.dtype != b.dtype or a.device != b.device:
+        raise ValueError("a and b must match in shape, dtype and device")
+    a = a.contiguous()
+    return product_into(a, b.contiguous(), torch.empty_like(a))
 
 
 def spec_laplacian(spec, N, scale=1.0, out=None):
@@ -92,7 +95,7 @@ def spec_laplacian(spec, N, scale=1.0, out=None):
     if tuple(spec.shape) != (F, (N + 1) * (N + 2) // 2, 2):
         raise ValueError("spec must be [F, %d, 2]" % ((N + 1) * (N + 2) // 2))
     out = torch.empty_like(spec) if out is None else _check_out(out, spec.shape, spec)
-    stream = torch.cuda.current_stream(spec.device).cuda_stream
+    stream = _lib.raw_stream(spec.device)
     _lib.check(lib.sht_spec_laplacian(N, F, _dbl(spec), float(scale), ctypes.c_void_p(spec.data_ptr()),
                                       ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(stream)))
     return out
@@ -113,7 +116,7 @@ def grid_residual(x, kappa, y, f, alpha, out=None):
     if n_per < 1 or n % n_per:
         raise ValueError("kappa must tile x")
     r = torch.empty_like(ts[0]) if out is None else _check_out(out, ts[0].shape, ts[0])
-    stream = torch.cuda.current_stream(x.device).cuda_stream
+    stream = _lib.raw_stream(x.device)
     _lib.check(lib.sht_grid_residual(n, n_per, _dbl(ts[0]), float(alpha), *[ctypes.c_void_p(t.data_ptr()) for t in ts],
                                      ctypes.c_void_p(r.data_ptr()), ctypes.c_void_p(stream)))
     return r
