@@ -17,7 +17,9 @@ BUILD = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-HIP_SOURCES = ["sht_fft.hip", "sht_zonal_any.hip", "sht_zonal_analysis_f32.hip", "sht_zonal_synthesis_f32.hip", "sht_zonal_analysis_f64.hip", "sht_zonal_synthesis_f64.hip",
+HIP_SOURCES = ["sht_fft.hip", "sht_zonal_any.hip",
+               "sht_zonal_analysis_f32.hip", "sht_zonal_synthesis_f32.hip",
+               "sht_zonal_analysis_f64.hip", "sht_zonal_synthesis_f64.hip",
                "sht_legendre.hip", "sht_legendre_bf16.hip", "sht_transfer.hip", "sht_api.hip"]
 CXX_SOURCES = ["sht_host.cpp", "sht_plan.cpp"]
 

@@ -106,6 +106,8 @@ def raw_stream(device):
     """The hipStream_t of torch's current stream on a CUDA (HIP) device, as an
     integer, without building a torch.cuda.Stream object (1.9 us a call)."""
     import torch
+    if device.type != "cuda":  # a host pointer must not reach a kernel
+        raise ValueError("expected a CUDA (HIP) device, got %s" % device)
     index = device.index
     if index is None:
         index = torch.cuda.current_device()

@@ -40,6 +40,8 @@ class NonlinearTerms:
             raise ValueError("spectra must be triangular with truncation <= %d" % self.N)
         p = self.plan
         s = torch.cat([U, V, W]).to(p.dtype)
+        if tuple(s.shape[1:]) != (nc, 2):
+            raise ValueError("spectra must be [1, %d, 2]" % nc)
         g = p.inverse(s if Nt == self.N else spec_retruncate(s, Nt, self.N))
         # the products go straight into the analysis' input (stacking them
         # copied three grids); the third analysed slot is unused
