@@ -52,8 +52,7 @@ int go(const FftArgs1& a0, int ncu, hipStream_t st) {
 
 }  // namespace
 
-// Launch a's level; -1 if these kernels do not
-// take it.
+// Launch a's level; -1 if these kernels do not take it.
 int SHT_GROUP_LAUNCH(const FftArgs1& a, int ncu, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   switch (a.lev[0].I) {

@@ -27,8 +27,8 @@ SHAPES = [
     (54, 20, 41, 17), (81, 40, 33, 4), (90, 44, 40, 8), (125, 62, 30, 3), (128, 63, 127, 33), (135, 60, 25, 16),
     (240, 79, 160, 12), (243, 121, 21, 5), (256, 85, 171, 7), (512, 170, 40, 19), (625, 300, 9, 3), (720, 30, 61, 41),
     (750, 374, 8, 6), (768, 383, 9, 9), (1024, 511, 12, 5), (1250, 100, 11, 4), (1280, 639, 10, 9),
-    (1536, 500, 9, 6), (2000, 40, 21, 3), (2048, 1023, 6, 2), (2187, 50, 15, 2), (3072, 20, 33, 7), (3125, 30, 13, 3),
-    (3240, 1619, 5, 1), (4096, 25, 21, 9),
+    (1536, 500, 9, 6), (2000, 40, 21, 3), (2048, 350, 6, 2), (2187, 50, 15, 2), (3072, 20, 33, 7), (3125, 30, 13, 3),
+    (3240, 401, 5, 1), (4096, 25, 21, 9),
 ]
 
 

@@ -28,15 +28,12 @@ def _rel(x, ref):
 def test_every_length(I, form):
     from paper_1711_11296_amd import Plan
     dt = torch.float64 if form == "fp64" else torch.float32
+    # N: a few wavenumbers, a third of the row, all of it (the oracle's time
+    # bounds the large ones: 1440 and 2304 run up to (I - 1) / 2)
     k = LENGTHS.index(I)
-    N = [(I - 1) // 2, 37, I // 3][k % 3]
-    J = 21 + k % 2
-    # at least 256 items of the kernel's group size (1 to 8 fields)
-    F = 8 * (256 // ((J + 1) // 2) + 1) + 3
-    if N > 300:
-        J, F = 9 + k % 2, 8 * 52 + 5
-    if N > 900:
-        F = 131 if form == "fp64" else 8 * 52 + 1
+    N = [(I - 1) // 2, 37, I // 3][k % 3] if I <= 800 or I in (1440, 2304) else [37, 90][k % 2]
+    J = 9 + k % 2
+    F = 8 * 52 + 5 if N < 900 else 131  # at least 256 items of the kernel's group size (1 to 8 fields)
     p = Plan(N, J, I, F, grid="fejer2", form=form, otf=True)
     pick = [0, F // 2, F - 1]
     g = torch.randn((F, J, I), dtype=dt, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(I))
