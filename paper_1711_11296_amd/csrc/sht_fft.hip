@@ -19,11 +19,11 @@
 //
 // Three families of kernels: sht_group.h (lengths 16 R2 R3 known at compile
 // time), sht_any.h (any length), and here the ones that hold their runs in
-// registers, which lengths past 2048 use in one direction (launch_held),
+// registers, which some lengths past 2048 use (launch_held),
 // with the choice of kernel and the multi-level launches.
 //
-// Work decomposition of the kernels here: one workgroup per (mirror row pair, block of FB
-// fields).  The FB fields go through the LDS buffer one after the other and
+// Work decomposition of the kernels here: one workgroup per (mirror row
+// pair, block of FB fields).  The FB fields go through the LDS buffer one after the other and
 // the wavenumbers m <= N of all FB fields are kept in registers, so that each
 // workspace access is a contiguous run of 2*FB values (64 bytes) per (m,
 // parity, row) instead of one isolated complex value; the analysis stores
@@ -607,19 +607,37 @@ static hipError_t launch_p3(const FftArgs1& a, int maxN, hipStream_t st) {
 // (450), 2560 456 (523), 2880 497 (599), 3072 516 us (657)) and FP64
 // synthesis (2880, 48 fields, 801 rows: 422 (440)).  With 4 fields of a block
 // per item, which is all the LDS holds there, the group kernels' analysis
-// stores 32-byte pieces.  Up to three wavenumbers per thread (I <= 3072).
+// stores 32-byte pieces.  FP64's group kernels (2 fields, 32-byte pieces too)
+// hold their own except where the wavenumbers' regions lie a multiple of
+// 32 KiB apart, Cp a multiple of 64 (64 fields, 1919 rows: 2160 685 (780),
+// 2304 734 (916), 2560 960 (1131), 2880 1172 us (1452); 96 fields, 1201 rows:
+// 2880 1098 (1205); 48 fields, other strides: both 390; 3072, where the runs
+// spill: 1422 (1336)).  Up to three wavenumbers per thread (I <= 3072).
+// FP64 analysis takes the larger radix second: beside the runs a thread then
+// holds 12 values of the last pass, not 15 (2880: 1567 us with radix 15 last,
+// 102 spills); the synthesis, which stores from there, gains nothing.
+template <typename T, bool ANA, int I, int R2, int R3>
+using HeldPlan = std::conditional_t<sizeof(T) == 8 && ANA, Plan3<I, R3, R2>, Plan3<I, R2, R3>>;
+
 template <typename T, int FB, bool ANA>
 static bool launch_held(const FftArgs1& a, int maxN, hipStream_t st, hipError_t* err) {
-  if constexpr ((sizeof(T) == 4) != ANA) {
+  if constexpr (sizeof(T) == 4 && !ANA) {
     return false;
   } else {
+    constexpr bool ana64 = sizeof(T) == 8 && ANA;
+    if (ana64 && a.lev[0].Cp % 64 != 0) return false;
     switch (a.lev[0].I) {
-      case 2160: *err = launch_p3<T, FB, ANA, Plan3<2160, 9, 15>>(a, maxN, st); return true;
+      case 2160: *err = launch_p3<T, FB, ANA, HeldPlan<T, ANA, 2160, 9, 15>>(a, maxN, st); return true;
       case 2304: *err = launch_p3<T, FB, ANA, Plan3<2304, 12, 12>>(a, maxN, st); return true;
-      case 2400: *err = launch_p3<T, FB, ANA, Plan3<2400, 10, 15>>(a, maxN, st); return true;
+      case 2400: *err = launch_p3<T, FB, ANA, HeldPlan<T, ANA, 2400, 10, 15>>(a, maxN, st); return true;
       case 2560: *err = launch_p3<T, FB, ANA, Plan3<2560, 16, 10>>(a, maxN, st); return true;
-      case 2880: *err = launch_p3<T, FB, ANA, Plan3<2880, 12, 15>>(a, maxN, st); return true;
-      case 3072: *err = launch_p3<T, FB, ANA, Plan3<3072, 16, 12>>(a, maxN, st); return true;
+      case 2880: *err = launch_p3<T, FB, ANA, HeldPlan<T, ANA, 2880, 12, 15>>(a, maxN, st); return true;
+      case 3072:
+        if constexpr (ana64)
+          return false;
+        else
+          *err = launch_p3<T, FB, ANA, Plan3<3072, 16, 12>>(a, maxN, st);
+        return true;
       default: return false;
     }
   }

@@ -64,3 +64,21 @@ def test_few_fields_and_items(I, N, J, F, form):
     assert _rel(s[pick].double().cpu().numpy(), O.forward(g[pick].double().cpu().numpy(), N, "cc_poles")) < TOL[form]
     assert _rel(x[pick].double().cpu().numpy(), O.inverse(a[pick].double().cpu().numpy(), N, J, I, "cc_poles")) < TOL[form]
     p.close()
+
+
+# one to three wavenumbers per thread of the register-held kernels, 64 fields:
+# a region stride of 32 KiB times a whole number in FP64
+@pytest.mark.parametrize("form", ["fp32", "fp64"])
+@pytest.mark.parametrize("I,N", [(2160, 37), (2160, 1079), (2304, 600), (2400, 520), (2400, 1199), (2560, 511),
+                                 (2560, 1279), (2880, 512), (2880, 1024), (3072, 1023)])
+def test_held_runs(I, N, form):
+    from paper_1711_11296_amd import Plan
+    dt = torch.float64 if form == "fp64" else torch.float32
+    J, F, pick = 9, 64, [0, 33, 63]
+    p = Plan(N, J, I, F, grid="fejer2", form=form, otf=True)
+    g = torch.randn((F, J, I), dtype=dt, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(N))
+    s = p.forward(g)
+    torch.cuda.synchronize()
+    ref = O.forward(g[pick].double().cpu().numpy(), N, "fejer2")
+    assert _rel(s[pick].double().cpu().numpy(), ref) < TOL[form]
+    p.close()
