@@ -340,9 +340,11 @@ int build_plan(int nlev, const int* Nv, const int* Jv, const int* Iv, const int*
   {
     long long Cp[SHT_MAX_LEVELS];
     for (int l = 0; l < nlev; ++l) Cp[l] = P->lev[l].Cp;
-    for (int dir = 0; dir < 2; ++dir)
+    for (int dir = 0; dir < 2; ++dir) {
+      const int def = default_tile(o.form, nlev, Nv, Jv, Fv, FB, P->jst.data(), dir == 0, ncu);
       (dir == 0 ? P->ncb_fwd : P->ncb_inv) = choose_tile(o.form, P->otf != 0, nlev, Nv, Jv, Fv, Cp, P->jst.data(),
-                                                         dir == 0, ncu, nullptr);
+                                                         dir == 0, def, ncu, nullptr);
+    }
   }
   // flops kept by the reduced transform (whole analysis blocks left out)
   P->flops_kept = 0.0;

@@ -12,48 +12,121 @@
 
 namespace sht {
 
-double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const int* jst,
-                     bool analysis, int k, int ncu) {
-  // fixed work of a K block in units of one column block's products: the
-  // barrier and, in the split form, the split of the table operand; with
-  // generated P~ the recurrence comes on top
-  double a = form == SHT_FORM_FP64 ? (analysis ? 0.3 : 0.6) : form == SHT_FORM_FP32 ? (analysis ? 0.4 : 1.0) : 2.2;
-  if (gen) a += analysis ? 3.0 : 1.5;
-  const int rows = analysis ? (form == SHT_FORM_BF16X6 ? 256 : 128) : 128;
-  double total = 0, longest = 0;
-  long long ntiles = 0, mb = 0;
+// 16-column blocks that the least-padding width rounds the rows to.
+static int padding_tile(int form, int nlev, const int* N, const int* J, const int* F) {
+  int best = 1;
+  double bestc = 1e300;
+  for (int k : {10, 8, 5, 4, 2, 1}) {
+    if (form == SHT_FORM_FP64 && (k == 10 || k == 5)) continue;
+    double c = 0;
+    for (int l = 0; l < nlev; ++l)
+      c += (double)(N[l] + 1) * (N[l] + 2) * ((J[l] + 1) / 2) * (double)roundup(2LL * F[l], 16LL * k);
+    if (c < bestc * (1 - 1e-12)) {
+      bestc = c;
+      best = k;
+    }
+  }
+  return best;
+}
+
+static long long row_length(int F, int g, int FB) { return roundup(2LL * F, std::lcm(16LL * g, 2LL * FB)); }
+
+// Tiles of a direction with k column blocks; add(level, m, K blocks of one
+// tile, tiles) is called for every (level, m).
+template <class Add>
+static void each_tile(int form, int nlev, const int* N, const int* J, const int* F, const int* jst, bool analysis,
+                      int k, Add add) {
+  const int rows = analysis && form == SHT_FORM_BF16X6 ? 256 : 128;
+  long long mb = 0;
   for (int l = 0; l < nlev; ++l) {
     const int Jh = (J[l] + 1) / 2, jt = (Jh + 127) / 128;
     const long long ncol = (2LL * F[l] + 16 * k - 1) / (16 * k);
     for (int m = 0; m <= N[l]; ++m) {
-      const int nm = N[l] - m + 1, j0 = jst ? jst[mb + m] : 0;
-      const double blocks = analysis ? (Jh - j0 / 32 * 32 + 31) / 32 : (nm + 31) / 32;
-      const long long n = (analysis ? (nm + rows - 1) / rows : jt - j0 / 128) * ncol;
-      const double c = blocks * (k + a) * (rows / 128);
-      total += n * c;
-      ntiles += n;
-      if (n > 0 && c > longest) longest = c;
+      const int nm = N[l] - m + 1;
+      const int j0 = jst ? jst[mb + m] : 0;
+      const int blocks = analysis ? (Jh - j0 / 32 * 32 + 31) / 32 : (nm + 31) / 32;
+      add(blocks * (rows / 128), (analysis ? (nm + rows - 1) / rows : jt - j0 / 128) * ncol);
     }
     mb += N[l] + 1;
   }
+}
+
+double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const int* jst,
+                     bool analysis, int k, int ncu) {
+  // fixed work of a K block in units of one column block's products: the
+  // barrier, the split of the table operand in the split form and the
+  // recurrence of generated P~
+  double a;
+  if (form == SHT_FORM_FP64)
+    a = analysis ? (gen ? 0.8 : 0.6) : (gen ? 0.7 : 0.8);
+  else if (form == SHT_FORM_FP32)
+    a = analysis ? (gen ? 2.5 : 0.4) : (gen ? 2.5 : 1.0);
+  else
+    a = analysis ? 5.0 : (gen ? 6.5 : 3.5);
+  double total = 0, longest = 0;
+  long long ntiles = 0;
+  each_tile(form, nlev, N, J, F, jst, analysis, k, [&](int blocks, long long n) {
+    const double c = blocks * (k + a);
+    total += n * c;
+    ntiles += n;
+    if (n > 0 && c > longest) longest = c;
+  });
   if (ntiles == 0) return 0;
-  // per compute unit: whole rounds of the analysis' tiles, which cost the
-  // same in one level; the synthesis' lists start with the longest tiles and
-  // end with short ones
-  const double per = (double)ntiles / ncu;
-  if (analysis && nlev == 1) return total / ntiles * std::ceil(per);
-  return total / ncu + 0.5 * longest;
+  // per compute unit: the analysis' tiles cost the same in one level; where
+  // one or two workgroups fill a unit (split form, generated P~) they run in
+  // whole rounds, else more narrow ones share it.  The synthesis' lists start
+  // with the longest tiles and end with short ones.
+  if (analysis && nlev == 1 && (gen || form == SHT_FORM_BF16X6))
+    return total / ntiles * std::ceil((double)ntiles / ncu);
+  return total / ncu + (analysis ? 1.0 : 0.5) * longest;
+}
+
+int default_tile(int form, int nlev, const int* N, const int* J, const int* F, int FB, const int* jst, bool analysis,
+                 int ncu) {
+  const int g = padding_tile(form, nlev, N, J, F);
+  auto fits = [&](int k) {
+    bool ok = k <= max_ncb(form, analysis);
+    for (int l = 0; l < nlev; ++l) ok = ok && row_length(F[l], g, FB) % (16 * k) == 0;
+    return ok;
+  };
+  auto tight = [&](int k) {
+    bool ok = true;
+    for (int l = 0; l < nlev; ++l) ok = ok && roundup(2LL * F[l], 16LL * k) == row_length(F[l], g, FB);
+    return ok;
+  };
+  int k = g;
+  if (!fits(k))
+    for (int c : {1, 2, 4, 5, 8})
+      if (fits(c)) k = c;
+  for (;;) {
+    long long n = 0;
+    each_tile(form, nlev, N, J, F, jst, analysis, k, [&](int, long long t) { n += t; });
+    if (n >= 2LL * ncu) return k;
+    int next = 0;
+    for (int c : {1, 2, 4, 5, 8})
+      if (c < k && fits(c) && tight(c)) next = c;
+    if (!next) return k;
+    k = next;
+  }
+}
+
+// generated P~ in FP32, analysis: these widths spill 35 registers and take
+// longer than their neighbours (N = 255, 200 fields: 203 us with seven blocks,
+// 147 with five)
+static bool tile_spills(int form, bool gen, bool analysis, int k) {
+  return gen && analysis && form == SHT_FORM_FP32 && (k == 7 || k == 9);
 }
 
 int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const long long* Cp,
-                const int* jst, bool analysis, int ncu, double* cost) {
+                const int* jst, bool analysis, int def, int ncu, double* cost) {
+  constexpr double margin = 1 / 0.95;
   int best = 1;
   double bestc = 1e300;
   for (int k = max_ncb(form, analysis); k >= 1; --k) {
-    bool ok = true;
+    bool ok = !tile_spills(form, gen, analysis, k);
     for (int l = 0; l < nlev; ++l) ok = ok && Cp[l] % (16 * k) == 0;
     if (!ok) continue;
-    const double c = legendre_cost(form, gen, nlev, N, J, F, jst, analysis, k, ncu);
+    const double c = legendre_cost(form, gen, nlev, N, J, F, jst, analysis, k, ncu) * (k == def ? 1.0 : margin);
     if (c < bestc * (1 - 1e-12)) {
       bestc = c;
       best = k;
@@ -66,6 +139,8 @@ int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const 
 int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J, const int* F, int FB, int ncu,
                        long long ws_limit) {
   const int elem = form == SHT_FORM_FP64 ? 8 : 4;
+  const int def_a = default_tile(form, nlev, N, J, F, FB, nullptr, true, ncu);
+  const int def_s = default_tile(form, nlev, N, J, F, FB, nullptr, false, ncu);
   long long least = 0;
   std::vector<long long> Cp(nlev);
   int best = 1;
@@ -74,7 +149,7 @@ int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J,
     for (int g = max_ncb(form, true); g >= 1; --g) {
       long long ws = 0;
       for (int l = 0; l < nlev; ++l) {
-        Cp[l] = roundup(2LL * F[l], std::lcm(16LL * g, 2LL * FB));
+        Cp[l] = row_length(F[l], g, FB);
         ws += (N[l] + 1) * ws_block(Cp[l], elem, false) * (((J[l] + 1) / 2 + SHT_K_PAD - 1) / SHT_K_PAD) * elem;
       }
       if (pass == 0) {
@@ -85,8 +160,8 @@ int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J,
       // where that would cross the limit
       if (ws > least + least / 4 || (ws > ws_limit && least <= ws_limit)) continue;
       double ca = 0, cs = 0;
-      choose_tile(form, gen, nlev, N, J, F, Cp.data(), nullptr, true, ncu, &ca);
-      choose_tile(form, gen, nlev, N, J, F, Cp.data(), nullptr, false, ncu, &cs);
+      choose_tile(form, gen, nlev, N, J, F, Cp.data(), nullptr, true, def_a, ncu, &ca);
+      choose_tile(form, gen, nlev, N, J, F, Cp.data(), nullptr, false, def_s, ncu, &cs);
       // ties: the tighter rows, then the wider granularity
       const double c = (ca + cs) * (1 + 1e-3 * (double)ws / (double)least);
       if (c < bestc * (1 - 1e-9)) {

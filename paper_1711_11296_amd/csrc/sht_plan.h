@@ -31,16 +31,31 @@ inline long long roundup(long long a, long long b) { return (a + b - 1) / b * b;
 // Time estimate of one direction's Legendre kernel with column tiles of k
 // 16-column blocks on ncu compute units, in units of one K block's products
 // for one column block: every tile costs (K blocks) (k + a) with a the work
-// of a K block that does not depend on the tile's width.  a was fitted to
-// timings of every width (T479 with 45 and 100 fields, T319 with 45): FP32
-// 0.4 / 1.0 (analysis / synthesis), FP64 0.3 / 0.6, split form 2.2.
+// of a K block that does not depend on the tile's width.  a was fitted, with
+// the shape of the sum over tiles, to timings of every width at truncations
+// 21..639 with J = 2N + 1 and N + 1 and 8..400 fields (1000 plans with tables,
+// 1245 with generated P~); the widths it picks take 1.00 to 1.05 times the
+// best one's time (geometric mean per form and direction).
 // gen: generated P~; jst as for build_tiles (or null).
 double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const int* jst,
                      bool analysis, int k, int ncu);
 
-// Column blocking of a direction: the k of least estimated time among those that tile every level's workspace row Cp exactly.
+// The width a direction takes unless the estimate promises more: of the
+// widths 1, 2, 4, 5, 8, 10 the one that pads the columns least (the wider on
+// ties), narrowed as long as the compute units would get fewer than two tiles
+// each.
+int default_tile(int form, int nlev, const int* N, const int* J, const int* F, int FB, const int* jst, bool analysis,
+                 int ncu);
+
+// Column blocking of a direction: of the widths that tile every level's
+// workspace row Cp exactly the one of least estimated time, where a width
+// other than def (default_tile) has to gain 5 %, about what the estimate can
+// tell apart.  Over the 4500 kernels of the fit the estimate alone took more
+// than 3 % longer than def in 220, the worst 38 % (FP64 with generated P~,
+// N = 213, 48 fields, synthesis: 45.9 us with three blocks, 33.4 with def's
+// two); with the margin in 62, the worst 18 %.
 int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const long long* Cp,
-                const int* jst, bool analysis, int ncu, double* cost);
+                const int* jst, bool analysis, int def, int ncu, double* cost);
 
 // Granularity g of the workspace rows (16-column blocks; Cp is 2 F rounded
 // up to lcm(16 g, 2 FB)): the one whose divisors serve both directions best.
