@@ -702,11 +702,14 @@ std::string tune_key(const sht_plan_s* P) {
 // A column blocking c (16-column units) is admissible for a direction when
 // the kernel takes it and it tiles every level's workspace row exactly (tiles
 // wholly past the last field are not generated).
+std::vector<int> blockings(const sht_plan_s* P, bool analysis) {
+  long long Cp[SHT_MAX_LEVELS];
+  for (int l = 0; l < P->nlev; ++l) Cp[l] = P->lev[l].Cp;
+  return tune_widths(P->form, P->nlev, Cp, analysis);
+}
 bool blocking_ok(const sht_plan_s* P, bool analysis, int c) {
-  if (c < 1 || c > max_ncb(P->form, analysis)) return false;
-  for (int l = 0; l < P->nlev; ++l)
-    if (P->lev[l].Cp % (16 * c)) return false;
-  return true;
+  const std::vector<int> w = blockings(P, analysis);
+  return std::find(w.begin(), w.end(), c) != w.end();
 }
 
 bool tune_lookup(const std::string& key, int v[6]) {
@@ -760,8 +763,6 @@ int autotune(sht_plan_s* P) {
                       (v[2] == P->ncb_inv || blocking_ok(P, false, v[2])) && (v[1] == 0 || v[1] == 1) &&
                       (v[3] == 0 || v[3] == 1) && (v[4] == 0 || v[4] == 1) && (v[5] == 0 || v[5] == 1);
   if (!cached) {
-    int ncu = 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, P->device) != hipSuccess) ncu = 0;
     void* spec = nullptr;
     hipStream_t st = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -777,13 +778,9 @@ int autotune(sht_plan_s* P) {
       const bool analysis = dir == 0;
       float best = 1e30f;
       int bc = analysis ? P->ncb_fwd : P->ncb_inv, bs = 0;
-      for (int c = 1; c <= max_ncb(P->form, analysis); ++c)
+      for (int c : blockings(P, analysis))
         for (int sched = 0; sched < 2 && !rc; ++sched) {
-          if (!blocking_ok(P, analysis, c)) continue;
           std::vector<Tile> t = build_tiles(P->form, P->nlev, P->lev, P->jst.data(), analysis, c, sched);
-          // a blocking that leaves compute units without a tile cannot beat a
-          // narrower one (c = 1 is always admissible)
-          if (c > 1 && std::count_if(t.begin(), t.end(), [](const Tile& x) { return x.level >= 0; }) < ncu) continue;
           Tile* dt = nullptr;
           if ((rc = hip_check(hipMalloc(reinterpret_cast<void**>(&dt), t.size() * sizeof(Tile)), "tune alloc"))) break;
           (void)hipMemcpy(dt, t.data(), t.size() * sizeof(Tile), hipMemcpyHostToDevice);

@@ -136,6 +136,16 @@ int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const 
   return best;
 }
 
+std::vector<int> tune_widths(int form, int nlev, const long long* Cp, bool analysis) {
+  std::vector<int> w;
+  for (int k = 1; k <= max_ncb(form, analysis); ++k) {
+    bool ok = true;
+    for (int l = 0; l < nlev; ++l) ok = ok && Cp[l] % (16 * k) == 0;
+    if (ok) w.push_back(k);
+  }
+  return w;
+}
+
 int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J, const int* F, int FB, int ncu,
                        long long ws_limit) {
   const int elem = form == SHT_FORM_FP64 ? 8 : 4;

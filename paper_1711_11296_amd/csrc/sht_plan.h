@@ -57,6 +57,12 @@ int default_tile(int form, int nlev, const int* N, const int* J, const int* F, i
 int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const long long* Cp,
                 const int* jst, bool analysis, int def, int ncu, double* cost);
 
+// The widths the autotuner times for a direction: every one that tiles the
+// rows.  (Few wide tiles can beat more narrow ones, also where they leave
+// compute units without a tile: FP64, T170 with 19 fields, analysis, 214 tiles
+// of three blocks 17.6 us, 642 of one block 17.8.)
+std::vector<int> tune_widths(int form, int nlev, const long long* Cp, bool analysis);
+
 // Granularity g of the workspace rows (16-column blocks; Cp is 2 F rounded
 // up to lcm(16 g, 2 FB)): the one whose divisors serve both directions best.
 // 100 fields (13 blocks) take 14 blocks, two tiles of 7: Legendre analysis /
