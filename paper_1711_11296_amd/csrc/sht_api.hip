@@ -681,8 +681,7 @@ std::string tune_path() {
 }
 
 // The key pins everything a cached choice depends on: device architecture,
-// HIP runtime version, the tuner's version, form, every level's sizes and the
-// workspace layout (row length Cp, fields per zonal item).
+// HIP runtime version and tune_plan_key.
 std::string tune_key(const sht_plan_s* P) {
   hipDeviceProp_t prop;
   std::string arch = "unknown";
@@ -691,12 +690,8 @@ std::string tune_key(const sht_plan_s* P) {
     if (ch == ' ') ch = '_';
   int rt = 0;
   (void)hipRuntimeGetVersion(&rt);
-  std::string k = arch + " hip" + std::to_string(rt) + " v3 form" + std::to_string(P->form) + " fb" +
-                  std::to_string(P->fb) + " lev" + std::to_string(P->nlev);
-  for (int l = 0; l < P->nlev; ++l)
-    k += " " + std::to_string(P->lev[l].N) + "," + std::to_string(P->lev[l].J) + "," + std::to_string(P->lev[l].I) +
-         "," + std::to_string(P->lev[l].F) + "," + std::to_string(P->lev[l].Cp);
-  return k;
+  return arch + " hip" + std::to_string(rt) + " " +
+         tune_plan_key(P->form, P->fb, P->grid, P->reduced != 0, P->nlev, P->lev);
 }
 
 // A column blocking c (16-column units) is admissible for a direction when

@@ -146,6 +146,16 @@ std::vector<int> tune_widths(int form, int nlev, const long long* Cp, bool analy
   return w;
 }
 
+std::string tune_plan_key(int form, int fb, int grid, bool reduced, int nlev, const LevelDesc* lev) {
+  std::string k = "v3 kern" + std::to_string(kKernelGen) + " form" + std::to_string(form) + " fb" + std::to_string(fb) +
+                  " grid" + std::to_string(grid) + " red" + std::to_string(reduced ? 1 : 0) + " lev" +
+                  std::to_string(nlev);
+  for (int l = 0; l < nlev; ++l)
+    k += " " + std::to_string(lev[l].N) + "," + std::to_string(lev[l].J) + "," + std::to_string(lev[l].I) + "," +
+         std::to_string(lev[l].F) + "," + std::to_string(lev[l].Cp);
+  return k;
+}
+
 int choose_granularity(int form, bool gen, int nlev, const int* N, const int* J, const int* F, int FB, int ncu,
                        long long ws_limit) {
   const int elem = form == SHT_FORM_FP64 ? 8 : 4;

@@ -6,6 +6,7 @@
 #ifndef SHT_PLAN_H_
 #define SHT_PLAN_H_
 
+#include <string>
 #include <vector>
 
 #include "sht_internal.h"
@@ -62,6 +63,15 @@ int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const 
 // compute units without a tile: FP64, T170 with 19 fields, analysis, 214 tiles
 // of three blocks 17.6 us, 642 of one block 17.8.)
 std::vector<int> tune_widths(int form, int nlev, const long long* Cp, bool analysis);
+
+// The part of the tuner's cache key that does not depend on the device: line
+// format v3, the generation of the kernels that were timed (kKernelGen: raised
+// whenever Legendre or zonal kernels or the candidates change, so that a line
+// timed on others is not used), form, zonal item width, grid and reduced
+// transform (which fix the latitudes left out, so the tile lists), and every
+// level's sizes and row length.
+constexpr int kKernelGen = 2;
+std::string tune_plan_key(int form, int fb, int grid, bool reduced, int nlev, const LevelDesc* lev);
 
 // Granularity g of the workspace rows (16-column blocks; Cp is 2 F rounded
 // up to lcm(16 g, 2 FB)): the one whose divisors serve both directions best.

@@ -93,9 +93,24 @@ static void check_tune_widths() {
         }
 }
 
+// A cached line is one plan's: the key tells apart the kernels it was timed
+// on, the reduced transform and the grid (other tile lists).
+static void check_tune_key() {
+  const int N = 170, J = 341, I = 512, F = 19;
+  LevelDesc lev[SHT_MAX_LEVELS];
+  Layout Y;
+  layout_levels(1, &N, &J, &I, &F, 48, 4, lev, &Y);
+  const std::string k = tune_plan_key(SHT_FORM_FP64, 4, SHT_GRID_FEJER2, false, 1, lev);
+  CHECK(k != tune_plan_key(SHT_FORM_FP64, 4, SHT_GRID_FEJER2, true, 1, lev), "reduced: %s", k.c_str());
+  CHECK(k != tune_plan_key(SHT_FORM_FP64, 4, SHT_GRID_GAUSS, false, 1, lev), "grid: %s", k.c_str());
+  // the key of the lines timed on the kernels before the present ones
+  CHECK(k.find("v3 form") == std::string::npos && k.find("v3 kern") == 0, "generation: %s", k.c_str());
+}
+
 int main() {
   check_widths();
   check_tune_widths();
+  check_tune_key();
   std::printf("rules_check: %d failures\n", g_fail);
   return g_fail ? 1 : 0;
 }
