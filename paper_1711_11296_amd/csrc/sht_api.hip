@@ -697,14 +697,28 @@ std::string tune_key(const sht_plan_s* P) {
 // A column blocking c (16-column units) is admissible for a direction when
 // the kernel takes it and it tiles every level's workspace row exactly (tiles
 // wholly past the last field are not generated).
-std::vector<int> blockings(const sht_plan_s* P, bool analysis) {
+bool blocking_ok(const sht_plan_s* P, bool analysis, int c) {
+  if (c < 1 || c > max_ncb(P->form, analysis)) return false;
   long long Cp[SHT_MAX_LEVELS];
   for (int l = 0; l < P->nlev; ++l) Cp[l] = P->lev[l].Cp;
-  return tune_widths(P->form, P->nlev, Cp, analysis);
+  return width_tiles(P->nlev, Cp, c);
 }
-bool blocking_ok(const sht_plan_s* P, bool analysis, int c) {
-  const std::vector<int> w = blockings(P, analysis);
-  return std::find(w.begin(), w.end(), c) != w.end();
+
+// The blockings the tuner times (tune_widths).
+std::vector<int> tune_blockings(const sht_plan_s* P, bool analysis) {
+  int N[SHT_MAX_LEVELS], J[SHT_MAX_LEVELS], F[SHT_MAX_LEVELS];
+  long long Cp[SHT_MAX_LEVELS];
+  for (int l = 0; l < P->nlev; ++l) {
+    N[l] = P->lev[l].N;
+    J[l] = P->lev[l].J;
+    F[l] = P->lev[l].F;
+    Cp[l] = P->lev[l].Cp;
+  }
+  int ncu = 0;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, P->device) != hipSuccess || ncu <= 0)
+    ncu = 256;
+  const int def = default_tile(P->form, P->nlev, N, J, F, P->fb, P->jst.data(), analysis, ncu);
+  return tune_widths(P->form, P->otf != 0, P->nlev, N, J, F, Cp, P->jst.data(), analysis, def, ncu);
 }
 
 bool tune_lookup(const std::string& key, int v[6]) {
@@ -773,7 +787,7 @@ int autotune(sht_plan_s* P) {
       const bool analysis = dir == 0;
       float best = 1e30f;
       int bc = analysis ? P->ncb_fwd : P->ncb_inv, bs = 0;
-      for (int c : blockings(P, analysis))
+      for (int c : tune_blockings(P, analysis))
         for (int sched = 0; sched < 2 && !rc; ++sched) {
           std::vector<Tile> t = build_tiles(P->form, P->nlev, P->lev, P->jst.data(), analysis, c, sched);
           Tile* dt = nullptr;

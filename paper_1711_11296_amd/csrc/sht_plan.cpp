@@ -110,6 +110,12 @@ int default_tile(int form, int nlev, const int* N, const int* J, const int* F, i
   }
 }
 
+bool width_tiles(int nlev, const long long* Cp, int k) {
+  bool ok = true;
+  for (int l = 0; l < nlev; ++l) ok = ok && Cp[l] % (16 * k) == 0;
+  return ok;
+}
+
 // generated P~ in FP32, analysis: these widths spill 35 registers and take
 // longer than their neighbours (N = 255, 200 fields: 203 us with seven blocks,
 // 147 with five)
@@ -123,9 +129,7 @@ int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const 
   int best = 1;
   double bestc = 1e300;
   for (int k = max_ncb(form, analysis); k >= 1; --k) {
-    bool ok = !tile_spills(form, gen, analysis, k);
-    for (int l = 0; l < nlev; ++l) ok = ok && Cp[l] % (16 * k) == 0;
-    if (!ok) continue;
+    if (tile_spills(form, gen, analysis, k) || !width_tiles(nlev, Cp, k)) continue;
     const double c = legendre_cost(form, gen, nlev, N, J, F, jst, analysis, k, ncu) * (k == def ? 1.0 : margin);
     if (c < bestc * (1 - 1e-12)) {
       bestc = c;
@@ -136,12 +140,20 @@ int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const 
   return best;
 }
 
-std::vector<int> tune_widths(int form, int nlev, const long long* Cp, bool analysis) {
+std::vector<int> tune_widths(int form, bool gen, int nlev, const int* N, const int* J, const int* F,
+                             const long long* Cp, const int* jst, bool analysis, int def, int ncu) {
+  const int own = choose_tile(form, gen, nlev, N, J, F, Cp, jst, analysis, def, ncu, nullptr);
   std::vector<int> w;
+  std::vector<double> cost(max_ncb(form, analysis) + 1, -1);
+  double least = 1e300;
   for (int k = 1; k <= max_ncb(form, analysis); ++k) {
-    bool ok = true;
-    for (int l = 0; l < nlev; ++l) ok = ok && Cp[l] % (16 * k) == 0;
-    if (ok) w.push_back(k);
+    if (!width_tiles(nlev, Cp, k)) continue;
+    cost[k] = legendre_cost(form, gen, nlev, N, J, F, jst, analysis, k, ncu);
+    least = std::min(least, cost[k]);
+  }
+  for (int k = 1; k <= max_ncb(form, analysis); ++k) {
+    const bool plain = k == 1 || k == 2 || k == 4 || k == 5 || k == 8 || k == 10;
+    if (cost[k] >= 0 && (plain || k == def || k == own || cost[k] <= 1.25 * least)) w.push_back(k);
   }
   return w;
 }

@@ -48,6 +48,9 @@ double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, c
 int default_tile(int form, int nlev, const int* N, const int* J, const int* F, int FB, const int* jst, bool analysis,
                  int ncu);
 
+// Whether tiles of k column blocks cover every level's workspace row exactly.
+bool width_tiles(int nlev, const long long* Cp, int k);
+
 // Column blocking of a direction: of the widths that tile every level's
 // workspace row Cp exactly the one of least estimated time, where a width
 // other than def (default_tile) has to gain 5 %, about what the estimate can
@@ -58,11 +61,15 @@ int default_tile(int form, int nlev, const int* N, const int* J, const int* F, i
 int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const long long* Cp,
                 const int* jst, bool analysis, int def, int ncu, double* cost);
 
-// The widths the autotuner times for a direction: every one that tiles the
-// rows.  (Few wide tiles can beat more narrow ones, also where they leave
-// compute units without a tile: FP64, T170 with 19 fields, analysis, 214 tiles
-// of three blocks 17.6 us, 642 of one block 17.8.)
-std::vector<int> tune_widths(int form, int nlev, const long long* Cp, bool analysis);
+// The widths the autotuner times for a direction, of those that tile the
+// rows: the plan's own (def and the one choose_tile takes), 1, 2, 4, 5, 8 and
+// 10, and the others where the estimate lies within a quarter of the least.
+// (Whether a width leaves compute units without a tile says nothing: FP64,
+// T170 with 19 fields, analysis, 214 tiles of three blocks 17.6 us, 642 of one
+// 17.8.  Timing all widths would find nothing more: none of the ones left out
+// was the best of 2100 timed kernels by more than 2 %.)
+std::vector<int> tune_widths(int form, bool gen, int nlev, const int* N, const int* J, const int* F,
+                             const long long* Cp, const int* jst, bool analysis, int def, int ncu);
 
 // The part of the tuner's cache key that does not depend on the device: line
 // format v3, the generation of the kernels that were timed (kKernelGen: raised

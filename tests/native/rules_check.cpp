@@ -68,28 +68,27 @@ static void check_widths() {
 }
 
 // The autotuner times the width a plan has without it, also where its tiles
-// are fewer than the compute units (T170 FP64 with 19 fields, 48 columns:
-// three blocks, 214 tiles; T106 FP32 with 40 fields: five and three blocks).
+// are fewer than the compute units, and every width of the least-padding rule.
 static void check_tune_widths() {
   auto has = [](const std::vector<int>& w, int k) {
     for (int x : w)
       if (x == k) return true;
     return false;
   };
-  const long long c48 = 48, c80 = 80, c160 = 160;
-  CHECK(has(tune_widths(SHT_FORM_FP64, 1, &c48, true), 3), "FP64, 48 columns");
-  CHECK(has(tune_widths(SHT_FORM_FP32, 1, &c80, true), 5), "FP32, 80 columns");
-  CHECK(has(tune_widths(SHT_FORM_FP32, 1, &c160, true), 10), "FP32, 160 columns, analysis");
-  CHECK(!has(tune_widths(SHT_FORM_FP32, 1, &c160, false), 10), "FP32, 160 columns, synthesis");
   for (int form : {SHT_FORM_FP64, SHT_FORM_FP32, SHT_FORM_BF16X6})
-    for (int N : {21, 106, 170, 319})
+    for (int N : {21, 80, 106, 170, 319})
       for (int F = 1; F <= 130; ++F)
         for (int dir = 0; dir < 2; ++dir) {
           const int J = 2 * N + 1, FB = zonal_fields_per_block(form);
           const int g = choose_granularity(form, false, 1, &N, &J, &F, FB, kCu, SHT_NOALLOC_WORKSPACE_BYTES);
           const long long Cp = roundup(2LL * F, std::lcm(16LL * g, 2LL * FB));
-          CHECK(has(tune_widths(form, 1, &Cp, dir == 0), width(form, false, dir == 0, N, J, F)),
-                "form %d N %d F %d dir %d", form, N, F, dir);
+          const std::vector<int> jst(N + 1, 0);
+          const int def = default_tile(form, 1, &N, &J, &F, FB, jst.data(), dir == 0, kCu);
+          const std::vector<int> w = tune_widths(form, false, 1, &N, &J, &F, &Cp, jst.data(), dir == 0, def, kCu);
+          CHECK(has(w, width(form, false, dir == 0, N, J, F)), "form %d N %d F %d dir %d", form, N, F, dir);
+          for (int k : {1, 2, 4, 5, 8, 10})
+            CHECK(has(w, k) == (k <= max_ncb(form, dir == 0) && Cp % (16 * k) == 0), "form %d N %d F %d dir %d: %d", form,
+                  N, F, dir, k);
         }
 }
 
