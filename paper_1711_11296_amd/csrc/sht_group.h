@@ -13,7 +13,7 @@
 // registers (sht_fft.hip; one 512-thread workgroup per compute unit at 190
 // to 250 registers) nothing but the current pass lives in registers, so two
 // or more workgroups, or one of 1024 threads, overlap their memory and
-// compute phases.  GroupShape has the shapes and what they measured.
+// compute phases.  GroupShape (sht_zonal_rule.h) has the shapes and what they measured.
 #ifndef SHT_GROUP_H_
 #define SHT_GROUP_H_
 
@@ -22,61 +22,9 @@
 #include "sht_any.h"
 #include "sht_dft.h"
 #include "sht_internal.h"
+#include "sht_zonal_rule.h"
 
 namespace sht {
-
-// Every length 16 R2 R3 from 288 on with radices up to 16.
-#define SHT_GROUP_LENGTHS(X)                                                                                      \
-  X(288) X(320) X(384) X(400) X(432) X(480) X(512) X(576) X(640) X(720) X(768) X(800) X(864) X(960) X(1024)       \
-  X(1152) X(1200) X(1280) X(1296) X(1440) X(1536) X(1600) X(1728) X(1920) X(2048) X(2160) X(2304) X(2400) X(2560) \
-  X(2880) X(3072) X(3600) X(3840) X(4096)
-
-// Radices of the second and third pass for NT threads and FC sequences: a
-// thread holds ceil(FC (I / R) / NT) butterflies of R values in a pass; the
-// pair of least sum (a second, nearly empty round of butterflies costs as
-// much as a full one, and its registers), then the larger second radix.
-constexpr bool grp_radix(int r) {
-  return r == 2 || r == 3 || r == 4 || r == 5 || r == 6 || r == 8 || r == 9 || r == 10 || r == 12 || r == 15 || r == 16;
-}
-constexpr int grp_held(int I, int R, int NT, int FC) { return (FC * (I / R) + NT - 1) / NT * R; }
-constexpr int grp_r2(int I, int NT, int FC) {
-  int best = 0, cost = 1 << 30;
-  for (int r = 16; r >= 2; --r) {
-    const int q = I / 16;
-    if (q % r || !grp_radix(r) || !grp_radix(q / r)) continue;
-    const int c = grp_held(I, r, NT, FC) + grp_held(I, q / r, NT, FC);
-    if (c < cost) {
-      cost = c;
-      best = r;
-    }
-  }
-  return best;
-}
-constexpr int grp_most_held(int I, int NT, int FC) {
-  const int r2 = grp_r2(I, NT, FC), a = grp_held(I, r2, NT, FC), b = grp_held(I, I / 16 / r2, NT, FC);
-  return a > b ? a : b;
-}
-
-// Three passes of radices 16, R2, R3 over sequences that lie side by side in
-// LDS.  The first pass stores element 16 j + t at the padded position
-// 17 j + t, so that the lanes of a wave, which own consecutive j, hit
-// distinct banks; the second reads that order (its inputs j + t I/R2 sit at
-// j + j/16 + t (17/16)(I/R2), I/R2 being a multiple of 16) and writes the
-// natural order; the third reads and writes the natural order.  Twiddles of
-// passes two and three are staged in LDS as [t-1][k] (k = butterfly position
-// within its Ns-block).
-template <int I_, int R2_, int R3_>
-struct Plan3 {
-  static constexpr int I = I_, R1 = 16, R2 = R2_, R3 = R3_;
-  static_assert(R1 * R2 * R3 == I, "radices must multiply to I");
-  static constexpr int nb1 = I / R1, nb2 = I / R2, nb3 = I / R3;
-  static constexpr int Ns2 = R1, Ns3 = R1 * R2;
-  static_assert(nb3 == Ns3, "last pass");
-  static_assert(I % 16 == 0 && nb2 % 16 == 0, "padded layout");
-  static constexpr int IP = I + I / 16;        // padded field stride
-  static constexpr int S2P = nb2 + nb2 / 16;   // padded stride of pass-2 inputs
-  static constexpr int tw2 = 0, tw3 = (R2 - 1) * Ns2, ntw = tw3 + (R3 - 1) * Ns3;
-};
 
 // field stride in LDS
 template <class P>
@@ -397,36 +345,6 @@ struct Grp {
     }
     return item;
   }
-};
-
-// Shape of a length's kernel: NT threads, FC fields per item, waves per SIMD
-// the registers are sized for, PF: the next item is fetched into registers
-// during the current one (else another workgroup covers the latency).
-// Chosen from sweeps over lengths (MI355X, 801 or 1601 rows, analysis /
-// synthesis in us; "held" = the kernels of sht_fft.hip where they exist, else
-// those of sht_any.h):
-//  FP32, 300 fields      480: 72 / 66 (held 87 / 74)       1024: 310 / 281 (413 / 424)
-//                        800: 202 / 171 (236 / 263)        1280: 476 / 487 (603 / 626)
-//  FP32, 400 fields 1440: 852 / 900 (1045 / 1061)   64 fields 2048: 279 / 300 (445 / 453)
-//  FP64, 48 fields       640: 40 / 39 (78 / 78)            1280: 152 / 149 (272 / 318)
-// FP32 analysis takes all 8 fields of a workspace block (64-byte pieces;
-// with 4 fields 1440 rose to 1137) while a thread holds at most 16 values
-// and a pass at most 20 per buffer; FP32 synthesis mostly 4.  From 1600 on
-// one workgroup fills a compute unit's LDS: it has 1024 threads and fetches
-// ahead.
-template <typename T, int I, bool ANA>
-struct GroupShape {
-  static constexpr bool dbl = sizeof(T) == 8;
-  static constexpr bool all8 =
-      !dbl && (ANA ? I <= 2048 && grp_most_held(I, I <= 512 ? 256 : I <= 1024 ? 512 : 1024, 8) <= 20
-                   : I > 512 && I <= 1024 && grp_most_held(I, 512, 8) <= 16);
-  static constexpr int NT = dbl ? (I <= 1024 ? 256 : 512)
-                            : all8 ? (I <= 512 ? 256 : I <= 1024 ? 512 : 1024)
-                                   : (I <= 512 ? 256 : I <= 1600 ? 512 : 1024);
-  static constexpr int FC = dbl ? (I <= 1920 ? 4 : I <= 3072 ? 2 : 1) : all8 ? 8 : I <= 3840 ? 4 : 2;
-  static constexpr bool PF = dbl ? (I > 1024 && (ANA || I <= 1280 || I > 1920)) : !all8 && I > 1600;
-  static constexpr int WPE = dbl ? 2 : 4;
-  using P = Plan3<I, grp_r2(I, NT, FC), I / 16 / grp_r2(I, NT, FC)>;
 };
 
 }  // namespace sht

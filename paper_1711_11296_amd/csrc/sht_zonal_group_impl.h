@@ -33,8 +33,7 @@ int go(const FftArgs1& a0, int ncu, hipStream_t st) {
   L.nfb = (L.F + S::FC - 1) / S::FC;
   L.fft_item0 = 0;
   const long long items = (long long)L.Jh * L.nfb;
-  // few items or mostly empty groups: the any-length kernels split further
-  if (items < ncu || 2 * S::FC > 3 * L.F) return -1;
+  if (!group_takes(S::FC, L, ncu)) return -1;
   // 32-bit lane offsets within the rows of one group
   if ((double)S::FC * L.J * L.I * sizeof(T) >= 4294967296.0 || items > 0x7fffffff) return -1;
   a.nitems = (int)items;

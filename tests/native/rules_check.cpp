@@ -5,6 +5,7 @@
 #include <vector>
 
 #include "sht_plan.h"
+#include "sht_zonal_rule.h"
 
 using namespace sht;
 
@@ -106,8 +107,52 @@ static void check_tune_key() {
   CHECK(k.find("v3 form") == std::string::npos && k.find("v3 kern") == 0, "generation: %s", k.c_str());
 }
 
+static LevelDesc level(int J, int I, int F) {
+  LevelDesc L{};
+  L.N = I / 3;
+  L.J = J;
+  L.Jh = (J + 1) / 2;
+  L.I = I;
+  L.F = F;
+  return L;
+}
+
+// The group kernels take levels with few items (fewer than compute units),
+// whose empty sequences cost nothing, and leave mostly empty groups to the
+// any-length kernels only where every unit has an item.  Times in us: group,
+// any-length.
+static void check_group_rule() {
+  struct {
+    bool dbl, analysis;
+    int J, I, F;
+    bool takes;
+  } const rows[] = {
+      {true, true, 479, 960, 3, true},     // 14, 18: the Tl479 grid of the aliasing experiment
+      {true, false, 479, 960, 3, true},    // 14, 18
+      {true, true, 64, 1600, 20, true},    // 18, 24
+      {false, false, 64, 400, 8, true},    // 8, 11
+      {false, false, 427, 480, 1, true},   // 9, 13
+      {true, false, 64, 400, 1, true},     // 7, 9
+      {false, true, 641, 1920, 1, false},  // 22, 16
+      {true, true, 641, 1600, 1, false},   // 21, 16
+      {false, true, 641, 1440, 64, true},  // many full groups
+  };
+  for (const auto& r : rows) {
+    const int fc = group_fields(r.dbl, r.analysis, r.I);
+    CHECK(fc >= 1 && fc <= 8, "I %d: %d", r.I, fc);
+    CHECK(group_takes(fc, level(r.J, r.I, r.F), kCu) == r.takes, "dbl %d analysis %d J %d I %d F %d", r.dbl, r.analysis,
+          r.J, r.I, r.F);
+  }
+  CHECK(group_fields(false, true, 256) == 0 && group_fields(true, true, 1000) == 0, "lengths without a group kernel");
+  CHECK(level_shares(false, true, level(129, 200, 3), kCu), "no group kernel");
+  CHECK(level_shares(false, true, level(257, 400, 3), kCu), "few items");
+  CHECK(level_shares(false, true, level(641, 960, 1), kCu), "mostly empty groups");
+  CHECK(!level_shares(false, true, level(1025, 1600, 32), kCu), "many items");
+}
+
 int main() {
   check_widths();
+  check_group_rule();
   check_tune_widths();
   check_tune_key();
   std::printf("rules_check: %d failures\n", g_fail);
