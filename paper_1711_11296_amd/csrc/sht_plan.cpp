@@ -58,7 +58,7 @@ double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, c
   // recurrence of generated P~
   double a;
   if (form == SHT_FORM_FP64)
-    a = analysis ? (gen ? 0.8 : 0.6) : (gen ? 0.7 : 0.8);
+    a = analysis ? (gen ? 0.8 : 0.6) : (gen ? 1.0 : 0.8);
   else if (form == SHT_FORM_FP32)
     a = analysis ? (gen ? 2.5 : 0.4) : (gen ? 2.5 : 1.0);
   else
