@@ -597,50 +597,41 @@ static hipError_t launch_p3(const FftArgs1& a, int maxN, hipStream_t st) {
   constexpr int MSMAX = ((P::I + 1) / 2 + NT - 1) / NT;  // N + 1 <= (I + 1) / 2
   static_assert(MSMAX == 3, "wavenumbers per thread");
   const int nm = maxN + 1;
-  if (nm > 2 * NT) return launch_p3_ms<T, P, NT, FB, FC, 3, ANA>(a, st);
+  if (nm > 2 * NT) {
+    if constexpr (sizeof(T) == 8 && (!ANA || P::I == 2160)) return hipErrorInvalidValue;  // (held_takes: not taken)
+    else return launch_p3_ms<T, P, NT, FB, FC, 3, ANA>(a, st);
+  }
   if (nm > NT) return launch_p3_ms<T, P, NT, FB, FC, 2, ANA>(a, st);
   return launch_p3_ms<T, P, NT, FB, FC, 1, ANA>(a, st);
 }
 
-// Lengths past 2048 whose S and A runs are better held in registers: FP32
-// analysis (64 fields, 1601 rows, group kernels in brackets: I = 2304 398
-// (450), 2560 456 (523), 2880 497 (599), 3072 516 us (657)) and FP64
-// synthesis (2880, 48 fields, 801 rows: 422 (440)).  With 4 fields of a block
-// per item, which is all the LDS holds there, the group kernels' analysis
-// stores 32-byte pieces.  FP64's group kernels (2 fields, 32-byte pieces too)
-// hold their own except where the wavenumbers' regions lie a multiple of
-// 32 KiB apart, Cp a multiple of 64 (64 fields, 1919 rows: 2160 685 (780),
-// 2304 734 (916), 2560 960 (1131), 2880 1172 us (1452); 96 fields, 1201 rows:
-// 2880 1098 (1205); 48 fields, other strides: both 390; 3072, where the runs
-// spill: 1422 (1336)).  Up to three wavenumbers per thread (I <= 3072).
-// FP64 analysis takes the larger radix second: beside the runs a thread then
-// holds 12 values of the last pass, not 15 (2880: 1567 us with radix 15 last,
-// 102 spills); the synthesis, which stores from there, gains nothing.
-template <typename T, bool ANA, int I, int R2, int R3>
-using HeldPlan = std::conditional_t<sizeof(T) == 8 && ANA, Plan3<I, R3, R2>, Plan3<I, R2, R3>>;
-
+// The levels that held_takes gives to the register-held kernels.  FP64
+// analysis takes the larger radix second: beside the runs a thread then holds
+// 12 values of the last pass, not 15 (2880, 64 fields, 1919 rows: 1567 us with
+// radix 15 last, 102 spills; 1172 with 6).  Spills at two / three wavenumbers
+// per thread: FP64 analysis 0..10 / 13..48 registers, the others none.
 template <typename T, int FB, bool ANA>
 static bool launch_held(const FftArgs1& a, int maxN, hipStream_t st, hipError_t* err) {
-  if constexpr (sizeof(T) == 4 && !ANA) {
-    return false;
-  } else {
-    constexpr bool ana64 = sizeof(T) == 8 && ANA;
-    if (ana64 && a.lev[0].Cp % 64 != 0) return false;
+  if (!held_takes(sizeof(T) == 8, ANA, a.lev[0], g_num_cu)) return false;
+  if constexpr (sizeof(T) == 8 && !ANA) {
+    *err = launch_p3<T, FB, ANA, Plan3<2880, 12, 15>>(a, maxN, st);
+    return true;
+  } else if constexpr (ANA) {
+    constexpr bool dbl = sizeof(T) == 8;
     switch (a.lev[0].I) {
-      case 2160: *err = launch_p3<T, FB, ANA, HeldPlan<T, ANA, 2160, 9, 15>>(a, maxN, st); return true;
+      case 2160: *err = launch_p3<T, FB, ANA, Plan3<2160, dbl ? 15 : 9, dbl ? 9 : 15>>(a, maxN, st); return true;
       case 2304: *err = launch_p3<T, FB, ANA, Plan3<2304, 12, 12>>(a, maxN, st); return true;
-      case 2400: *err = launch_p3<T, FB, ANA, HeldPlan<T, ANA, 2400, 10, 15>>(a, maxN, st); return true;
+      case 2400: *err = launch_p3<T, FB, ANA, Plan3<2400, dbl ? 15 : 10, dbl ? 10 : 15>>(a, maxN, st); return true;
       case 2560: *err = launch_p3<T, FB, ANA, Plan3<2560, 16, 10>>(a, maxN, st); return true;
-      case 2880: *err = launch_p3<T, FB, ANA, HeldPlan<T, ANA, 2880, 12, 15>>(a, maxN, st); return true;
+      case 2880: *err = launch_p3<T, FB, ANA, Plan3<2880, dbl ? 15 : 12, dbl ? 12 : 15>>(a, maxN, st); return true;
       case 3072:
-        if constexpr (ana64)
-          return false;
-        else
+        if constexpr (!dbl) {
           *err = launch_p3<T, FB, ANA, Plan3<3072, 16, 12>>(a, maxN, st);
-        return true;
-      default: return false;
+          return true;
+        }
     }
   }
+  return false;
 }
 
 // Single-level plans whose I has a compile-time three-pass plan.
