@@ -58,7 +58,7 @@ double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, c
   // recurrence of generated P~
   double a;
   if (form == SHT_FORM_FP64)
-    a = analysis ? (gen ? 0.8 : 0.6) : (gen ? 1.0 : 0.8);
+    a = analysis ? (gen ? 0.8 : 0.6) : (gen ? 2.0 : 1.25);
   else if (form == SHT_FORM_FP32)
     a = analysis ? (gen ? 2.5 : 0.4) : (gen ? 2.5 : 1.0);
   else
@@ -78,7 +78,9 @@ double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, c
   // with the longest tiles and end with short ones.
   if (analysis && nlev == 1 && (gen || form == SHT_FORM_BF16X6))
     return total / ntiles * std::ceil((double)ntiles / ncu);
-  return total / ncu + (analysis ? 1.0 : 0.5) * longest;
+  // the FP64 synthesis' narrowest tiles are the ones of which two fit a unit
+  const double pair = form == SHT_FORM_FP64 && !analysis && k <= (gen ? 2 : 1) ? (gen ? 0.75 : 0.85) : 1.0;
+  return (total / ncu + (analysis ? 1.0 : 0.5) * longest) * pair;
 }
 
 int default_tile(int form, int nlev, const int* N, const int* J, const int* F, int FB, const int* jst, bool analysis,

@@ -57,7 +57,7 @@ bool width_tiles(int nlev, const long long* Cp, int k);
 // tell apart.  Over the 4500 kernels of the fit the estimate alone took more
 // than 3 % longer than def in 220, the worst 38 % (FP64 with generated P~,
 // N = 213, 48 fields, synthesis: 45.9 us with three blocks, 33.4 with def's
-// two); with the margin in 62, the worst 18 %.
+// two); with the margin in 42, the worst 17 %.
 int choose_tile(int form, bool gen, int nlev, const int* N, const int* J, const int* F, const long long* Cp,
                 const int* jst, bool analysis, int def, int ncu, double* cost);
 

@@ -44,6 +44,8 @@ static void check_widths() {
   } const rows[] = {
       {SHT_FORM_FP64, true, false, 213, 214, 48, 2},    // 33.3, 45.9 with 3
       {SHT_FORM_FP64, true, false, 213, 427, 48, 2},    // 54, 67.5 with 6
+      {SHT_FORM_FP64, true, false, 639, 1279, 48, 6},   // 650, 766 with 3
+      {SHT_FORM_FP64, true, false, 720, 33, 48, 2},     // 125, 173 with 3
       {SHT_FORM_FP32, true, true, 255, 511, 200, 5},    // 147, 203.5 with 7
       {SHT_FORM_FP32, true, true, 426, 853, 200, 5},    // 510, 703.9 with 7
       {SHT_FORM_FP32, false, true, 341, 683, 48, 2},    // 60, 71.9 with 6
