@@ -137,10 +137,19 @@ __device__ __forceinline__ int gen_swz(int row) {
 // the generated block is written after the products (its previous contents
 // were read into registers before the last barrier), read after the next
 // barrier, and a second barrier guards it against the next block's writes.
+// Waves per SIMD the analysis is compiled for.  The FP64 generated kernel with
+// 8 column blocks fills the LDS, one workgroup per compute unit: it takes the
+// registers of two.  The FP32 generated kernels with one and two column blocks
+// are bound by the recurrence's latency: within 80 registers three workgroups
+// share a compute unit instead of two (N = 960, 641 rows, 3 fields 175 -> 161
+// us; N = 1365, 16 fields 412 -> 387 with two blocks, 9 spills and all).
+template <typename T, int NCB, bool GEN>
+constexpr int analysis_wpe() {
+  return sizeof(T) == 8 && GEN && NCB > 4 ? 2 : sizeof(T) == 4 && GEN && NCB <= 2 ? 6 : 4;
+}
+
 template <typename T, int NCB, bool GEN, int NL>
-// (The FP64 generated kernel with 8 column blocks fills the LDS, one
-// workgroup per compute unit: it takes the registers of two waves per SIMD.)
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GEN && NCB > 4 ? 2 : 4))) void k_legendre_analysis(const GemmArgsN<NL> g) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(analysis_wpe<T, NCB, GEN>()))) void k_legendre_analysis(const GemmArgsN<NL> g) {
   typedef typename Acc<T>::type AccT;
   typedef typename V16<T>::type V;
   using S = AnalysisShape<T, NCB, GEN>;
