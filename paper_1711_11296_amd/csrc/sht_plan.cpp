@@ -62,7 +62,7 @@ double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, c
   else if (form == SHT_FORM_FP32)
     a = analysis ? (gen ? 2.5 : 0.4) : (gen ? 2.5 : 1.0);
   else
-    a = analysis ? 5.0 : (gen ? 6.5 : 3.5);
+    a = analysis ? 5.0 : 8.0;
   double total = 0, longest = 0;
   long long ntiles = 0;
   each_tile(form, nlev, N, J, F, jst, analysis, k, [&](int blocks, long long n) {
@@ -80,7 +80,7 @@ double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, c
     return total / ntiles * std::ceil((double)ntiles / ncu);
   // the FP64 synthesis' narrowest tiles are the ones of which two fit a unit
   const double pair = form == SHT_FORM_FP64 && !analysis && k <= (gen ? 2 : 1) ? (gen ? 0.75 : 0.85) : 1.0;
-  return (total / ncu + (analysis ? 1.0 : 0.5) * longest) * pair;
+  return (total / ncu + (analysis || form == SHT_FORM_BF16X6 ? 1.0 : 0.5) * longest) * pair;
 }
 
 int default_tile(int form, int nlev, const int* N, const int* J, const int* F, int FB, const int* jst, bool analysis,
