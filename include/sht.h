@@ -108,8 +108,8 @@ typedef enum {
   SHT_ZONAL_AUTO = 0,        /* per direction: with autotune, whichever of
                                 the two below timed faster at plan time;
                                 without, one launch where the levels allow
-                                it and the one-launch kernel of the form and
-                                direction runs without register spills */
+                                it in FP64 plans of 3 to 8 fields, where it
+                                measured faster */
   SHT_ZONAL_ONE_LAUNCH = 1,  /* one persistent launch over every level's
                                 work items where every level has I = 400,
                                 800 or 1600 or I <= 1024 (else as below) */

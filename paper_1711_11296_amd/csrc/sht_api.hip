@@ -18,6 +18,7 @@
 
 #include "sht_internal.h"
 #include "sht_plan.h"
+#include "sht_zonal_rule.h"
 
 using namespace sht;
 
@@ -217,12 +218,6 @@ int build_plan(int nlev, const int* Nv, const int* Jv, const int* Iv, const int*
   P->otf = o.otf != 0;
   P->zonal = o.zonal;
   P->one_fwd = P->one_inv = o.zonal != SHT_ZONAL_PER_LENGTH;
-  if (o.zonal == SHT_ZONAL_AUTO && nlev > 1) {
-    // without a timing, one launch only where its kernel keeps everything in
-    // registers (the autotuner, if asked for, times both and decides)
-    P->one_fwd = !zonal_one_launch_spills(o.form, true);
-    P->one_inv = !zonal_one_launch_spills(o.form, false);
-  }
   P->nlev = nlev;
   P->elem = o.form == SHT_FORM_FP64 ? 8 : 4;
   int rc = hip_check(hipGetDevice(&P->device), "hipGetDevice");
@@ -243,6 +238,11 @@ int build_plan(int nlev, const int* Nv, const int* Jv, const int* Iv, const int*
   // ---- level descriptors and sizes ----
   Layout Y;
   layout_levels(nlev, Nv, Jv, Iv, Fv, BN, FB, P->lev, &Y);
+  if (o.zonal == SHT_ZONAL_AUTO && nlev > 1) {
+    // without a timing (the autotuner, if asked for, times both and decides)
+    P->one_fwd = one_launch_default(o.form == SHT_FORM_FP64, true, nlev, P->lev, ncu);
+    P->one_inv = one_launch_default(o.form == SHT_FORM_FP64, false, nlev, P->lev, ncu);
+  }
   const long long item = Y.items, goff = Y.grid, soff = Y.spec, woff = Y.ws, moff = Y.nm_total;
   const std::vector<long long>&taboff = Y.taboff, &taboff_syn = Y.taboff_syn, &seedoff = Y.seedoff,
                            &recoff = Y.recoff;

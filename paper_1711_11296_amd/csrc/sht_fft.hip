@@ -825,19 +825,6 @@ static hipError_t launch_zonal_t(bool analysis, const FftArgs& a, int maxN, hipS
   return launch_generic<T>(analysis, a, st);
 }
 
-int zonal_one_launch_spills(int form, bool analysis) {
-  const void* k = nullptr;
-  if (form == SHT_FORM_FP64)
-    k = analysis ? reinterpret_cast<const void*>(ZLevels<double>::kernel<4, true, true>())
-                 : reinterpret_cast<const void*>(ZLevels<double>::kernel<4, false, true>());
-  else
-    k = analysis ? reinterpret_cast<const void*>(ZLevels<float>::kernel<8, true, true>())
-                 : reinterpret_cast<const void*>(ZLevels<float>::kernel<8, false, true>());
-  hipFuncAttributes fa;
-  if (hipFuncGetAttributes(&fa, k) != hipSuccess) return 1;
-  return fa.localSizeBytes > 0 ? 1 : 0;
-}
-
 int launch_zonal(int form, bool analysis, const FftArgs& a, int maxN, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   // the kernels' item width must match every level's analysis column block

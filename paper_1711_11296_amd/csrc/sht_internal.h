@@ -178,9 +178,6 @@ constexpr long long ws_odd(int Jh, long long Cp, long long wblk, int jb) {
 // offsets from a per-wave base: 64 regions must stay below 4 GiB (else the
 // any-length kernels run).
 inline bool zonal_offsets_fit(long long wblk, long long elem) { return 64.0 * (double)wblk * (double)elem < 4294967296.0; }
-// 1 if the one-launch multi-level zonal kernel of this form and direction
-// keeps values in scratch memory (register spills), else 0
-int zonal_one_launch_spills(int form, bool analysis);
 // Lengths 16 R2 R3 of a single level (sht_group.h): -1 where these kernels do
 // not take the level, else a hipError_t; ncu compute units.
 int launch_zonal_group_analysis_f32(const FftArgs1& a, int ncu, void* stream);

@@ -168,6 +168,27 @@ inline bool level_shares(bool dbl, bool analysis, const LevelDesc& L, int ncu) {
   return fc == 0 || !group_takes(fc, L, ncu) || (long long)L.Jh * ((L.F + fc - 1) / fc) < ncu;
 }
 
+// Whether a multi-level plan's zonal stage defaults to one launch over all
+// levels (k_zonal_levels) where they allow it: in FP64 with 3 to 8 fields, at
+// least 1.85 items of 4 fields per compute unit and a level that would share
+// the any-length launch.  One launch / per length in us (cc_poles grids from I
+// = 100 doubling): five levels, 3 fields, synthesis 45 / 58, 5 fields 73 / 83,
+// 8 fields 80 / 89, analysis 37 / 52, 65 / 82, 71 / 92; four levels, 5 fields
+// 30 / 33 and 27 / 34; three levels (0.9 to 1.8 items), 3 fields, synthesis 13
+// / 11; 12 fields, synthesis 128 / 123; FP32 synthesis 1.0 to 2.3 times as
+// long.
+inline bool one_launch_default(bool dbl, bool analysis, int nlev, const LevelDesc* lev, int ncu) {
+  if (!dbl) return false;
+  double items = 0;
+  bool fields = true, share = false;
+  for (int l = 0; l < nlev; ++l) {
+    items += (double)lev[l].Jh * ((lev[l].F + 3) / 4);
+    fields = fields && lev[l].F >= 3 && lev[l].F <= 8;
+    share = share || level_shares(dbl, analysis, lev[l], ncu);
+  }
+  return nlev > 1 && fields && share && items >= 1.85 * ncu;
+}
+
 }  // namespace sht
 
 #endif  // SHT_ZONAL_RULE_H_
