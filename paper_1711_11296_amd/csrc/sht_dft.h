@@ -215,8 +215,6 @@ template <typename T>
 struct Dft<T, 15> : DftCT<T, 5, 3> {};
 template <typename T>
 struct Dft<T, 16> : DftCT<T, 4, 4> {};
-template <typename T>
-struct Dft<T, 20> : DftCT<T, 5, 4> {};
 
 // q = floor(j / d) for 0 <= j < 2^16 and 2 <= d <= 4096, with
 // magic = floor((2^32 - 1) / d) + 1 = ceil(2^32 / d): the excess

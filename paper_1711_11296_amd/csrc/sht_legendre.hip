@@ -92,13 +92,6 @@ __host__ __device__ constexpr int tile_col(int ncb, int c, int i) {
   return 16 * c + i;
 }
 
-// LDS reads that read_cols takes
-template <typename T>
-__host__ __device__ constexpr int col_reads(int ncb) {
-  const int E = 16 / (int)sizeof(T);
-  return ncb / E + ((ncb % E) & 1) + ((ncb % E) >> 1);
-}
-
 // Lane i's values of all column blocks from one LDS row.
 template <typename T, int NCB>
 __device__ __forceinline__ void read_cols(const T* row, int i, T (&b)[NCB]) {
@@ -221,9 +214,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(analysis_wp
 #pragma unroll
   for (int c = 0; c < NCB; ++c) acc[c] = AccT{0, 0, 0, 0};
 
-  // The table operand is fetched two K blocks ahead into two register sets
-  // used in turn (loop unrolled by two); the workspace operand one block
-  // ahead (LDS stages).
+  // Both operands are fetched one K block ahead: the table's into two register
+  // sets used in turn (loop unrolled by two), the workspace's into two LDS
+  // stages.
   V an[2][KQ / E];
   // (issued unconditionally, also by waves without rows in this tile and
   // for blocks past the end, clamped: with straight-line loads the wait
@@ -677,9 +670,13 @@ static hipError_t launch_ncb(bool analysis, const GemmArgsN<NL>& g, hipStream_t 
   const dim3 grid(g.ntiles), block(512);
   if constexpr (sizeof(T) == 8 && NCB > 8) return hipErrorInvalidValue;  // FP64 takes at most 8
   else if (analysis) {
-    const size_t lds = AnalysisShape<T, NCB, GEN>::lds_bytes(GEN);
-    lds_optin<k_legendre_analysis<T, NCB, GEN, NL>>(lds);
-    hipLaunchKernelGGL((k_legendre_analysis<T, NCB, GEN, NL>), grid, block, lds, st, g);
+    // (widths that would spill: tile_spills never lets a plan choose them)
+    if constexpr (sizeof(T) == 4 && GEN && (NCB == 7 || NCB == 9)) return hipErrorInvalidValue;
+    else {
+      const size_t lds = AnalysisShape<T, NCB, GEN>::lds_bytes(GEN);
+      lds_optin<k_legendre_analysis<T, NCB, GEN, NL>>(lds);
+      hipLaunchKernelGGL((k_legendre_analysis<T, NCB, GEN, NL>), grid, block, lds, st, g);
+    }
   } else {
     // wider synthesis tiles do not fit the register file
     if constexpr (NCB > kMaxSynthesisNcb) return hipErrorInvalidValue;
