@@ -1,7 +1,10 @@
 // CPU check of the rules that choose kernels and tile widths (sht_plan.h).
 // Built and run by tests/test_host_rules.py.
+#include <algorithm>
 #include <cstdio>
+#include <map>
 #include <numeric>
+#include <tuple>
 #include <vector>
 
 #include "sht_plan.h"
@@ -218,7 +221,42 @@ static void check_one_launch() {
   }
 }
 
+// Tile lists of the widths that no power of two gives: every (m, row or
+// latitude block, column block) once, nothing else, in both orders, with and
+// without latitudes left out.  (Built with the planner's bounds assertions.)
+static void check_odd_tiles() {
+  struct {
+    int form, N, J, I, F;
+  } const plans[] = {{SHT_FORM_FP64, 130, 261, 300, 21}, {SHT_FORM_FP32, 140, 101, 288, 67},
+                     {SHT_FORM_FP32, 40, 300, 96, 103},  {SHT_FORM_BF16X6, 300, 97, 640, 45}};
+  for (const auto& c : plans)
+    for (int k : {3, 6, 7, 9})
+      for (int part = 0; part < 2; ++part) {
+        LevelDesc lev[SHT_MAX_LEVELS];
+        Layout Y;
+        layout_levels(1, &c.N, &c.J, &c.I, &c.F, 16 * k, zonal_fields_per_block(c.form), lev, &Y);
+        std::vector<int> jst(Y.nm_total, 0);
+        for (int m = 0; part && m < Y.nm_total; ++m) jst[m] = std::min(32 * (m % 5), lev[0].Jh);
+        for (int dir = 0; dir < 2; ++dir)
+          for (int sched = 0; sched < 2 && k <= max_ncb(c.form, dir == 0); ++sched) {
+            std::map<std::tuple<int, int, int>, int> seen;
+            for (const Tile& t : build_tiles(c.form, 1, lev, jst.data(), dir == 0, k, sched))
+              if (t.level >= 0) seen[{t.m, t.rb, t.cb}] += 1;
+            size_t n = 0;
+            const int rows = c.form == SHT_FORM_BF16X6 ? 256 : 128;
+            for (int m = 0; m <= c.N; ++m)
+              for (int cb = 0; 16 * k * cb < 2 * c.F; ++cb)
+                for (int b = dir == 0 ? 0 : jst[m] / 128;
+                     dir == 0 ? b * rows < c.N - m + 1 : b * 128 < lev[0].Jh; ++b, ++n)
+                  CHECK(seen[std::make_tuple(m, b, cb)] == 1, "form %d k %d dir %d m %d block %d column %d", c.form, k,
+                        dir, m, b, cb);
+            CHECK(seen.size() == n, "form %d k %d dir %d", c.form, k, dir);
+          }
+      }
+}
+
 int main() {
+  check_odd_tiles();
   check_widths();
   check_one_launch();
   check_held_rule();

@@ -14,7 +14,7 @@ CSRC = os.path.join(ROOT, "paper_1711_11296_amd", "csrc")
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 def test_rules(tmp_path):
     exe = str(tmp_path / "rules_check")
-    r = subprocess.run(["g++", "-std=c++17", "-O1", "-I" + CSRC, "-I" + os.path.join(ROOT, "include"),
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-DSHT_CHECK", "-I" + CSRC, "-I" + os.path.join(ROOT, "include"),
                         os.path.join(CSRC, "sht_plan.cpp"), os.path.join(CSRC, "sht_host.cpp"),
                         os.path.join(ROOT, "tests", "native", "rules_check.cpp"), "-pthread", "-o", exe],
                        capture_output=True, text=True)
