@@ -78,6 +78,10 @@ double legendre_cost(int form, bool gen, int nlev, const int* N, const int* J, c
   // with the longest tiles and end with short ones.
   if (analysis && nlev == 1 && (gen || form == SHT_FORM_BF16X6))
     return total / ntiles * std::ceil((double)ntiles / ncu);
+  // the FP64 analysis with few tiles: alone on their units they run faster
+  // (three blocks at most; wider ones gain nothing: N = 63, 64 fields, four
+  // blocks 15 % longer than one)
+  if (analysis && nlev == 1 && form == SHT_FORM_FP64 && k <= 3 && ntiles <= ncu) return 1.45 * longest;
   // the FP64 synthesis' narrowest tiles are the ones of which two fit a unit
   const double pair = form == SHT_FORM_FP64 && !analysis && k <= (gen ? 2 : 1) ? (gen ? 0.75 : 0.85) : 1.0;
   return (total / ncu + (analysis || form == SHT_FORM_BF16X6 ? 1.0 : 0.5) * longest) * pair;

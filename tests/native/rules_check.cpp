@@ -55,6 +55,8 @@ static void check_widths() {
       {SHT_FORM_FP32, false, true, 159, 160, 72, 1},    // 14.7, 16.9 with 9
       {SHT_FORM_FP64, false, true, 106, 213, 400, 2},   // 64, 77.5 with 8
       {SHT_FORM_FP64, false, true, 319, 320, 16, 2},    // 26, 31.1 with 1
+      {SHT_FORM_FP64, false, true, 170, 341, 19, 3},    // 17.6, 18.4 with 1
+      {SHT_FORM_FP64, false, true, 63, 127, 64, 2},     // 8.0, 8.7 with 3
       {SHT_FORM_FP64, false, false, 159, 160, 128, 4},  // 37, 44.4 with 2
       {SHT_FORM_FP64, false, false, 341, 342, 32, 4},   // 67, 78.6 with 2
       {SHT_FORM_FP32, false, true, 479, 959, 100, 7},   // 264, 345 with the default's 1
