@@ -8,7 +8,9 @@
 // that short rows fill a workgroup too, and between the passes nothing is
 // held in registers: the fold (or its inverse) reads (writes) the sequences
 // in LDS and stores (loads) 16-byte pieces of the workspace runs directly.
-// Rows move as 16-byte vectors where the row length allows it.  The next
+// Rows move as 16-byte vectors of any length: the last vector of a row starts
+// early enough to end with it (its first values are its neighbour's too), and
+// rows need only be aligned to their elements.  The next
 // item's rows (runs) are fetched into registers while the current item is
 // transformed.
 //
@@ -162,10 +164,12 @@ __device__ __forceinline__ AnyItem any_item(const FftArgsN<NL>& a, int slot) {
   return it;
 }
 
-// The rows of FC fields as vectors of V values: unit x = (field, vector).
+// The rows of FC fields as vectors of V values, aligned like T (the hardware
+// takes such vector accesses): unit x = (field, vector).
 template <typename T, int V>
 struct AnyVec {
-  typedef T type __attribute__((ext_vector_type(V)));
+  typedef T vec __attribute__((ext_vector_type(V)));
+  typedef vec type __attribute__((aligned(sizeof(T))));
 };
 template <typename T>
 struct AnyVec<T, 1> {
@@ -180,7 +184,18 @@ __device__ __forceinline__ T any_get(const typename AnyVec<T, V>::type& v, int e
     return v[e];
 }
 
-// analysis: grid [F][J][I] -> workspace S/A.  VEC: rows as 16-byte vectors;
+// Vectors of a row, and the first value of vector v.
+template <int V>
+__host__ __device__ constexpr int any_nvec(int I) {
+  return (I + V - 1) / V;
+}
+template <int V>
+__device__ __forceinline__ int any_first(int v, int I) {
+  return V == 1 ? v : min(v * V, I - V);
+}
+
+// analysis: grid [F][J][I] -> workspace S/A.  VEC: rows as 16-byte vectors
+// (I at least one vector);
 // VW: fields per workspace piece (2 in FP32 with FC >= 2: 16 bytes).
 // The slots item, item + G, ... below `end` (any levels); returns the first
 // slot past them.  Every thread of the workgroup calls it alike.
@@ -199,7 +214,7 @@ __device__ __forceinline__ int any_analysis_run(const FftArgsN<NL>& a, int item,
   auto load_rows = [&](int slot) __attribute__((always_inline)) {
     const AnyItem it = any_item(a, slot);
     const LevelDesc& L = a.lev[NL == 1 ? 0 : it.l];
-    const int nv = L.I / V, F = L.F - it.fg * FC;  // fields of this group that exist
+    const int nv = any_nvec<V>(L.I), F = L.F - it.fg * FC;  // fields of this group that exist
     const unsigned mv = L.ivm;
     const T* rn = grid0 + L.grid_off + ((long long)it.fg * FC * L.J + it.jp) * L.I;
     const T* rs = grid0 + L.grid_off + ((long long)it.fg * FC * L.J + it.js) * L.I;
@@ -207,7 +222,7 @@ __device__ __forceinline__ int any_analysis_run(const FftArgsN<NL>& a, int item,
 #pragma unroll
     for (int u = 0; u < LU; ++u) {
       const int x = (int)threadIdx.x + u * NT;
-      const int f = nv > 1 ? fastdiv(x, mv) : x, i = (x - f * nv) * V;
+      const int f = nv > 1 ? fastdiv(x, mv) : x, i = any_first<V>(x - f * nv, L.I);
       pn[u] = TV{};
       ps[u] = TV{};
       if (f < FC && f < F) {
@@ -229,12 +244,12 @@ __device__ __forceinline__ int any_analysis_run(const FftArgsN<NL>& a, int item,
       lcur = it.l;
     }
     {
-      const int nv = I / V;
+      const int nv = any_nvec<V>(I);
       const unsigned mv = L.ivm;
 #pragma unroll
       for (int u = 0; u < LU; ++u) {
         const int x = (int)threadIdx.x + u * NT;
-        const int f = nv > 1 ? fastdiv(x, mv) : x, i = (x - f * nv) * V;
+        const int f = nv > 1 ? fastdiv(x, mv) : x, i = any_first<V>(x - f * nv, I);
         if (f < FC) {
           cx<T>* d = buf + f * IP + i;
 #pragma unroll
@@ -373,7 +388,7 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgsN<NL>& a, int item
     any_fft<T, NT>(buf, twl, L, IP, FC);
 
     const T rscale = row_scale<T>(a, L, it.jp);
-    const int nv = I / V, F = L.F - it.fg * FC;
+    const int nv = any_nvec<V>(I), F = L.F - it.fg * FC;
     const unsigned mv = L.ivm;
     T* rn = grid0 + L.grid_off + ((long long)it.fg * FC * L.J + it.jp) * I;
     T* rs = grid0 + L.grid_off + ((long long)it.fg * FC * L.J + it.js) * I;
@@ -381,7 +396,7 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgsN<NL>& a, int item
 #pragma unroll
     for (int u = 0; u < LU; ++u) {
       const int x = (int)threadIdx.x + u * NT;
-      const int f = nv > 1 ? fastdiv(x, mv) : x, i = (x - f * nv) * V;
+      const int f = nv > 1 ? fastdiv(x, mv) : x, i = any_first<V>(x - f * nv, I);
       if (f < FC && f < F) {
         const cx<T>* z = buf + f * IP + i;
         TV n, s;

@@ -718,11 +718,12 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
     } else {
       if (L.I > ZLevels<T>::template CRt<true>::maxi || L.N + 1 > NT) return false;
       k = 3;
-      maxIrt = L.I > maxIrt ? L.I : maxIrt;
+      const int r = any_nvec<16 / (int)sizeof(T)>(L.I) * (16 / (int)sizeof(T));
+      maxIrt = r > maxIrt ? r : maxIrt;
       maxNrt = L.N > maxNrt ? L.N : maxNrt;
       const int ip = any_stride(L), V = 16 / (int)sizeof(T);
       maxIP = ip > maxIP ? ip : maxIP;
-      vec = vec && L.I % V == 0;
+      vec = vec && L.I >= V;
     }
     kinds |= 1 << k;
     b.lev[l].zk = k;
@@ -744,7 +745,7 @@ static bool launch_levels_one(bool analysis, const FftArgs& a, hipStream_t st, h
   for (int l = 0; l < a.nlev; ++l) {
     LevelDesc& L = b.lev[l];
     if (L.zk == 3) {
-      const int nv = vec ? L.I / (16 / (int)sizeof(T)) : L.I;
+      const int nv = vec ? any_nvec<16 / (int)sizeof(T)>(L.I) : L.I;
       L.ivm = nv > 1 ? 0xFFFFFFFFu / (unsigned)nv + 1u : 0u;
       L.nfb = (L.F + (1 << b.lfc) - 1) >> b.lfc;
     }

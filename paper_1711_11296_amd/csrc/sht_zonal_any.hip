@@ -73,9 +73,9 @@ static hipError_t any_shape(bool analysis, bool small, bool vec, const FftArgsN<
 
 template <typename T>
 static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStream_t st) {
-  constexpr int E = AnyCap<T>::E;
+  constexpr int E = AnyCap<T>::E, V = 16 / (int)sizeof(T);
   FftArgs a = a0;
-  int maxI = 0, maxN = 0, maxIP = 0, maxF = 0;
+  int maxI = 0, maxR = 0, maxN = 0, maxIP = 0, maxF = 0;  // maxR: whole vectors
   bool vec = true;
   for (int l = 0; l < a.nlev; ++l) {
     const LevelDesc& L = a.lev[l];
@@ -84,7 +84,9 @@ static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStrea
     maxF = L.F > maxF ? L.F : maxF;
     const int ip = any_stride(L);
     maxIP = ip > maxIP ? ip : maxIP;
-    vec = vec && L.I % (16 / (int)sizeof(T)) == 0;
+    const int r = any_nvec<V>(L.I) * V;
+    maxR = r > maxR ? r : maxR;
+    vec = vec && L.I >= V;
   }
   // fields per item: as many as a workspace run holds, as long as two
   // workgroups share a compute unit's LDS, no group is mostly empty and the
@@ -97,11 +99,11 @@ static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStrea
     return n;
   };
   int lfc = sizeof(T) == 4 ? 3 : 2;
-  while (lfc > 0 && ((1 << lfc) * (long long)maxI > 512LL * E || (1 << lfc) * (maxN + 1LL) > 256LL * E ||
+  while (lfc > 0 && ((1 << lfc) * (long long)maxR > 512LL * E || (1 << lfc) * (maxN + 1LL) > 256LL * E ||
                      lds_of(1 << lfc) > kAnyMaxLds / 2 || (1 << (lfc - 1)) >= maxF || items_of(1 << lfc) < ncu))
     --lfc;
   const int fc = 1 << lfc;
-  const bool small = fc * (long long)maxI <= 256LL * E && fc * (maxN + 1LL) <= 128LL * E;
+  const bool small = fc * (long long)maxR <= 256LL * E && fc * (maxN + 1LL) <= 128LL * E;
   a.lfc = lfc;
   a.tw_lds = (fc * maxIP + 1) & ~1;
   const size_t lds = ((size_t)a.tw_lds + maxI) * sizeof(cx<T>);
@@ -109,7 +111,7 @@ static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStrea
   long long items = 0;
   for (int l = 0; l < a.nlev; ++l) {
     LevelDesc& L = a.lev[l];
-    const int nv = vec ? L.I / (16 / (int)sizeof(T)) : L.I;
+    const int nv = vec ? any_nvec<V>(L.I) : L.I;
     L.ivm = nv > 1 ? 0xFFFFFFFFu / (unsigned)nv + 1u : 0u;
     L.nfb = (L.F + fc - 1) / fc;
     L.fft_item0 = (int)items;
