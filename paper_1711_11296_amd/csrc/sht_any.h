@@ -37,28 +37,21 @@
 
 #include "sht_dft.h"
 #include "sht_internal.h"
+#include "sht_zonal_rule.h"
 
 namespace sht {
 
-// Complex values per thread: FC I <= NT E and FC (N + 1) <= NT E / 2.
-// (FP32: a pass then holds at most 20 complex values and the prefetch 24
-// floats, compiled for 4 waves per SIMD; FP64 takes the registers of 2.  Of
-// the single-level FP32 kernels the analysis of whole 16-byte vectors fits;
-// the synthesis spills 14 registers with groups of 2 fields or more and 47
-// with single fields, and with scalar rows the analysis 30 and the synthesis
-// 67 or 99.  No FP64 kernel spills.)
+// Complex values per thread.  (FP32: a pass then holds at most 20 complex
+// values and the prefetch 24 floats, compiled for 4 waves per SIMD; FP64 takes
+// the registers of 2.  With
+// rows in vectors the single-level FP32 synthesis spills 10 registers with
+// groups of 2 fields or more and 44 with single fields, the analysis none;
+// with scalar rows, which only lengths below a vector take, 30 to 99.  The
+// several-level and the FP64 kernels spill none.)
 template <typename T>
 struct AnyCap {
-  static constexpr int E = sizeof(T) == 4 ? 12 : 8;
+  static constexpr int E = any_values(sizeof(T));
 };
-
-// Field stride in LDS: room for the padded first pass; 2 mod 16, so that
-// the fold's lanes (adjacent wavenumbers of several fields) spread over the
-// banks.
-__host__ __device__ inline int any_stride(const LevelDesc& L) {
-  const int pad = L.nrad > 1 && L.rad[0] % 2 == 0 ? L.I / L.rad[0] : 0;
-  return ((L.I + pad + 15) & ~15) + 2;
-}
 
 template <typename T, int NT, int R>
 __device__ __forceinline__ void any_pass(cx<T>* buf, const cx<T>* tw, int IP, int nfc, int p, int nb, int Ns,
@@ -182,16 +175,6 @@ __device__ __forceinline__ T any_get(const typename AnyVec<T, V>::type& v, int e
     return v;
   else
     return v[e];
-}
-
-// Vectors of a row, and the first value of vector v.
-template <int V>
-__host__ __device__ constexpr int any_nvec(int I) {
-  return (I + V - 1) / V;
-}
-template <int V>
-__device__ __forceinline__ int any_first(int v, int I) {
-  return V == 1 ? v : min(v * V, I - V);
 }
 
 // analysis: grid [F][J][I] -> workspace S/A.  VEC: rows as 16-byte vectors

@@ -30,8 +30,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(any_wpe<T>()
 // ---------------------------------------------------------------------------
 // launcher
 // ---------------------------------------------------------------------------
-constexpr size_t kAnyMaxLds = 160 * 1024;
-
 template <auto Kernel, class A>
 static hipError_t any_go(const A& a, int NT, int wpe, size_t lds, int ncu, hipStream_t st) {
   static size_t done = 0;
@@ -55,8 +53,9 @@ static hipError_t any_dir(bool analysis, const FftArgsN<NL>& a, size_t lds, int 
                   : any_go<k_zonal_any_synthesis<T, NT, VEC, VW, NL>>(a, NT, any_wpe<T>(), lds, ncu, st);
 }
 
+// NT: threads of an item
 template <typename T, int NL>
-static hipError_t any_shape(bool analysis, bool small, bool vec, const FftArgsN<NL>& a, size_t lds, int ncu,
+static hipError_t any_shape(bool analysis, int NT, bool vec, const FftArgsN<NL>& a, size_t lds, int ncu,
                             hipStream_t st) {
   auto go = [&](auto nt, auto vw) {
     constexpr int NT = decltype(nt)::value, VW = decltype(vw)::value;
@@ -67,51 +66,26 @@ static hipError_t any_shape(bool analysis, bool small, bool vec, const FftArgsN<
   using N512 = std::integral_constant<int, 512>;
   using One = std::integral_constant<int, 1>;
   using VWT = std::integral_constant<int, sizeof(T) == 4 ? 2 : 1>;
-  if (a.lfc == 0) return small ? go(N256{}, One{}) : go(N512{}, One{});
-  return small ? go(N256{}, VWT{}) : go(N512{}, VWT{});
+  if constexpr (sizeof(T) == 4) {
+    if (NT == 1024) return any_dir<T, 1024, true, 2>(analysis, a, lds, ncu, st);
+  }
+  if (a.lfc == 0) return NT == 256 ? go(N256{}, One{}) : go(N512{}, One{});
+  return NT == 256 ? go(N256{}, VWT{}) : go(N512{}, VWT{});
 }
 
 template <typename T>
 static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStream_t st) {
-  constexpr int E = AnyCap<T>::E, V = 16 / (int)sizeof(T);
+  constexpr int V = 16 / (int)sizeof(T);
   FftArgs a = a0;
-  int maxI = 0, maxR = 0, maxN = 0, maxIP = 0, maxF = 0;  // maxR: whole vectors
-  bool vec = true;
-  for (int l = 0; l < a.nlev; ++l) {
-    const LevelDesc& L = a.lev[l];
-    maxI = L.I > maxI ? L.I : maxI;
-    maxN = L.N > maxN ? L.N : maxN;
-    maxF = L.F > maxF ? L.F : maxF;
-    const int ip = any_stride(L);
-    maxIP = ip > maxIP ? ip : maxIP;
-    const int r = any_nvec<V>(L.I) * V;
-    maxR = r > maxR ? r : maxR;
-    vec = vec && L.I >= V;
-  }
-  // fields per item: as many as a workspace run holds, as long as two
-  // workgroups share a compute unit's LDS, no group is mostly empty and the
-  // device has an item per compute unit (T85 with 7 fields: 28 us a pair with
-  // two per unit, one field each, 24 with one)
-  auto lds_of = [&](int fc) { return (size_t)((size_t)fc * maxIP + maxI) * sizeof(cx<T>); };
-  auto items_of = [&](int fc) {
-    long long n = 0;
-    for (int l = 0; l < a.nlev; ++l) n += (long long)a.lev[l].Jh * ((a.lev[l].F + fc - 1) / fc);
-    return n;
-  };
-  int lfc = sizeof(T) == 4 ? 3 : 2;
-  while (lfc > 0 && ((1 << lfc) * (long long)maxR > 512LL * E || (1 << lfc) * (maxN + 1LL) > 256LL * E ||
-                     lds_of(1 << lfc) > kAnyMaxLds / 2 || (1 << (lfc - 1)) >= maxF || items_of(1 << lfc) < ncu))
-    --lfc;
-  const int fc = 1 << lfc;
-  const bool small = fc * (long long)maxR <= 256LL * E && fc * (maxN + 1LL) <= 128LL * E;
-  a.lfc = lfc;
-  a.tw_lds = (fc * maxIP + 1) & ~1;
-  const size_t lds = ((size_t)a.tw_lds + maxI) * sizeof(cx<T>);
-  if (lds > kAnyMaxLds) return hipErrorInvalidValue;
+  const AnyShape s = any_choice(sizeof(T), a.nlev, a.lev, ncu);
+  const int fc = 1 << s.lfc;
+  a.lfc = s.lfc;
+  a.tw_lds = s.tw_lds;
+  if (s.lds > kAnyMaxLds) return hipErrorInvalidValue;
   long long items = 0;
   for (int l = 0; l < a.nlev; ++l) {
     LevelDesc& L = a.lev[l];
-    const int nv = vec ? any_nvec<V>(L.I) : L.I;
+    const int nv = s.vec ? any_nvec<V>(L.I) : L.I;
     L.ivm = nv > 1 ? 0xFFFFFFFFu / (unsigned)nv + 1u : 0u;
     L.nfb = (L.F + fc - 1) / fc;
     L.fft_item0 = (int)items;
@@ -119,8 +93,8 @@ static hipError_t any_launch(bool analysis, const FftArgs& a0, int ncu, hipStrea
   }
   if (items > 0x7fffffff) return hipErrorInvalidValue;
   a.nitems = (int)items;
-  return a.nlev == 1 ? any_shape<T>(analysis, small, vec, one_level(a), lds, ncu, st)
-                     : any_shape<T>(analysis, small, vec, a, lds, ncu, st);
+  return a.nlev == 1 ? any_shape<T>(analysis, s.nt, s.vec, one_level(a), s.lds, ncu, st)
+                     : any_shape<T>(analysis, s.nt, s.vec, a, s.lds, ncu, st);
 }
 
 int launch_zonal_any(bool dbl, bool analysis, const FftArgs& a, int ncu, void* stream) {

@@ -1,5 +1,6 @@
 // Which zonal kernel a level takes: the lengths, shapes and choices of the
-// group kernels (sht_group.h) and the register-held ones (sht_fft.hip).
+// group kernels (sht_group.h), the any-length ones (sht_any.h) and the
+// register-held ones (sht_fft.hip).
 // Plain C++ (no HIP), so that the rules are checked on the CPU too.
 #ifndef SHT_ZONAL_RULE_H_
 #define SHT_ZONAL_RULE_H_
@@ -103,6 +104,78 @@ inline int group_fields(bool dbl, bool analysis, int I) {
 #undef SHT_GROUP_FIELDS
     default: return 0;
   }
+}
+
+// The any-length kernels (sht_any.h): complex values per thread, so that
+// FC I <= NT E (I in whole vectors) and FC (N + 1) <= NT E / 2; the LDS of a
+// workgroup.
+constexpr int any_values(size_t value_size) { return value_size == 4 ? 12 : 8; }
+constexpr size_t kAnyMaxLds = 160 * 1024;
+
+// Field stride in LDS: room for the padded first pass; 2 mod 16, so that
+// the fold's lanes (adjacent wavenumbers of several fields) spread over the
+// banks.
+constexpr int any_stride(const LevelDesc& L) {
+  const int pad = L.nrad > 1 && L.rad[0] % 2 == 0 ? L.I / L.rad[0] : 0;
+  return ((L.I + pad + 15) & ~15) + 2;
+}
+
+// Vectors of a row, and the first value of vector v.
+template <int V>
+constexpr int any_nvec(int I) {
+  return (I + V - 1) / V;
+}
+template <int V>
+constexpr int any_first(int v, int I) {
+  return V == 1 || v * V < I - V ? v * V : I - V;
+}
+
+struct AnyShape {
+  int lfc, nt;  // log2 of the fields per item, threads per item
+  bool vec;     // rows as 16-byte vectors
+  int tw_lds;   // LDS offset of the twiddles, complex values
+  size_t lds;   // bytes
+};
+
+inline AnyShape any_choice(size_t value_size, int nlev, const LevelDesc* lev, int ncu) {
+  const int E = any_values(value_size), V = 16 / (int)value_size;
+  int maxI = 0, maxR = 0, maxN = 0, maxIP = 0, maxF = 0;  // maxR: whole vectors
+  bool vec = true;
+  for (int l = 0; l < nlev; ++l) {
+    const LevelDesc& L = lev[l];
+    maxI = L.I > maxI ? L.I : maxI;
+    maxN = L.N > maxN ? L.N : maxN;
+    maxF = L.F > maxF ? L.F : maxF;
+    const int ip = any_stride(L);
+    maxIP = ip > maxIP ? ip : maxIP;
+    const int r = (L.I + V - 1) / V * V;
+    maxR = r > maxR ? r : maxR;
+    vec = vec && L.I >= V;
+  }
+  // fields per item: as many as a workspace run holds, as long as two
+  // workgroups share a compute unit's LDS, no group is mostly empty and the
+  // device has an item per compute unit (T85 with 7 fields: 28 us a pair with
+  // two per unit, one field each, 24 with one)
+  auto tw_of = [&](int fc) { return (fc * maxIP + 1) & ~1; };
+  auto lds_of = [&](int fc) { return ((size_t)tw_of(fc) + maxI) * 2 * value_size; };
+  auto items_of = [&](int fc) {
+    long long n = 0;
+    for (int l = 0; l < nlev; ++l) n += (long long)lev[l].Jh * ((lev[l].F + fc - 1) / fc);
+    return n;
+  };
+  auto holds = [&](int fc, long long nt) { return fc * (long long)maxR <= nt * E && fc * (maxN + 1LL) <= nt / 2 * E; };
+  int lfc = value_size == 4 ? 3 : 2;
+  while (lfc > 0 && (!holds(1 << lfc, 512) || lds_of(1 << lfc) > kAnyMaxLds / 2 || (1 << (lfc - 1)) >= maxF ||
+                     items_of(1 << lfc) < ncu))
+    --lfc;
+  // FP32 rows of which 512 threads hold one field: 1024 threads hold two, whose
+  // workspace pieces are 16 bytes instead of 8 (641 rows, 64 fields, analysis /
+  // synthesis: 3200 439 / 502 -> 356 / 405 us, 4000 587 / 609 -> 441 / 533)
+  const bool two = value_size == 4 && lfc == 0 && vec && maxR > 3072 && maxF >= 2 && items_of(2) >= ncu &&
+                   lds_of(2) <= kAnyMaxLds;
+  if (two) lfc = 1;
+  const int fc = 1 << lfc;
+  return {lfc, two ? 1024 : holds(fc, 256) ? 256 : 512, vec, tw_of(fc), lds_of(fc)};
 }
 
 // Whether a length's group kernel (fc fields per item) takes a level rather

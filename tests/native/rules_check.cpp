@@ -257,7 +257,63 @@ static void check_odd_tiles() {
       }
 }
 
+// The any-length kernels' shapes: what an item holds fits its threads and the
+// LDS, and the vectors of a row cover it and stay in it, for every length that
+// a plan takes and the largest wavenumber it may have.
+static void check_any_shapes() {
+  for (size_t size : {4, 8}) {
+    const int E = any_values(size), V = 16 / (int)size;
+    for (int I = 1; I <= 4096; ++I) {
+      int rad[SHT_MAX_RADICES], nrad = 0;
+      if (!factor_radices(I, rad, &nrad)) continue;
+      for (int F : {1, 2, 3, 64})
+        for (int J : {3, 641}) {
+          LevelDesc L = level(J, I, F);
+          L.N = (I - 1) / 2;
+          L.nrad = nrad;
+          std::copy(rad, rad + nrad, L.rad);
+          if (((size_t)any_stride(L) + 1 + I) * 2 * size > kAnyMaxLds || I > 512 * E) continue;
+          const AnyShape s = any_choice(size, 1, &L, kCu);
+          const long long fc = 1 << s.lfc, rows = s.vec ? (I + V - 1) / V * V : I;
+          CHECK(s.nt == 256 || s.nt == 512 || (s.nt == 1024 && size == 4 && s.lfc == 1 && s.vec),
+                "%zu I %d F %d: %d threads", size, I, F, s.nt);
+          CHECK(fc * rows <= (long long)s.nt * E && 2 * fc * (L.N + 1) <= (long long)s.nt * E &&
+                    fc * any_stride(L) <= s.tw_lds && s.lds <= kAnyMaxLds &&
+                    (s.tw_lds + (size_t)I) * 2 * size <= s.lds,
+                "%zu I %d F %d J %d: %lld fields, %d threads, %zu bytes", size, I, F, J, fc, s.nt, s.lds);
+          CHECK(s.vec == (I >= V), "%zu I %d", size, I);
+        }
+    }
+    for (int I = V; I < 700; ++I) {
+      std::vector<int> seen(I, 0);
+      const int nv = size == 4 ? any_nvec<4>(I) : any_nvec<2>(I);
+      for (int v = 0; v < nv; ++v) {
+        const int i = size == 4 ? any_first<4>(v, I) : any_first<2>(v, I);
+        CHECK(i >= 0 && i + V <= I, "%zu I %d vector %d", size, I, v);
+        for (int e = 0; e < V; ++e) seen.at(i + e) += 1;
+      }
+      CHECK(*std::min_element(seen.begin(), seen.end()) >= 1, "%zu I %d", size, I);
+    }
+  }
+  struct {
+    size_t size;
+    int I, F, fields, threads;
+  } const rows[] = {
+      {4, 625, 64, 8, 512},   // odd rows in vectors too
+      {4, 3375, 64, 2, 1024}, {4, 3375, 1, 1, 512}, {4, 3000, 64, 2, 512},
+      {8, 1080, 64, 2, 512},
+  };
+  for (const auto& r : rows) {
+    LevelDesc L = level(641, r.I, r.F);
+    CHECK(factor_radices(r.I, L.rad, &L.nrad), "%d", r.I);
+    const AnyShape s = any_choice(r.size, 1, &L, kCu);
+    CHECK(1 << s.lfc == r.fields && s.nt == r.threads && s.vec, "%zu I %d F %d: %d fields, %d threads", r.size, r.I,
+          r.F, 1 << s.lfc, s.nt);
+  }
+}
+
 int main() {
+  check_any_shapes();
   check_odd_tiles();
   check_widths();
   check_one_launch();

@@ -1,0 +1,58 @@
+"""Any-length zonal kernels with items for every compute unit: the long FP32
+rows of which a workgroup of 1024 threads holds two fields (odd lengths, whose
+vectors overlap at the row's end, an odd field count, a full spectrum, and
+several levels of different lengths in one launch).  Oracle on the first and last field; bounds as for every
+parity test."""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O
+from paper_1711_11296_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-12, "fp32": 1e-6}
+
+
+def _rel(x, ref):
+    return np.linalg.norm(x - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("form,I,N,J,F", [
+    ("fp32", 3125, 60, 129, 9), ("fp32", 3375, 200, 515, 2), ("fp32", 4050, 500, 65, 17), ("fp32", 3645, 40, 515, 3)])
+def test_many_items(form, I, N, J, F):
+    from paper_1711_11296_amd import Plan
+    dt = torch.float64 if form == "fp64" else torch.float32
+    p = Plan(N, J, I, F, grid="fejer2", form=form)
+    pick = [0, F - 1]
+    g = torch.from_numpy(inputs.random_grid(F, J, I, seed=I)).to("cuda:0", dt)
+    a = torch.from_numpy(inputs.random_spectra(N, F, seed=I + 1, profile="white")).to("cuda:0", dt)
+    s, x = p.forward(g), p.inverse(a)
+    torch.cuda.synchronize()
+    gh, ah = g[pick].double().cpu().numpy(), a[pick].double().cpu().numpy()
+    assert _rel(s[pick].double().cpu().numpy(), O.forward(gh, N, "fejer2")) < TOL[form]
+    assert _rel(x[pick].double().cpu().numpy(), O.inverse(ah, N, J, I, "fejer2")) < TOL[form]
+    p.close()
+
+
+def test_levels_share_the_launch():
+    """Rows of 3125, 250, 45 and 3375 values in one launch of 1024 threads: items of
+    two fields, far from full where the row is short."""
+    from paper_1711_11296_amd import Plan
+    levels = [(60, 129, 3125, 7), (80, 129, 250, 5), (20, 33, 45, 2), (200, 129, 3375, 1)]
+    p = Plan(levels=levels, grid="cc_poles", form="fp32", zonal="per_length")
+    specs = [inputs.random_spectra(N, F, seed=I, profile="inv1") for N, J, I, F in levels]
+    a = torch.from_numpy(np.concatenate([s.ravel() for s in specs])).to("cuda:0", torch.float32)
+    g = p.inverse(a)
+    s = p.forward(g)
+    torch.cuda.synchronize()
+    gh, sh, go, so = g.double().cpu().numpy().ravel(), s.double().cpu().numpy().ravel(), 0, 0
+    for (N, J, I, F), spec in zip(levels, specs):
+        gl, sl = gh[go:go + F * J * I].reshape(F, J, I), sh[so:so + spec.size].reshape(spec.shape)
+        go, so = go + F * J * I, so + spec.size
+        assert _rel(gl, O.inverse(spec, N, J, I, "cc_poles")) < TOL["fp32"], I
+        assert _rel(sl, O.forward(gl, N, "cc_poles")) < TOL["fp32"], I
+    p.close()
