@@ -168,6 +168,11 @@ inline AnyShape any_choice(size_t value_size, int nlev, const LevelDesc* lev, in
   while (lfc > 0 && (!holds(1 << lfc, 512) || lds_of(1 << lfc) > kAnyMaxLds / 2 || (1 << (lfc - 1)) >= maxF ||
                      items_of(1 << lfc) < ncu))
     --lfc;
+  // FP64 at 512 to 1024: groups that 256 threads hold, so that two workgroups
+  // share a compute unit (641 rows, 64 fields, analysis / synthesis: 625 101 /
+  // 95 -> 87 / 84 us, 810 152 / 131 -> 138 / 130; longer rows lose up to 12 %)
+  if (value_size == 8 && maxR > 512 && maxR <= 1024)
+    while (lfc > 0 && !holds(1 << lfc, 256)) --lfc;
   // FP32 rows of which 512 threads hold one field: 1024 threads hold two, whose
   // workspace pieces are 16 bytes instead of 8 (641 rows, 64 fields, analysis /
   // synthesis: 3200 439 / 502 -> 356 / 405 us, 4000 587 / 609 -> 441 / 533)

@@ -301,7 +301,7 @@ static void check_any_shapes() {
   } const rows[] = {
       {4, 625, 64, 8, 512},   // odd rows in vectors too
       {4, 3375, 64, 2, 1024}, {4, 3375, 1, 1, 512}, {4, 3000, 64, 2, 512},
-      {8, 1080, 64, 2, 512},
+      {8, 625, 64, 2, 256},   {8, 810, 64, 2, 256}, {8, 1080, 64, 2, 512},
   };
   for (const auto& r : rows) {
     LevelDesc L = level(641, r.I, r.F);

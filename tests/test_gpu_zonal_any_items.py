@@ -1,7 +1,8 @@
 """Any-length zonal kernels with items for every compute unit: the long FP32
 rows of which a workgroup of 1024 threads holds two fields (odd lengths, whose
 vectors overlap at the row's end, an odd field count, a full spectrum, and
-several levels of different lengths in one launch).  Oracle on the first and last field; bounds as for every
+several levels of different lengths in one launch), and the FP64 groups that
+256 threads hold.  Oracle on the first and last field; bounds as for every
 parity test."""
 
 import numpy as np
@@ -22,7 +23,8 @@ def _rel(x, ref):
 
 
 @pytest.mark.parametrize("form,I,N,J,F", [
-    ("fp32", 3125, 60, 129, 9), ("fp32", 3375, 200, 515, 2), ("fp32", 4050, 500, 65, 17), ("fp32", 3645, 40, 515, 3)])
+    ("fp32", 3125, 60, 129, 9), ("fp32", 3375, 200, 515, 2), ("fp32", 4050, 500, 65, 17), ("fp32", 3645, 40, 515, 3),
+    ("fp64", 625, 312, 257, 5), ("fp64", 729, 100, 171, 7), ("fp64", 1000, 499, 129, 9)])
 def test_many_items(form, I, N, J, F):
     from paper_1711_11296_amd import Plan
     dt = torch.float64 if form == "fp64" else torch.float32
