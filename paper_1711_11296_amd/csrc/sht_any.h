@@ -44,9 +44,9 @@ namespace sht {
 // Complex values per thread.  (FP32: a pass then holds at most 20 complex
 // values and the prefetch 24 floats, compiled for 4 waves per SIMD; FP64 takes
 // the registers of 2.  With
-// rows in vectors the single-level FP32 synthesis spills 10 registers with
-// groups of 2 fields or more and 44 with single fields, the analysis none;
-// with scalar rows, which only lengths below a vector take, 30 to 99.  The
+// rows in vectors the single-level FP32 synthesis spills 8 registers with
+// groups of 2 fields or more and 37 with single fields, the analysis none;
+// with scalar rows, which only lengths below a vector take, 30 to 97.  The
 // several-level and the FP64 kernels spill none.)
 template <typename T>
 struct AnyCap {
@@ -308,6 +308,16 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgsN<NL>& a, int item
   const int lfc = a.lfc, FC = 1 << lfc;
 
   TW pS[UM], pA[UM];
+  // rows below the first 128-latitude tile the Legendre synthesis computes for
+  // a wavenumber (reduced transform) are zero; with one level a thread's
+  // wavenumbers are the same in every item
+  int lim[UM];
+  if constexpr (NL == 1)
+#pragma unroll
+    for (int u = 0; u < UM; ++u) {
+      const int m = ((int)threadIdx.x + u * NT) >> (lfc - LVW);
+      lim[u] = m > a.lev[0].N ? 0x7fffffff : a.jstart ? a.jstart[a.lev[0].m_base + m] & ~127 : 0;
+    }
   auto load_ws = [&](int slot) __attribute__((always_inline)) {
     const AnyItem it = any_item(a, slot);
     const LevelDesc& L = a.lev[NL == 1 ? 0 : it.l];
@@ -320,9 +330,8 @@ __device__ __forceinline__ int any_synthesis_run(const FftArgsN<NL>& a, int item
       const int m = x >> (lfc - LVW), f0 = (x - (m << (lfc - LVW))) * VW;
       pS[u] = TW{};
       pA[u] = TW{};
-      // rows below the first 128-latitude tile the Legendre synthesis
-      // computes for this m (reduced transform) are zero
-      if (m <= L.N && it.fg * FC + f0 < L.F && (!a.jstart || it.jp >= (a.jstart[L.m_base + m] & ~127))) {
+      if (NL == 1 ? it.jp >= lim[u] && it.fg * FC + f0 < L.F
+                  : m <= L.N && it.fg * FC + f0 < L.F && (!a.jstart || it.jp >= (a.jstart[L.m_base + m] & ~127))) {
         const T* s = ws + m * region + 2 * f0;
         pS[u] = *reinterpret_cast<const TW*>(s);
         pA[u] = *reinterpret_cast<const TW*>(s + odd);

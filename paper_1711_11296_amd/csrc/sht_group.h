@@ -258,6 +258,21 @@ struct Grp {
     const long long plane2 = L.wblk;
     const unsigned step = (unsigned)(plane2 * (long long)sizeof(T));
     TW pS[UM], pA[UM];
+    // rows below the first 128-latitude tile the Legendre synthesis computes
+    // for a wavenumber (reduced transform) are zero; a thread's wavenumbers are
+    // the same in every item, and read per item the limits precede the runs in
+    // a chain of two loads (T959 FP32 reduced 690 -> 635 us).  The kernels whose
+    // registers are full without them read them per item all the same (I = 1600
+    // FP32, 641 rows, 64 fields, full transform: held 148 us, per item 124; the
+    // one launch over several levels 4-12 % longer)
+    constexpr bool LIM = NL == 1 && !(sizeof(T) == 4 && (I == 1600 || I == 3600));
+    int lim[UM];
+    if constexpr (LIM)
+#pragma unroll
+      for (int u = 0; u < UM; ++u) {
+        const int m = ((int)threadIdx.x + u * NT) / LV;
+        lim[u] = m > N ? 0x7fffffff : a.jstart ? a.jstart[L.m_base + m] & ~127 : 0;
+      }
     auto load_ws = [&](int slot) __attribute__((always_inline)) {
       const int itm = xcd_map(slot - s0, n);
       const int jp = itm / nfg, fg = itm - jp * nfg;
@@ -273,9 +288,8 @@ struct Grp {
         const int mw = __builtin_amdgcn_readfirstlane(m);
         const char* wb = reinterpret_cast<const char*>(w + mw * plane2);
         const unsigned lo = (unsigned)(m - mw) * step + (unsigned)(2 * f0 * sizeof(T));
-        // rows below the first 128-latitude tile the Legendre synthesis
-        // computes for this m (reduced transform) are zero
-        if (m <= N && fg * FC + f0 < F && (!a.jstart || jp >= (a.jstart[L.m_base + m] & ~127))) {
+        if (LIM ? jp >= lim[u] && fg * FC + f0 < F
+                : m <= N && fg * FC + f0 < F && (!a.jstart || jp >= (a.jstart[L.m_base + m] & ~127))) {
           pS[u] = *reinterpret_cast<const TW*>(wb + lo);
           pA[u] = *reinterpret_cast<const TW*>(wb + odd + lo);
         }

@@ -58,3 +58,25 @@ def test_levels_share_the_launch():
         assert _rel(gl, O.inverse(spec, N, J, I, "cc_poles")) < TOL["fp32"], I
         assert _rel(sl, O.forward(gl, N, "cc_poles")) < TOL["fp32"], I
     p.close()
+
+
+@pytest.mark.parametrize("form,I,N,J,F", [
+    ("fp32", 1000, 333, 801, 5), ("fp64", 1250, 300, 801, 3), ("fp32", 3375, 250, 771, 2), ("fp32", 1600, 400, 801, 6),
+    ("fp64", 1440, 350, 801, 5), ("fp32", 2048, 300, 771, 9)])
+def test_reduced(form, I, N, J, F):
+    """Latitudes left out per wavenumber: the synthesis of any-length and group
+    kernels takes them as zero, over several items of a workgroup (the
+    analysis fills the workspace before, so that a run read where the Legendre
+    synthesis wrote none shows)."""
+    from paper_1711_11296_amd import Plan
+    dt = torch.float64 if form == "fp64" else torch.float32
+    a = torch.from_numpy(inputs.random_spectra(N, F, seed=I + 1, profile="white")).to("cuda:0", dt)
+    p = Plan(N, J, I, F, grid="cc_poles", form=form, reduced=True)
+    assert p.legendre_flops_kept < p.legendre_flops
+    p.forward(torch.full((F, J, I), 1e3, dtype=dt, device="cuda:0"))
+    x = p.inverse(a)
+    torch.cuda.synchronize()
+    pick = [0, F - 1]
+    ref = O.inverse(a[pick].double().cpu().numpy(), N, J, I, "cc_poles")
+    assert _rel(x[pick].double().cpu().numpy(), ref) < TOL[form]
+    p.close()
