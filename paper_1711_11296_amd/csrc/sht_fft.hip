@@ -18,9 +18,9 @@
 //   x(lambda_i) = Re X^0 + 2 sum_{m>=1} Re(X^m e^{i m lambda_i}).
 //
 // Three families of kernels: sht_group.h (lengths 16 R2 R3 known at compile
-// time), sht_any.h (any length), and here the ones that hold their runs in
-// registers, which some lengths past 2048 use (launch_held),
-// with the choice of kernel and the multi-level launches.
+// time), sht_any.h (any length), and here the analysis kernels that hold their
+// runs in registers, which some lengths past 2048 use (launch_held), with the
+// choice of kernel and the multi-level launches.
 //
 // Work decomposition of the kernels here: one workgroup per (mirror row
 // pair, block of FB fields).  The FB fields go through the LDS buffer one after the other and
@@ -43,27 +43,6 @@
 #include "sht_group.h"
 
 namespace sht {
-
-// Store/load FB complex values (2*FB scalars, 64 bytes) starting at a
-// 64-byte aligned address, as 16-byte vector accesses.
-template <typename T, int FB>
-__device__ __forceinline__ void load_run(const T* src, cx<T> (&v)[FB]) {
-  typedef typename Vec16<T>::type V;
-  constexpr int E = 16 / sizeof(T);
-  const V* s = reinterpret_cast<const V*>(src);
-#pragma unroll
-  for (int k = 0; k < 2 * FB / E; ++k) {
-    const V o = s[k];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int q = k * E + e;
-      if (q & 1)
-        v[q >> 1].y = o[e];
-      else
-        v[q >> 1].x = o[e];
-    }
-  }
-}
 
 // The workspace run of one (wavenumber, parity, latitude pair, field block)
 // is 2 FB values = 64 bytes, and the thread of wavenumber m holds the whole
@@ -136,9 +115,8 @@ __device__ __forceinline__ void store_runs_quad(T* base, long long region, int m
 // ---------------------------------------------------------------------------
 // Fixed-length transforms: I = 16 R2 R3 in three passes with compile-time
 // radices, twiddle strides and index arithmetic (Plan3; the passes are those
-// of sht_group.h with a field stride of IP).  Analysis loads the grid rows
-// straight into the registers of the first pass; synthesis stores the last
-// pass straight to the grid rows.
+// of sht_group.h with a field stride of IP).  The grid rows are loaded
+// straight into the registers of the first pass.
 // ---------------------------------------------------------------------------
 template <typename T, class P, int NT, int FC>
 struct Fft3 {
@@ -176,24 +154,6 @@ struct Fft3 {
         for (int t = 0; t < 16; ++t) d[t] = v[s][t];
       }
     }
-  }
-
-  // first pass from the natural order in LDS (in place, padded result)
-  static __device__ __forceinline__ void pass1_lds(cx<T>* buf) {
-    cx<T> v[S1][16];
-#pragma unroll
-    for (int s = 0; s < S1; ++s) {
-      const int u = threadIdx.x + s * NT;
-      if (u < FC * P::nb1) {
-        const int f = u / P::nb1, j = u - f * P::nb1;
-        const cx<T>* src = buf + f * P::IP + j;
-#pragma unroll
-        for (int t = 0; t < 16; ++t) v[s][t] = src[t * P::nb1];
-      }
-    }
-    __syncthreads();
-    pass1_store(v, buf);
-    __syncthreads();
   }
 
   // second pass: padded order in, natural order out (in place)
@@ -376,122 +336,6 @@ __global__ __launch_bounds__(NT) void k_zonal_analysis_p3(const FftArgs1 a) {
   zonal_analysis_run_p3<T, P, NT, FB, FC, MS>(a, blockIdx.x, smem_raw);
 }
 
-template <typename T, class P, int NT, int FB, int FC, int MS>
-__device__ __forceinline__ void zonal_synthesis_run_p3(const FftArgs1& a, int item, unsigned char* smem_raw) {
-  using F3 = Fft3<T, P, NT, FC>;
-  constexpr int NRD = FB / FC, I = P::I;
-  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  cx<T>* twl = buf + FC * P::IP;
-  const LevelDesc& L = a.lev[0];
-  const int s0 = 0, end = a.nitems, n = end;
-  const T* ws = static_cast<const T*>(a.src) + L.ws_off;
-  T* grid = static_cast<T*>(a.dst) + L.grid_off;
-  const T msc = (T)a.mscale;
-  const int N = L.N, J = L.J;
-  const long long Cp = L.Cp;
-  const long long plane = L.wblk;
-
-  cx<T> stS[MS][FB], stA[MS][FB];
-  auto load_ws = [&](int slot) __attribute__((always_inline)) {
-    const int itm = xcd_map(slot - s0, n);
-    const int jp = itm / L.nfb, fb = itm - jp * L.nfb;
-    // the runs of the wave's 64 consecutive wavenumbers: a uniform base at
-    // its first wavenumber plus 32-bit lane offsets (zonal_offsets_fit)
-    const int lane = threadIdx.x & 63;
-    const unsigned lstep = (unsigned)(plane * (long long)sizeof(T));
-    const int jb = jp / SHT_K_PAD;
-    const long long odd = ws_odd(L.Jh, Cp, L.wblk, jb);
-#pragma unroll
-    for (int s = 0; s < MS; ++s) {
-      const int m = threadIdx.x + s * NT;
-      // rows below the first 128-latitude tile the Legendre synthesis
-      // computes for this m (reduced transform) are zero
-      if (m <= N && (!a.jstart || jp >= (a.jstart[L.m_base + m] & ~127))) {
-        const int mw = __builtin_amdgcn_readfirstlane(m - lane);
-        const char* wb = reinterpret_cast<const char*>(ws + jb * L.wjb + mw * plane +
-                                                       (long long)(jp % SHT_K_PAD) * Cp + 2 * fb * FB);
-        const T* sS = reinterpret_cast<const T*>(wb + (unsigned)lane * lstep);
-        load_run<T, FB>(sS, stS[s]);
-        load_run<T, FB>(sS + odd, stA[s]);
-      } else {
-#pragma unroll
-        for (int q = 0; q < FB; ++q) stS[s][q] = stA[s][q] = cx<T>{(T)0, (T)0};
-      }
-    }
-  };
-
-  if (item >= end) return;
-  F3::stage_twiddles(twl, static_cast<const cx<T>*>(L.tw));
-  load_ws(item);
-  for (; item < end; item += gridDim.x) {
-    const int itm = xcd_map(item - s0, n);
-    const int jp = itm / L.nfb, fb = itm - jp * L.nfb;
-    const bool eq = (J & 1) && (jp == (J >> 1));
-    const T rscale = row_scale<T>(a, L, jp);
-    const int next = item + (int)gridDim.x;
-
-#pragma unroll
-    for (int rd = 0; rd < NRD; ++rd) {
-#pragma unroll
-      for (int fc = 0; fc < FC; ++fc) {
-        cx<T>* bf = buf + fc * P::IP;
-        // zero the bins no thread fills: N < i < I-N
-        for (int i = N + 1 + threadIdx.x; i < I - N; i += NT) bf[i] = cx<T>{(T)0, (T)0};
-#pragma unroll
-        for (int s = 0; s < MS; ++s) {
-          const int m = threadIdx.x + s * NT;
-          if (m <= N) {
-            const cx<T> S = stS[s][rd * FC + fc], A = stA[s][rd * FC + fc];
-            const T sc = m == 0 ? (T)1 : msc;
-            cx<T> Xn = {sc * (S.x + A.x), sc * (S.y + A.y)};
-            cx<T> Xs = {sc * (S.x - A.x), sc * (S.y - A.y)};
-            if (m == 0) {
-              Xn.y = (T)0;
-              Xs.y = (T)0;
-            }
-            // conj(Z) with Z^m = Xn + i Xs and Z^{I-m} = conj(Xn) + i conj(Xs);
-            // the forward FFT of conj(Z) is the conjugate of the inverse one
-            bf[m] = cx<T>{Xn.x - Xs.y, -(Xn.y + Xs.x)};
-            if (m > 0) bf[I - m] = cx<T>{Xn.x + Xs.y, Xn.y - Xs.x};
-          }
-        }
-      }
-      __syncthreads();
-      if (rd + 1 == NRD && next < end) load_ws(next);
-      F3::pass1_lds(buf);
-      F3::pass2(buf, twl);
-      cx<T> v3[F3::S3][P::R3];
-      F3::pass3_regs(v3, buf, twl);
-#pragma unroll
-      for (int s = 0; s < F3::S3; ++s) {
-        const int u = threadIdx.x + s * NT;
-        if (u < FC * P::nb3) {
-          const int f = u / P::nb3, j = u - f * P::nb3;
-          const int fld = fb * FB + rd * FC + f;
-          if (fld < L.F) {
-            T* rn = grid + ((long long)fld * J + jp) * I + j;
-            T* rs = grid + ((long long)fld * J + (J - 1 - jp)) * I + j;
-#pragma unroll
-            for (int t = 0; t < P::R3; ++t) rn[t * P::Ns3] = rscale * v3[s][t].x;
-            if (!eq) {
-#pragma unroll
-              for (int t = 0; t < P::R3; ++t) rs[t * P::Ns3] = -rscale * v3[s][t].y;
-            }
-          }
-        }
-      }
-      __syncthreads();  // the next round refills the buffer
-    }
-  }
-}
-
-template <typename T, class P, int NT, int FB, int FC, int MS>
-__global__ __launch_bounds__(NT) void k_zonal_synthesis_p3(const FftArgs1 a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  zonal_synthesis_run_p3<T, P, NT, FB, FC, MS>(a, blockIdx.x, smem_raw);
-}
-
-
 // ---------------------------------------------------------------------------
 // Multi-level plans in one launch.  A configuration says how a level runs:
 // with a compile-time three-pass plan (ZGrp) or with runtime radices (ZRt).
@@ -570,7 +414,7 @@ static void lds_optin(size_t bytes) {
 
 static int g_num_cu = 0;
 
-template <typename T, class P, int NT, int FB, int FC, int MS, bool ANA>
+template <typename T, class P, int NT, int FB, int FC, int MS>
 static hipError_t launch_p3_ms(const FftArgs1& a, hipStream_t st) {
   const size_t lds = (size_t)(FC * P::IP + P::ntw) * sizeof(cx<T>);
   int per_cu = (int)(kMaxLds / lds);
@@ -580,29 +424,24 @@ static hipError_t launch_p3_ms(const FftArgs1& a, hipStream_t st) {
   int nwg = g_num_cu * per_cu;
   nwg = nwg < a.nitems ? nwg : a.nitems;
   const dim3 grid(nwg), block(NT);
-  if constexpr (ANA) {
-    lds_optin<k_zonal_analysis_p3<T, P, NT, FB, FC, MS>>(lds);
-    hipLaunchKernelGGL((k_zonal_analysis_p3<T, P, NT, FB, FC, MS>), grid, block, lds, st, a);
-  } else {
-    lds_optin<k_zonal_synthesis_p3<T, P, NT, FB, FC, MS>>(lds);
-    hipLaunchKernelGGL((k_zonal_synthesis_p3<T, P, NT, FB, FC, MS>), grid, block, lds, st, a);
-  }
+  lds_optin<k_zonal_analysis_p3<T, P, NT, FB, FC, MS>>(lds);
+  hipLaunchKernelGGL((k_zonal_analysis_p3<T, P, NT, FB, FC, MS>), grid, block, lds, st, a);
   return hipGetLastError();
 }
 
 // Two fields per round (four spill registers and cost ~5 %) on 512 threads.
-template <typename T, int FB, bool ANA, class P>
+template <typename T, int FB, class P>
 static hipError_t launch_p3(const FftArgs1& a, int maxN, hipStream_t st) {
   constexpr int NT = 512, FC = 2;
   constexpr int MSMAX = ((P::I + 1) / 2 + NT - 1) / NT;  // N + 1 <= (I + 1) / 2
   static_assert(MSMAX == 3, "wavenumbers per thread");
   const int nm = maxN + 1;
   if (nm > 2 * NT) {
-    if constexpr (sizeof(T) == 8 && (!ANA || P::I == 2160)) return hipErrorInvalidValue;  // (held_takes: not taken)
-    else return launch_p3_ms<T, P, NT, FB, FC, 3, ANA>(a, st);
+    if constexpr (sizeof(T) == 8 && P::I == 2160) return hipErrorInvalidValue;  // (held_takes: not taken)
+    else return launch_p3_ms<T, P, NT, FB, FC, 3>(a, st);
   }
-  if (nm > NT) return launch_p3_ms<T, P, NT, FB, FC, 2, ANA>(a, st);
-  return launch_p3_ms<T, P, NT, FB, FC, 1, ANA>(a, st);
+  if (nm > NT) return launch_p3_ms<T, P, NT, FB, FC, 2>(a, st);
+  return launch_p3_ms<T, P, NT, FB, FC, 1>(a, st);
 }
 
 // The levels that held_takes gives to the register-held kernels.  FP64
@@ -610,26 +449,21 @@ static hipError_t launch_p3(const FftArgs1& a, int maxN, hipStream_t st) {
 // 12 values of the last pass, not 15 (2880, 64 fields, 1919 rows: 1567 us with
 // radix 15 last, 102 spills; 1172 with 6).  Spills at two / three wavenumbers
 // per thread: FP64 analysis 0..10 / 13..48 registers, the others none.
-template <typename T, int FB, bool ANA>
+template <typename T, int FB>
 static bool launch_held(const FftArgs1& a, int maxN, hipStream_t st, hipError_t* err) {
-  if (!held_takes(sizeof(T) == 8, ANA, a.lev[0], g_num_cu)) return false;
-  if constexpr (sizeof(T) == 8 && !ANA) {
-    *err = launch_p3<T, FB, ANA, Plan3<2880, 12, 15>>(a, maxN, st);
-    return true;
-  } else if constexpr (ANA) {
-    constexpr bool dbl = sizeof(T) == 8;
-    switch (a.lev[0].I) {
-      case 2160: *err = launch_p3<T, FB, ANA, Plan3<2160, dbl ? 15 : 9, dbl ? 9 : 15>>(a, maxN, st); return true;
-      case 2304: *err = launch_p3<T, FB, ANA, Plan3<2304, 12, 12>>(a, maxN, st); return true;
-      case 2400: *err = launch_p3<T, FB, ANA, Plan3<2400, dbl ? 15 : 10, dbl ? 10 : 15>>(a, maxN, st); return true;
-      case 2560: *err = launch_p3<T, FB, ANA, Plan3<2560, 16, 10>>(a, maxN, st); return true;
-      case 2880: *err = launch_p3<T, FB, ANA, Plan3<2880, dbl ? 15 : 12, dbl ? 12 : 15>>(a, maxN, st); return true;
-      case 3072:
-        if constexpr (!dbl) {
-          *err = launch_p3<T, FB, ANA, Plan3<3072, 16, 12>>(a, maxN, st);
-          return true;
-        }
-    }
+  if (!held_takes(sizeof(T) == 8, a.lev[0])) return false;
+  constexpr bool dbl = sizeof(T) == 8;
+  switch (a.lev[0].I) {
+    case 2160: *err = launch_p3<T, FB, Plan3<2160, dbl ? 15 : 9, dbl ? 9 : 15>>(a, maxN, st); return true;
+    case 2304: *err = launch_p3<T, FB, Plan3<2304, 12, 12>>(a, maxN, st); return true;
+    case 2400: *err = launch_p3<T, FB, Plan3<2400, dbl ? 15 : 10, dbl ? 10 : 15>>(a, maxN, st); return true;
+    case 2560: *err = launch_p3<T, FB, Plan3<2560, 16, 10>>(a, maxN, st); return true;
+    case 2880: *err = launch_p3<T, FB, Plan3<2880, dbl ? 15 : 12, dbl ? 12 : 15>>(a, maxN, st); return true;
+    case 3072:
+      if constexpr (!dbl) {
+        *err = launch_p3<T, FB, Plan3<3072, 16, 12>>(a, maxN, st);
+        return true;
+      }
   }
   return false;
 }
@@ -642,7 +476,7 @@ static bool launch_fixed(bool analysis, const FftArgs& a, int maxN, hipStream_t 
   // from a per-wave base
   if (!zonal_offsets_fit(a.lev[0].wblk, sizeof(T))) return false;
   const FftArgs1 o = one_level(a);
-  if (analysis ? launch_held<T, FB, true>(o, maxN, st, err) : launch_held<T, FB, false>(o, maxN, st, err)) return true;
+  if (analysis && launch_held<T, FB>(o, maxN, st, err)) return true;
   const int e = sizeof(T) == 8 ? (analysis ? launch_zonal_group_analysis_f64(o, g_num_cu, st)
                                            : launch_zonal_group_synthesis_f64(o, g_num_cu, st))
                                : (analysis ? launch_zonal_group_analysis_f32(o, g_num_cu, st)

@@ -196,15 +196,15 @@ inline bool group_takes(int fc, const LevelDesc& L, int ncu) {
   return 2 * fc <= 3 * L.F || (long long)L.Jh * ((L.F + fc - 1) / fc) < ncu;
 }
 
-// Whether a level goes to the register-held kernels of sht_fft.hip (8 fields
-// per item in FP32, 4 in FP64, lengths 2160..3072) rather than to the group
-// kernel.  Those hold 4 (2) fields there and write the analysis workspace in
-// 32-byte pieces, which costs once the workspace no longer fits the 256 MB of
-// memory-side cache; the held kernels write whole 64-byte runs, but have half
-// the items, work through 8 (4) fields whether they exist or not, and spill in
-// FP64 from 1024 wavenumbers on.  Both sides measured (us, group / held; ws =
-// bytes of workspace):
-//  FP32 analysis, from 120 MB where Cp is a multiple of 128, from 400 MB
+// Whether the analysis of a level goes to the register-held kernels of
+// sht_fft.hip (8 fields per item in FP32, 4 in FP64, lengths 2160..3072)
+// rather than to the group kernel.  Those hold 4 (2) fields there and write
+// the workspace in 32-byte pieces, which costs once it no longer fits the 256
+// MB of memory-side cache; the held kernels write whole 64-byte runs, but have
+// half the items, work through 8 (4) fields whether they exist or not, and
+// spill in FP64 from 1024 wavenumbers on.  Both sides measured (us, group /
+// held; ws = bytes of workspace):
+//  FP32, from 120 MB where Cp is a multiple of 128, from 400 MB
 //   elsewhere, and from 250 MB below 2560 in the first case only:
 //   2880, 1919 rows, 64 fields 710 / 579, 32 fields 313 / 300; 3072, 2049
 //   rows, 64 fields 847 / 634, 128 rows, 128 fields (134 MB) 119 / 109; 2880,
@@ -212,31 +212,27 @@ inline bool group_takes(int fc, const LevelDesc& L, int ncu) {
 //   fields (252 MB) 200 / 185, N = 1151, 641 rows, 64 fields 240 / 208; 2160,
 //   64 and 128 fields up to 240 MB 6-17 % longer; 2160..2400 with 96 fields
 //   (Cp = 192) 3-12 % longer at any size.
-//  FP64 analysis, where Cp is a multiple of 128 from 90 MB, else of 64 from
+//  FP64, where Cp is a multiple of 128 from 90 MB, else of 64 from
 //   230 MB; at three wavenumbers per thread the former from 400 MB and not at
 //   2160: 2880, 1919 rows, 64 fields 1473 / 1164, 32 fields 702 / 597; 2304,
 //   128 rows, 64 fields 79 / 67; 2880, N = 1439, 641 rows, 64 fields 659 / 581,
 //   32 fields 314 / 312; 2160, N = 1079, 641 rows, 128 fields 832 / 983; few
 //   fields or rows (2880, 641 rows, 8 fields) 63 / 82.  3072, where the runs
 //   spill at two wavenumbers too, gains nothing (1745 / 1697, else equal).
-//  FP64 synthesis only at 2880 below 1024 wavenumbers, where whole rounds of
-//   the persistent workgroups come out equal (a held item does the work of two
-//   group items; 3-5 % shorter up to 16 rounds, 1 % from 48 on, and 1-5 %
-//   longer between): 641 rows, 12 fields 96 / 91; 1919 rows, 64 fields 1356 /
-//   1343; N = 1439 (spills) 587 / 662; 2160..2560 and 3072 2-40 % longer.
-inline bool held_takes(bool dbl, bool analysis, const LevelDesc& L, int ncu) {
+//  No synthesis: beside the group kernels that hold the reduced transform's
+//   limits, 2880, FP64, N = 959, 1919 rows, 64 fields 1337 / 1350, N = 639
+//   1124 / 1232, N = 300 809 / 910; only with up to 16 items of 4 fields per
+//   unit and N >= 959 up to 5 % shorter (511 rows, 16 fields, N = 1023 96 /
+//   92, N = 959 92.5 / 91.9).
+inline bool held_takes(bool dbl, const LevelDesc& L) {
   const int I = L.I;
   if (I != 2160 && I != 2304 && I != 2400 && I != 2560 && I != 2880 && I != 3072) return false;
   const double ws = 2.0 * L.Jh * (L.N + 1) * L.Cp * (dbl ? 8 : 4);
   const bool c128 = L.Cp % 128 == 0;
-  if (!dbl) return analysis && (c128 ? ws >= (I >= 2560 ? 120e6 : 250e6) : I >= 2560 && ws >= 400e6);
-  if (analysis) {
-    if (I == 3072) return false;
-    if (L.N >= 1024) return c128 && I > 2160 && ws >= 400e6;
-    return c128 ? ws >= 90e6 : L.Cp % 64 == 0 && ws >= 230e6;
-  }
-  auto rounds = [&](int fc) { return ((long long)L.Jh * ((L.F + fc - 1) / fc) + ncu - 1) / ncu; };
-  return I == 2880 && L.N < 1024 && 2 * rounds(4) <= rounds(2) && (rounds(2) <= 16 || rounds(2) >= 48);
+  if (!dbl) return c128 ? ws >= (I >= 2560 ? 120e6 : 250e6) : I >= 2560 && ws >= 400e6;
+  if (I == 3072) return false;
+  if (L.N >= 1024) return c128 && I > 2160 && ws >= 400e6;
+  return c128 ? ws >= 90e6 : L.Cp % 64 == 0 && ws >= 230e6;
 }
 
 // Whether a level of a multi-level plan shares the any-length launch with

@@ -161,49 +161,33 @@ static void check_group_rule() {
 // held.
 static void check_held_rule() {
   struct {
-    bool dbl, analysis;
+    bool dbl;
     int N, J, I, F, Cp;
     bool takes;
   } const rows[] = {
-      {false, true, 959, 1919, 2880, 64, 128, true},    // 710, 579
-      {false, true, 959, 1919, 2880, 32, 64, true},     // 313, 300
-      {false, true, 1023, 2049, 3072, 64, 128, true},   // 847, 634
-      {false, true, 719, 641, 2160, 1, 16, false},      // one field of eight, 1.9 times as long
-      {false, true, 960, 641, 2880, 8, 16, false},      // 37, 52
-      {false, true, 1024, 128, 3072, 128, 256, true},   // 119, 109
-      {false, true, 719, 641, 2160, 64, 128, false},    // 1.12 times as long
-      {false, true, 799, 641, 2400, 96, 192, false},    // 1.06
-      {false, true, 767, 33, 2304, 64, 128, false},     // 1.13
-      {false, false, 959, 1919, 2880, 64, 128, false},  // no held synthesis
-      {true, true, 959, 1919, 2880, 64, 128, true},     // 1473, 1164
-      {true, true, 767, 128, 2304, 64, 128, true},      // 79, 67
-      {true, true, 1439, 641, 2880, 64, 128, true},     // 659, 581
-      {true, true, 1439, 641, 2880, 12, 32, false},     // 94, 118
-      {true, true, 1079, 641, 2160, 128, 256, false},   // 832, 983
-      {true, true, 1023, 2049, 3072, 64, 128, false},   // 1745, 1697: spills
-      {true, true, 959, 33, 2880, 64, 128, false},      // 1.26
-      {true, false, 959, 1919, 2880, 64, 128, true},    // 1356, 1343
-      {true, false, 719, 641, 2880, 12, 32, true},      // 96, 91
-      {true, false, 719, 641, 2880, 4, 16, false},      // 1.21
-      {true, false, 1439, 641, 2880, 64, 128, false},   // 587, 662
-      {true, false, 1199, 641, 2400, 64, 128, false},   // 478, 544
-      {true, false, 1023, 641, 3072, 64, 128, false},   // 1.06
+      {false, 959, 1919, 2880, 64, 128, true},    // 710, 579
+      {false, 959, 1919, 2880, 32, 64, true},     // 313, 300
+      {false, 1023, 2049, 3072, 64, 128, true},   // 847, 634
+      {false, 719, 641, 2160, 1, 16, false},      // one field of eight, 1.9 times as long
+      {false, 960, 641, 2880, 8, 16, false},      // 37, 52
+      {false, 1024, 128, 3072, 128, 256, true},   // 119, 109
+      {false, 719, 641, 2160, 64, 128, false},    // 1.12 times as long
+      {false, 799, 641, 2400, 96, 192, false},    // 1.06
+      {false, 767, 33, 2304, 64, 128, false},     // 1.13
+      {true, 959, 1919, 2880, 64, 128, true},     // 1473, 1164
+      {true, 767, 128, 2304, 64, 128, true},      // 79, 67
+      {true, 1439, 641, 2880, 64, 128, true},     // 659, 581
+      {true, 1439, 641, 2880, 12, 32, false},     // 94, 118
+      {true, 1079, 641, 2160, 128, 256, false},   // 832, 983
+      {true, 1023, 2049, 3072, 64, 128, false},   // 1745, 1697: spills
+      {true, 959, 33, 2880, 64, 128, false},      // 1.26
   };
   for (const auto& r : rows) {
     LevelDesc L = level(r.J, r.I, r.F);
     L.N = r.N;
     L.Cp = r.Cp;
-    CHECK(held_takes(r.dbl, r.analysis, L, kCu) == r.takes, "dbl %d analysis %d N %d J %d I %d F %d", r.dbl, r.analysis,
-          r.N, r.J, r.I, r.F);
+    CHECK(held_takes(r.dbl, L) == r.takes, "dbl %d N %d J %d I %d F %d", r.dbl, r.N, r.J, r.I, r.F);
   }
-  // never three wavenumbers per thread in the FP64 synthesis (not built)
-  for (int F = 1; F < 200; ++F)
-    for (int J = 2; J < 3000; J += 97) {
-      LevelDesc L = level(J, 2880, F);
-      L.N = 1024;
-      L.Cp = (2 * F + 15) / 16 * 16;
-      CHECK(!held_takes(true, false, L, kCu), "J %d F %d", J, F);
-    }
 }
 
 // One launch over all levels by default (I = 100 2^k, J = 64 2^k + 1): FP64
