@@ -70,8 +70,8 @@ def test_few_items(form, I, N, J, F):
     _check(N, J, I, F, form, kind="cc_poles", adjoints=I < 960)
 
 
-# FP64 synthesis on the register-held kernels: one and two wavenumbers per
-# thread, whole rounds of both kernels (17 row pairs: 255 and 510 items)
+# FP64 synthesis at 2880 with items for more than one round (17 row pairs: 510
+# items of 2 fields), few and many wavenumbers
 @pytest.mark.parametrize("N", [300, 1023])
-def test_held_synthesis(N):
+def test_long_rows(N):
     _check(N, 33, 2880, 60, "fp64", adjoints=N < 1000)
